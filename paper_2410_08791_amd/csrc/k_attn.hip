@@ -203,9 +203,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_kernel(const bf16_t* __re
     // Causal: query block i walks the key tiles up to its own diagonal.  With `paired` a work-group
     // takes the blocks nqb - 1 - i and i one after the other, so that every work-group has the same
     // amount of work (gridDim.x = ceil(nqb / 2)); the launcher asks for that when it still leaves two
-    // work-groups per CU.  Otherwise one block per work-group: ids are dealt to the CUs in
-    // order, two resident per CU, and every other batch of 256 ids walks the query blocks in
-    // the opposite direction, so a CU holds one heavy and one light block.
+    // work-groups per CU.  Otherwise one block per work-group: an XCD's ids are dealt to its 32 CUs
+    // in order, two resident per CU, and the heads of every other 32 jobs walk their query blocks in
+    // the opposite direction, so a CU holds one heavy and one light block.  (The direction is a
+    // property of the whole head: taken from the work-group's own id, two blocks of a head that lie
+    // on either side of a batch of ids could pick the same query block and leave another out.)
     const int nqb = (S + QB - 1) / QB;
     // The hardware deals consecutive work-group ids round-robin over the 8 XCDs, each with its own
     // L2.  Ids are remapped so that an XCD works through a contiguous range of (batch, head, query
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_kernel(const bf16_t* __re
     }
     for (int phase = 0; phase < nphase; ++phase) {
     const int qb = paired ? (phase ? bx : nqb - 1 - bx)                          // heavy block first
-                          : (!causal || ((lin >> 8) & 1)) ? bx : nqb - 1 - bx;
+                          : (!causal || (((job - bx) >> 5) & 1)) ? bx : nqb - 1 - bx;
     const int q0 = qb * QB;
     const int wq0 = q0 + wave * 32;          // this wave's first query
     const int qi = wq0 + l32;                // this lane's query

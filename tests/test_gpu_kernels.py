@@ -274,6 +274,27 @@ def test_attention(B, S, Hq, Hkv, hd, causal):
     np.testing.assert_allclose(lse.cpu().numpy(), want, rtol=0, atol=atol * max(1.0, np.abs(want).max()))
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,hd", [
+    (9, 296, 12, 3, 128),       # 324 work-groups, three blocks per head: heads straddle the batches of ids
+    (3, 777, 16, 4, 64),        # 336, seven blocks per head
+    (2, 1100, 17, 17, 80),      # 306, nine blocks per head, an odd number of heads
+])
+def test_attention_causal_writes_every_query_block(B, S, Hq, Hkv, hd):
+    """More causal work-groups than one round of the chip, too few to be paired, and heads whose blocks do
+    not divide the batches in which the walking direction alternates: every block once."""
+    rng = np.random.default_rng(S)
+    nq, nk = Hq * hd, Hkv * hd
+    qb, qkv = rand_bf16(rng, (B * S, nq + 2 * nk))
+    sh = O.StackShape(O.DECODER, 1, nq, Hq, Hkv, hd, 64, True)
+    ref = O.attention(qkv[:, :nq], qkv[:, nq:nq + nk], qkv[:, nq + nk:], B, S, sh)
+    o = torch.full((B * S, nq), 0x7FC1, dtype=torch.int16, device=DEV)      # bf16 NaN where nothing is written
+    qd = dev_u16(qb)
+    assert sp.spk_attention(stream_ptr(), ptr(qd), ptr(o), None, B, S, Hq, Hkv, hd, 1) == sp.SP_OK
+    sync()
+    got = bf16_vals(host_u16(o))
+    assert np.max(np.abs(got - ref)) <= 3 * BF16_EPS * np.max(np.abs(ref))   # as in test_attention
+
+
 def test_attention_rejects_unsupported_head_dim():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     assert sp.spk_attention(stream_ptr(), ptr(z), ptr(z), None, 1, 8, 2, 2, 48, 1) == sp.SP_ERR_INVALID_ARG
