@@ -724,8 +724,9 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& g) {
 // Tile ids: register-staged kernel 1 = 128x128, 2 = 128x256 (BM x BN), 3 = 256x256 (4 waves each),
 // 4 = 256x256 with 8 waves; LDS-DMA kernel (contraction-contiguous operands only) 5 = 256x256 and
 // 6 = 128x256 with 8 waves, 7 = 128x128 with 4 waves (two work-groups per CU), 8 = 256x192 with 8
-// waves in a 4 x 2 grid (not with the SwiGLU epilogue, which pairs tiles inside a wave); 9 = the
-// weight-streaming kernel for at most 64 activation rows (k_gemm_skinny.hip); 10 = 256x320 of the
+// waves in a 4 x 2 grid (not with the SwiGLU epilogue, which pairs tiles inside a wave); 9 =
+// at most 64 activation rows (the small-tile kernel, k_gemm_small.hip; 11, 12, 13 force its 16, 32 and
+// 64 row tiles there, 14..20 its tiles for any shape); 10 = 256x320 of the
 // LDS-DMA kernel, 4 x 2 waves (not with SwiGLU): N = 1280 is four of its columns, so the ViT-H
 // projections back to d_model are one round of 256 work-groups once the ragged rows are cut off.
 //
@@ -762,32 +763,36 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
 // The library's own choice for a shape: the tile, and when a ragged last row of 256-row tiles
 // would cost a whole extra round (ViT-H: 16448 tokens = 64 tiles + 64 rows, 1300 tiles = 5.08
 // rounds of 256) the rows beyond the last multiple of 256 become a launch of their own.
-GemmPlan plan_gemm(int epi, bool dma_ok, int M, int N) {
+GemmPlan plan_gemm(int epi, bool dma_ok, int M, int N, float* cost = nullptr) {
     GemmPlan pl{0, M, 0};
     if (!dma_ok) {
-        pl.tile = pick_tile(kRegTiles, M, N, epi);
+        pl.tile = pick_tile(kRegTiles, M, N, epi, cost);
         return pl;
     }
-    if (M <= SPK_SKINNY_MAX_ROWS) {     // a decode step: nothing of W is re-used, stream it
+    if (M <= SPK_FEW_ROWS) {     // a decode step: nothing of W is re-used, stream it
         pl.tile = 9;
         return pl;
     }
     float whole;
     pl.tile = pick_tile(kDmaTiles, M, N, epi, &whole);
+    if (cost) *cost = whole;
     const int tail = M % 256, body = M - tail;
     if (tail && body) {
         float c_body, c_tail;
         const int t_body = pick_tile(kDmaTiles, body, N, epi, &c_body);
         int t_tail;
-        if (tail <= SPK_SKINNY_MAX_ROWS) {
-            // the weight-streaming kernel in the units of pick_tile (a round of 256x256 tiles = 65536):
+        if (tail <= SPK_FEW_ROWS) {
+            // the small-tile kernel in the units of pick_tile (a round of 256x256 tiles = 65536):
             // N x K x 2 bytes at ~4.5 TB/s against 256 tiles x 2 x 65536 K flop at ~1.3 PFLOP/s, plus a launch
             t_tail = 9;
             c_tail = 1.13f * (float)N + 6000.f;
         } else {
             t_tail = pick_tile(kDmaTiles, tail, N, epi, &c_tail);
         }
-        if (c_body + c_tail < 0.97f * whole) pl = GemmPlan{t_body, body, t_tail};
+        if (c_body + c_tail < 0.97f * whole) {
+            pl = GemmPlan{t_body, body, t_tail};
+            if (cost) *cost = c_body + c_tail;
+        }
     }
     return pl;
 }
@@ -800,8 +805,23 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
     // the LDS-DMA kernel writes C (and reads R) in 16-byte pieces of a row
     const bool dma = DMA_OK && (g.ldc * CSZ) % 16 == 0;
     int tile = g.tile;
+    auto small = [&](int id) { GemmArgs t = g; t.tile = id; return spk_launch_gemm_small(st, EPI, t); };
+    if (tile == 9 || (tile >= 11 && tile <= 13)) {
+        // few rows: the small-tile kernel with its own choice of tile, or 16, 32, 64 rows per work-group
+        if (!DMA_OK || g.M > SPK_FEW_ROWS) return hipErrorInvalidValue;
+        float us;
+        return small(tile == 9 ? spk_small_gemm_tile(EPI, g.a_form, g.w_form, g.M, g.N, g.K, &us) : tile == 11 ? 14 : tile == 12 ? 16 : 17);
+    }
+    if (tile >= 14) return small(tile);
     if (!tile) {
-        const GemmPlan pl = plan_gemm(EPI, dma, g.M, g.N);
+        float small_us, large_cost;
+        const int small_id = spk_small_gemm_tile(EPI, g.a_form, g.w_form, g.M, g.N, g.K, &small_us);
+        const GemmPlan pl = plan_gemm(EPI, dma, g.M, g.N, &large_cost);
+        if (pl.tile == 9) return small(small_id);
+        // Both estimates are fits with 10-18 % error, so the small tiles have to be cheaper by a tenth:
+        // over 180 shapes of up to 2560 rows the choice is within 1 % of the better kernel on average
+        // (2.1 times as fast as the large tiles alone) and in one of them slower than the large tiles.
+        if (small_id && small_us < 0.9f * (4.5f + large_cost * (float)g.K * 4.55e-7f)) return small(small_id);
         tile = pl.tile;
         if (pl.body_rows < g.M) {
             GemmArgs a = g, b = g;
@@ -824,11 +844,7 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
         case 6: if (DMA_OK) return launch_dma<128, 256, EPI, 8, 2>(st, g); break;
         case 7: if (DMA_OK) return launch_dma<128, 128, EPI, 4, 2>(st, g); break;
         case 8: if (DMA_OK && EPI != EPI_SWIGLU_BF16) return launch_dma<256, 192, NOSWIGLU, 8, 4>(st, g); break;
-        case 9: if (DMA_OK) return spk_launch_gemm_skinny(st, EPI, g); break;
         case 10: if (DMA_OK && EPI != EPI_SWIGLU_BF16) return launch_dma<256, 320, NOSWIGLU, 8, 4>(st, g); break;
-        case 11: if (DMA_OK) return spk_launch_gemm_skinny(st, EPI, g, 16); break;
-        case 12: if (DMA_OK) return spk_launch_gemm_skinny(st, EPI, g, 32); break;
-        case 13: if (DMA_OK) return spk_launch_gemm_skinny(st, EPI, g, 64); break;
     }
     return hipErrorInvalidValue;
 }

@@ -45,19 +45,21 @@ struct GemmArgs {
     const float* R; int ldr;                // EPI_RESID_F32
     const bf16_t* bias;                     // [N] or nullptr
     int M, N, K;
-    int tile;                               // 0 = heuristic, else 1..9 = forced kernel and tile shape
+    int tile;                               // 0 = heuristic, else 1..20 = forced kernel and tile shape
 };
 
 // C[M,N] = sum_k A(m,k) W(n,k), bf16 operands, fp32 accumulate on MFMA.
 // Needs K % 64 == 0, N % 8 == 0, leading dimensions % 8 == 0, 16-byte aligned bases.
 hipError_t spk_launch_gemm(hipStream_t st, int epilogue, const GemmArgs& g);
-// The kernel for at most SPK_SKINNY_MAX_ROWS activation rows (tile id 9; both operands
-// contraction-contiguous): streams W once, 16 output columns per work-group, one to four tiles of
-// 16 rows per weight fragment.
-constexpr int SPK_SKINNY_MAX_ROWS = 64;
-hipError_t spk_launch_gemm_skinny(hipStream_t st, int epilogue, const GemmArgs& g, int rows_per_group = 0);
-// What tile = 0 resolves to for a shape (host code, no launch): rows [0, body_rows) run with
-// `tile`, rows [body_rows, M) -- none when body_rows == M -- with `tail_tile`.
+// The kernel for outputs that large tiles would spread over too few work-groups, down to the few rows
+// of a decode step (tile ids 14..20, k_gemm_small.hip).
+constexpr int SPK_FEW_ROWS = 64;
+hipError_t spk_launch_gemm_small(hipStream_t st, int epilogue, const GemmArgs& g);
+// Its cheapest tile for a shape and the estimated time in us (0: it does not take these operand forms).
+int spk_small_gemm_tile(int epilogue, int a_form, int w_form, int M, int N, int K, float* us);
+// The large-tile plan of a shape (host code, no launch): rows [0, body_rows) run with `tile`, rows
+// [body_rows, M) -- none when body_rows == M -- with `tail_tile`; tile 9 = at most SPK_FEW_ROWS rows, the small-tile
+// kernel.  A launch whose estimate the small-tile kernel undercuts runs on that one instead.
 struct GemmPlan { int tile, body_rows, tail_tile; };
 GemmPlan spk_gemm_plan_host(int epilogue, int a_form, int w_form, int M, int N);
 

@@ -115,6 +115,53 @@ def test_gemm_few_rows_streams_the_weights(epi, M, N, K, tile):
     assert np.all(np.abs(got - ref) <= tol + 1e-6), float(np.max(np.abs(got - ref)))
 
 
+@pytest.mark.parametrize("tile", [14, 15, 16, 17, 18, 19, 20])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (16, 16, 512), (97, 136, 64), (65, 264, 832), (257, 72, 1280)])
+@pytest.mark.parametrize("epi", [sp.EPI_BF16, sp.EPI_RESID_F32, sp.EPI_GELU_BF16, sp.EPI_SWIGLU_BF16, sp.EPI_F32])
+def test_gemm_small_tiles(epi, M, N, K, tile):
+    """Every tile of the small-tile kernel: one row and one column group, whole tiles, ragged rows and
+    columns; fewer k-tiles than contraction groups, a count no group count divides, many."""
+    rng = np.random.default_rng(M + N * 3 + K * 5 + epi)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (2 * N if epi == sp.EPI_SWIGLU_BF16 else N, K), 0.1)
+    bias_b, bias = (rand_bf16(rng, N, 0.5) if epi in (sp.EPI_GELU_BF16, sp.EPI_BF16, sp.EPI_RESID_F32) else (None, None))
+    R = rng.standard_normal((M, N)).astype(np.float32)
+    f32out = epi in (sp.EPI_RESID_F32, sp.EPI_F32)
+    Cd = torch.full((M + 1, N), 7.0 if f32out else 7, dtype=torch.float32 if f32out else torch.int16, device=DEV)
+    if epi == sp.EPI_RESID_F32:
+        Cd[:M] = dev_f32(R)
+    Ad, Wd = dev_u16(Ab), dev_u16(Wb)
+    bd = dev_u16(bias_b) if bias_b is not None else None
+    assert sp.spk_gemm(stream_ptr(), epi, ptr(Ad), K, 0, ptr(Wd), K, 0, ptr(Cd), N,
+                       ptr(Cd) if epi == sp.EPI_RESID_F32 else None, N, ptr(bd), M, N, K, tile) == sp.SP_OK
+    sync()
+    ref = gemm_ref(A, W, epi, R.astype(np.float64), bias, N)
+    out = Cd.cpu()
+    assert bool((out[M] == 7).all())                      # the row behind C
+    got = out[:M].numpy().astype(np.float64) if f32out else bf16_vals(host_u16(out[:M].contiguous()))
+    tol = 2e-6 * np.sqrt(K) * np.max(np.abs(ref)) + (0 if f32out else BF16_EPS * np.abs(ref))   # as in test_gemm_kmajor
+    assert np.all(np.abs(got - ref) <= tol + 1e-6), float(np.max(np.abs(got - ref)))
+
+
+@pytest.mark.parametrize("tile", [16, 18])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 64), (72, 136, 320), (264, 520, 1088)])
+def test_gemm_small_tiles_transposed_operands(M, N, K, tile):
+    """The backward forms on the small-tile kernel: W, and both operands, with the row index contiguous."""
+    rng = np.random.default_rng(M * 3 + N + K + tile)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (N, K), 0.1)
+    Ad, ATd, WTd = dev_u16(Ab), dev_u16(Ab.T), dev_u16(Wb.T)
+    C1 = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    C2 = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    assert sp.spk_gemm(stream_ptr(), sp.EPI_F32, ptr(Ad), K, 0, ptr(WTd), N, 1, ptr(C1), N, None, 0, None, M, N, K, tile) == sp.SP_OK
+    assert sp.spk_gemm(stream_ptr(), sp.EPI_F32, ptr(ATd), M, 1, ptr(WTd), N, 1, ptr(C2), N, None, 0, None, M, N, K, tile) == sp.SP_OK
+    sync()
+    ref = A @ W.T
+    tol = 2e-6 * np.sqrt(K) * np.max(np.abs(ref))
+    for C_ in (C1, C2):
+        assert np.all(np.abs(C_.cpu().numpy() - ref) <= tol)
+
+
 def test_gemm_few_rows_kernel_refuses_what_it_cannot_take():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     f = torch.zeros(1 << 14, dtype=torch.float32, device=DEV)
