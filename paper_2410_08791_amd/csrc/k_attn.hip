@@ -386,6 +386,7 @@ hipError_t launch_hd(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, c
 
 hipError_t spk_launch_attention(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, const AttnShape& a) {
     if (a.B <= 0 || a.S <= 0) return hipSuccess;
+    if (a.kt) return spk_launch_decode_step(st, qkv, o, a);
     if (a.Hkv <= 0 || a.Hq % a.Hkv || a.ld_qkv % 8 || a.B > 65535 || a.Hq > 65535) return hipErrorInvalidValue;
     if (((uintptr_t)qkv | (uintptr_t)o) & 15) return hipErrorInvalidValue;
     const float sl2 = 1.4426950408889634f / sqrtf((float)a.hd);

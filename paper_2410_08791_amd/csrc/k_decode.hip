@@ -34,138 +34,282 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict
         for (int d = threadIdx.x >> 6; d < hd; d += 4) kdst[(size_t)d * max_len + s] = tile[s][d];
 }
 
-// One work-group = one (query head, sequence): scores over n cached positions, softmax in
-// fp32, weighted sum of V.  Every load is 16 bytes per lane and eight or more are in flight
-// per lane: with one work-group per (head, sequence) the kernel is bound by memory latency,
-// not bandwidth (4-byte loads four deep took 34 us for 8 x 32 heads over 520 positions).
-// Scores: the cache is walked in chunks of 512 positions; a lane owns 8 consecutive positions
-// (one 16-byte piece of a Kt row), the four waves split the head dimension, and their partial
-// dot products meet in LDS.  Weighted sum: a lane owns 8 consecutive head-dimension elements
-// of a V row, a wave 512 / HD rows per step; the partial sums of the waves' row groups meet in
-// LDS.  Both reductions add in a fixed order.
-// Dynamic LDS (floats): n_pad probabilities | HD query | 8 | 4 x 512 score partials | 2048 output partials.
-template <int HD>
-__global__ __launch_bounds__(256) void decode_attn_kernel(const bf16_t* __restrict__ qkv, int ld_qkv,
-                                                          const bf16_t* __restrict__ kt, const bf16_t* __restrict__ v,
-                                                          bf16_t* __restrict__ o, int ld_o, int n, int n_pad,
-                                                          int max_len, int Hq, int Hkv, float scale) {
-    extern __shared__ float smem[];
-    constexpr int DW = HD / 4;             // head-dimension elements per wave in the score pass
+// Attention of one query per sequence over the cached positions [0, n), and (fresh) over the position n
+// whose key and value are still in the fused activation: they are taken from there and stored into the
+// cache by the way, so a decode step needs no append launch in front.
+//
+// One work-group = one split of the positions for one key/value head and G of the query heads that
+// share it: a cached byte is read once for all G (one work-group per query head read a group's cache
+// Hq / Hkv times and left most of the chip idle for few sequences: 2 x 32/8 heads over 8191 positions
+// 107 us).  Each of the eight waves walks its own run of positions, 128 at a time, with its own running
+// maximum, sum and output, and needs no barrier before the end: a lane holds 8 positions (16 bytes of a
+// Kt row), the quarter-waves split the head dimension and add up by two shuffles, so every load is 16
+// bytes and 16 (keys) or 8 (values) of them are in flight per lane.  The waves' results meet in LDS.  With
+// more than one split the unnormalised rows go to `part` (fp32: HD values, reference maximum in base 2,
+// denominator) and combine_kernel adds them in split order.
+// HBM-bound: 4 n Hkv hd bytes per sequence.
+constexpr int DEC_WAVES = 8;
+
+template <int HD, int G>
+__global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
+    const bf16_t* __restrict__ qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* __restrict__ o, int ld_o,
+    float* __restrict__ part, int n, int fresh, int per_split, int max_len, int Hq, int Hkv, float scale_log2e) {
+    constexpr int DQ = HD / 4;             // head-dimension elements per quarter-wave in the score pass
     constexpr int LPR = HD / 8;            // lanes per V row
-    constexpr int RPW = 64 / LPR;          // V rows per wave and step
-    float* sc = smem;
-    float* qs = sc + n_pad;
-    float* red = qs + HD;
-    float* scp = red + 8;                  // [4][512]
-    float* part = scp + 4 * 512;           // [4 * RPW][HD]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int hq = blockIdx.x, b = blockIdx.y, hk = hq / (Hq / Hkv);
-    if (tid < HD) qs[tid] = bf2f(qkv[(size_t)b * ld_qkv + hq * HD + tid]) * scale;
+    constexpr int RPI = 64 / LPR;          // V rows per load instruction
+    constexpr int TB = 128;                // positions per wave and step
+    constexpr int KBATCH = G == 8 ? 8 : DQ < 16 ? DQ : 16, VBATCH = G == 8 ? 4 : 8;
+    __shared__ float qs[G][HD];
+    __shared__ __attribute__((aligned(16))) float buf[DEC_WAVES * G * TB];   // a wave's probabilities, then its output rows
+    __shared__ float wm[DEC_WAVES][G], wl[DEC_WAVES][G];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = Hq / Hkv, ngb = (grp + G - 1) / G;
+    const int split = blockIdx.x, hk = blockIdx.y / ngb, h0 = (blockIdx.y % ngb) * G, b = blockIdx.z;
+    const bf16_t* row = qkv + (size_t)b * ld_qkv;
+    for (int i = threadIdx.x; i < G * HD; i += DEC_WAVES * 64) {
+        const int g = i / HD, h = min(h0 + g, grp - 1);       // heads past the group repeat its last one and are not stored
+        qs[g][i % HD] = bf2f(row[(size_t)(hk * grp + h) * HD + i % HD]) * scale_log2e;
+    }
     __syncthreads();
 
-    // scores.  max_len is a multiple of 8, so a lane's 8 positions lie inside the cache row even
-    // when some of them are not among the n valid ones (those are never stored).
-    const bf16_t* K = kt + (size_t)(b * Hkv + hk) * HD * max_len + (size_t)w * DW * max_len;
-    float mx = -INFINITY;
-    for (int c0 = 0; c0 < n; c0 += 512) {
-        const int t = c0 + lane * 8;
-        float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (t < n) {
-            // all of the lane's loads first, then the arithmetic (left to itself the compiler pairs
-            // every load with its use and waits for each in turn)
-            constexpr int DB = DW < 16 ? DW : 16;
+    bf16_t* K = kt + (size_t)(b * Hkv + hk) * HD * max_len;
+    bf16_t* V = v + (size_t)(b * Hkv + hk) * max_len * HD;
+    const int per_wave = (per_split / DEC_WAVES + 7) & ~7;
+    const int s1 = min(n, (split + 1) * per_split);
+    const int w0 = split * per_split + w * per_wave, w1 = min(s1, w0 + per_wave);
+    const int qw = lane >> 4, l16 = lane & 15;
+    const int vrow = lane / LPR, dp = 8 * (lane % LPR);
+    float m[G], l[G], oa[G][8];
 #pragma unroll
-            for (int d0 = 0; d0 < DW; d0 += DB) {
-                u32x4_t kk[DB];
+    for (int g = 0; g < G; ++g) {
+        m[g] = -INFINITY; l[g] = 0.f;
 #pragma unroll
-                for (int d = 0; d < DB; ++d) kk[d] = *reinterpret_cast<const u32x4_t*>(K + (size_t)(d0 + d) * max_len + t);
+        for (int e = 0; e < 8; ++e) oa[g][e] = 0.f;
+    }
+    float* ps = buf + w * G * TB;          // [position][G]
+    for (int t0 = w0; t0 < w1; t0 += TB) {
+        // scores.  max_len is a multiple of 8, so a lane's 8 positions lie inside the cache row.
+        const int t = t0 + l16 * 8;
+        float a[G][8];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[g][e] = 0.f;
+        if (t < w1) {
+#pragma unroll
+            for (int d0 = 0; d0 < DQ; d0 += KBATCH) {
+                u32x4_t kk[KBATCH];
+#pragma unroll
+                for (int d = 0; d < KBATCH; ++d)
+                    kk[d] = *reinterpret_cast<const u32x4_t*>(K + (size_t)(qw * DQ + d0 + d) * max_len + t);
+                __builtin_amdgcn_sched_barrier(0);      // all loads first: paired with their uses each would be waited for
+#pragma unroll
+                for (int d = 0; d < KBATCH; ++d)
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const float q = qs[g][qw * DQ + d0 + d];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            a[g][2 * e] = fmaf(q, bf_lo(kk[d][e]), a[g][2 * e]);
+                            a[g][2 * e + 1] = fmaf(q, bf_hi(kk[d][e]), a[g][2 * e + 1]);
+                        }
+                    }
                 __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // this step's first value rows are fetched under the softmax
+        const int rows = min(TB, w1 - t0);
+        u32x4_t vv[VBATCH];
 #pragma unroll
-                for (int d = 0; d < DB; ++d) {
-                    const float q = qs[w * DW + d0 + d];
-                    a[0] = fmaf(q, bf_lo(kk[d][0]), a[0]); a[1] = fmaf(q, bf_hi(kk[d][0]), a[1]);
-                    a[2] = fmaf(q, bf_lo(kk[d][1]), a[2]); a[3] = fmaf(q, bf_hi(kk[d][1]), a[3]);
-                    a[4] = fmaf(q, bf_lo(kk[d][2]), a[4]); a[5] = fmaf(q, bf_hi(kk[d][2]), a[5]);
-                    a[6] = fmaf(q, bf_lo(kk[d][3]), a[6]); a[7] = fmaf(q, bf_hi(kk[d][3]), a[7]);
+        for (int j = 0; j < VBATCH; ++j)
+            vv[j] = *reinterpret_cast<const u32x4_t*>(V + (size_t)min(t0 + j * RPI + vrow, w1 - 1) * HD + dp);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float x = a[g][e];
+                x += __shfl_xor(x, 16, 64);
+                x += __shfl_xor(x, 32, 64);
+                x = t + e < w1 ? x : -INFINITY;
+                a[g][e] = x;
+                mx = fmaxf(mx, x);
+            }
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+            const float mn = fmaxf(m[g], mx);            // finite: position t0 is valid
+            const float alpha = __builtin_amdgcn_exp2f(m[g] - mn);
+            m[g] = mn;
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                a[g][e] = __builtin_amdgcn_exp2f(a[g][e] - mn);
+                sum += a[g][e];
+            }
+            l[g] = l[g] * alpha + sum;                   // of this lane's positions
+#pragma unroll
+            for (int e = 0; e < 8; ++e) oa[g][e] *= alpha;
+            if (qw == (g & 3))
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ps[(l16 * 8 + e) * G + g] = a[g][e];
+        }
+        __builtin_amdgcn_wave_barrier();
+        // weighted sum: row groups of RPI value rows; a wave's LDS accesses are in order
+        for (int r0 = 0; r0 < rows; r0 += VBATCH * RPI) {
+            if (r0) {
+#pragma unroll
+                for (int j = 0; j < VBATCH; ++j)
+                    vv[j] = *reinterpret_cast<const u32x4_t*>(V + (size_t)min(t0 + r0 + j * RPI + vrow, w1 - 1) * HD + dp);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int j = 0; j < VBATCH; ++j) {
+                const int r = r0 + j * RPI + vrow;       // < TB; positions past the run have probability 0
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float p = ps[r * G + g];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        oa[g][2 * e] = fmaf(p, bf_lo(vv[j][e]), oa[g][2 * e]);
+                        oa[g][2 * e + 1] = fmaf(p, bf_hi(vv[j][e]), oa[g][2 * e + 1]);
+                    }
                 }
-                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (fresh && split == (int)gridDim.x - 1 && w == DEC_WAVES - 1) {
+        // the new position: scored and added like a run of one, and stored (by the first head block)
+        const bf16_t* kn = row + (size_t)(Hq + hk) * HD;
+        const bf16_t* vn = kn + (size_t)Hkv * HD;
+        constexpr int EPL = HD / 64;
+        const u32x4_t nv = *reinterpret_cast<const u32x4_t*>(vn + dp);
+        bf16_t kb[EPL];
+        float kf[EPL];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) scp[w * 512 + lane * 8 + e] = a[e];
-        __syncthreads();
+        for (int e = 0; e < EPL; ++e) { kb[e] = kn[lane + 64 * e]; kf[e] = bf2f(kb[e]); }
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int i = tid * 2 + e;
-            if (c0 + i < n) {
-                const float sv = (scp[i] + scp[512 + i]) + (scp[1024 + i] + scp[1536 + i]);
-                sc[c0 + i] = sv;
-                mx = fmaxf(mx, sv);
+        for (int g = 0; g < G; ++g) {
+            float s = 0.f;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) s = fmaf(qs[g][lane + 64 * e], kf[e], s);
+            s = wave_sum(s);
+            const float mn = fmaxf(m[g], s), alpha = __builtin_amdgcn_exp2f(m[g] - mn), p = __builtin_amdgcn_exp2f(s - mn);
+            m[g] = mn;
+            l[g] = l[g] * alpha + (l16 == 0 ? p : 0.f);
+            const float pr = vrow == 0 ? p : 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                oa[g][2 * e] = fmaf(pr, bf_lo(nv[e]), oa[g][2 * e] * alpha);
+                oa[g][2 * e + 1] = fmaf(pr, bf_hi(nv[e]), oa[g][2 * e + 1] * alpha);
             }
         }
-        __syncthreads();                   // scp is rewritten by the next chunk
+        if (h0 == 0) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) K[(size_t)(lane + 64 * e) * max_len + n] = kb[e];
+            if (vrow == 0) *reinterpret_cast<u32x4_t*>(V + (size_t)n * HD + dp) = nv;
+        }
     }
-    mx = wave_max(mx);
-    if (lane == 0) red[w] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float sum = 0.f;
-    for (int t = tid; t < n; t += 256) {
-        const float p = __expf(sc[t] - mx);
-        sc[t] = p;
-        sum += p;
-    }
-    sum = block_sum_256(sum, red + 4);     // its barriers also publish the probabilities
 
-    // weighted sum: wave w, row group g take keys t = (w * RPW + g) + 4 * RPW * j
-    const bf16_t* V = v + (size_t)(b * Hkv + hk) * max_len * HD;
-    const int g = lane / LPR, dp = 8 * (lane % LPR);
-    float oa[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    constexpr int VB = 8;                  // V rows of a lane in flight
-    for (int t0 = w * RPW + g; t0 < n; t0 += VB * 4 * RPW) {
-        u32x4_t vv[VB];
-        float pr[VB];
+    // a wave's row groups, then the waves, in a fixed order
 #pragma unroll
-        for (int j = 0; j < VB; ++j) {
-            const int t = t0 + j * 4 * RPW;
-            vv[j] = *reinterpret_cast<const u32x4_t*>(V + (size_t)min(t, n - 1) * HD + dp);
-            pr[j] = t < n ? sc[t] : 0.f;
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int g = 0; g < G; ++g) {
 #pragma unroll
-        for (int j = 0; j < VB; ++j) {
-            const float p = pr[j];
-            oa[0] = fmaf(p, bf_lo(vv[j][0]), oa[0]); oa[1] = fmaf(p, bf_hi(vv[j][0]), oa[1]);
-            oa[2] = fmaf(p, bf_lo(vv[j][1]), oa[2]); oa[3] = fmaf(p, bf_hi(vv[j][1]), oa[3]);
-            oa[4] = fmaf(p, bf_lo(vv[j][2]), oa[4]); oa[5] = fmaf(p, bf_hi(vv[j][2]), oa[5]);
-            oa[6] = fmaf(p, bf_lo(vv[j][3]), oa[6]); oa[7] = fmaf(p, bf_hi(vv[j][3]), oa[7]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int off = 1; off < 16; off <<= 1) l[g] += __shfl_xor(l[g], off, 64);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int off = LPR; off < 64; off <<= 1) oa[g][e] += __shfl_xor(oa[g][e], off, 64);
     }
+    __syncthreads();                       // buf changes hands
+    if (vrow == 0)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[(w * RPW + g) * HD + dp + e] = oa[e];
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) buf[(w * G + g) * HD + dp + e] = oa[g][e];
+    if (lane == 0)
+#pragma unroll
+        for (int g = 0; g < G; ++g) { wm[w][g] = m[g]; wl[w][g] = l[g]; }
     __syncthreads();
-    if (tid < HD) {
-        float acc = 0.f;
+    for (int i = threadIdx.x; i < G * HD; i += DEC_WAVES * 64) {
+        const int g = i / HD, d = i % HD;
+        if (h0 + g >= grp) continue;
+        float M = wm[0][g];
 #pragma unroll
-        for (int i = 0; i < 4 * RPW; ++i) acc += part[i * HD + tid];
-        o[(size_t)b * ld_o + hq * HD + tid] = f2bf(acc / sum);
+        for (int k = 1; k < DEC_WAVES; ++k) M = fmaxf(M, wm[k][g]);
+        float L = 0.f, acc = 0.f;
+#pragma unroll
+        for (int k = 0; k < DEC_WAVES; ++k) {
+            const float f = __builtin_amdgcn_exp2f(wm[k][g] - M);      // 0 for a wave without positions
+            L = fmaf(f, wl[k][g], L);
+            acc = fmaf(f, buf[(k * G + g) * HD + d], acc);
+        }
+        const int hq = hk * grp + h0 + g;
+        if (gridDim.x == 1) {
+            o[(size_t)b * ld_o + hq * HD + d] = f2bf(acc / L);
+        } else {
+            float* pr = part + ((size_t)(b * Hq + hq) * gridDim.x + split) * (HD + 2);
+            pr[d] = acc;
+            if (d == 0) { pr[HD] = M; pr[HD + 1] = L; }
+        }
     }
 }
 
+// At most 64 splits (kDecodeMaxLen / 512): lane s weighs split s, then every thread adds its element of the rows,
+// eight loads in flight (one dependent chain of loads per split took 10.5 us for 16 splits).
 template <int HD>
-hipError_t launch_decode(hipStream_t st, const bf16_t* qkv, int ld_qkv, const bf16_t* kt, const bf16_t* v, bf16_t* o,
-                         int ld_o, int B, int n, int max_len, int Hq, int Hkv) {
-    const int n_pad = (n + 3) / 4 * 4;
-    const size_t lds = ((size_t)n_pad + HD + 8 + 4 * 512 + 2048) * sizeof(float);
-    static LdsLimitOnce lds_limit;
-    if (lds > 48 * 1024) {
-        hipError_t e = lds_limit.set(reinterpret_cast<const void*>(decode_attn_kernel<HD>), (int)kDecodeMaxLds);
-        if (e != hipSuccess) return e;
+__global__ __launch_bounds__(HD) void combine_kernel(const float* __restrict__ part, int splits, bf16_t* __restrict__ o,
+                                                     int ld_o, int Hq) {
+    const int hq = blockIdx.x, b = blockIdx.y, d = threadIdx.x, lane = threadIdx.x & 63;
+    const float* p = part + (size_t)(b * Hq + hq) * splits * (HD + 2);
+    const bool on = lane < splits;
+    const float2 ml = on ? *reinterpret_cast<const float2*>(p + lane * (HD + 2) + HD) : make_float2(-INFINITY, 0.f);
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = j < splits ? p[j * (HD + 2) + d] : 0.f;
+    const float M = wave_max(ml.x);
+    const float f = on ? __builtin_amdgcn_exp2f(ml.x - M) : 0.f;
+    const float L = wave_sum(f * ml.y);
+    float acc = 0.f;
+    for (int s0 = 0; s0 < splits; s0 += 8) {
+        if (s0)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = s0 + j < splits ? p[(s0 + j) * (HD + 2) + d] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc = fmaf(__shfl(f, s0 + j, 64), v[j], acc);     // s0 + j <= 63
     }
-    decode_attn_kernel<HD><<<dim3(Hq, B), 256, lds, st>>>(qkv, ld_qkv, kt, v, o, ld_o, n, n_pad, max_len, Hq, Hkv,
-                                                          1.0f / sqrtf((float)HD));
+    o[(size_t)b * ld_o + hq * HD + d] = f2bf(acc / L);
+}
+
+template <int HD, int G>
+hipError_t launch_decode_g(hipStream_t st, const bf16_t* qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* o, int ld_o,
+                           float* part, int B, int n, int fresh, int max_len, int Hq, int Hkv) {
+    const int ngb = (Hq / Hkv + G - 1) / G;
+    // splits: enough work-groups for the chip, at least 512 positions each (a split saves less than the
+    // second launch costs below that), and no more rows of
+    // partial results than decode_scratch_floats counts
+    int splits = part ? std::min(std::max(kDecodeSplitGroups / (B * Hkv), 1), n / 512) : 1;
+    if (splits < 1) splits = 1;
+    int per = (n + splits - 1) / splits;
+    per = std::max((per + 63) / 64 * 64, 64);
+    splits = std::max((n + per - 1) / per, 1);           // none is empty
+    const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
+    decode_attn_kernel<HD, G><<<dim3(splits, Hkv * ngb, B), DEC_WAVES * 64, 0, st>>>(qkv, ld_qkv, kt, v, o, ld_o, part, n, fresh, per,
+                                                                                     max_len, Hq, Hkv, sl2);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    combine_kernel<HD><<<dim3(Hq, B), HD, 0, st>>>(part, splits, o, ld_o, Hq);
     return hipGetLastError();
+}
+
+template <int HD>
+hipError_t launch_decode(hipStream_t st, const bf16_t* qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* o, int ld_o,
+                         float* part, int B, int n, int fresh, int max_len, int Hq, int Hkv) {
+    const int grp = Hq / Hkv;
+    if (grp == 1) return launch_decode_g<HD, 1>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+    if (grp == 2) return launch_decode_g<HD, 2>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+    if (grp <= 4) return launch_decode_g<HD, 4>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+    return launch_decode_g<HD, 8>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
 }
 
 }  // namespace
@@ -178,13 +322,23 @@ hipError_t spk_launch_kv_append(hipStream_t st, const bf16_t* qkv, int ld_qkv, b
     return hipGetLastError();
 }
 
+static hipError_t decode_step(hipStream_t st, const bf16_t* qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* o, int ld_o,
+                              float* part, int B, int n, int fresh, int max_len, int Hq, int Hkv, int hd) {
+    if (B < 1 || n + fresh < 1 || n + fresh > max_len || (max_len & 7) || max_len > kDecodeMaxLen || Hkv < 1 || Hq % Hkv ||
+        ld_qkv % 8 || B > 65535 || ((uintptr_t)kt & 15) || ((uintptr_t)v & 15) || ((uintptr_t)qkv & 15))
+        return hipErrorInvalidValue;
+    if (hd == 128) return launch_decode<128>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+    if (hd == 64) return launch_decode<64>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+    return hipErrorInvalidValue;
+}
+
 hipError_t spk_launch_decode_attention(hipStream_t st, const bf16_t* qkv, int ld_qkv, const bf16_t* kt,
                                        const bf16_t* v, bf16_t* o, int ld_o, int B, int n, int max_len, int Hq,
                                        int Hkv, int hd) {
-    if (B < 1 || n < 1 || n > max_len || (max_len & 7) || max_len > kDecodeMaxLen || Hkv < 1 || Hq % Hkv ||
-        ((uintptr_t)kt & 15) || ((uintptr_t)v & 15))
-        return hipErrorInvalidValue;
-    if (hd == 128) return launch_decode<128>(st, qkv, ld_qkv, kt, v, o, ld_o, B, n, max_len, Hq, Hkv);
-    if (hd == 64) return launch_decode<64>(st, qkv, ld_qkv, kt, v, o, ld_o, B, n, max_len, Hq, Hkv);
-    return hipErrorInvalidValue;
+    // nothing is stored without a fresh position
+    return decode_step(st, qkv, ld_qkv, const_cast<bf16_t*>(kt), const_cast<bf16_t*>(v), o, ld_o, nullptr, B, n, 0, max_len, Hq, Hkv, hd);
+}
+
+hipError_t spk_launch_decode_step(hipStream_t st, const bf16_t* qkv, bf16_t* o, const AttnShape& a) {
+    return decode_step(st, qkv, a.ld_qkv, a.kt, a.v, o, a.Hq * a.hd, a.part, a.B, a.pos, 1, a.max_len, a.Hq, a.Hkv, a.hd);
 }

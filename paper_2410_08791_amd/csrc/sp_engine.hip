@@ -230,17 +230,16 @@ int sp_layer_forward(sp_engine* e, const unsigned char* w, float* h, int B, int 
         g = GemmArgs{a, dm, OP_KMAJOR, W(dec ? SP_T_WQKV : SP_T_E_WQKV), dm, OP_KMAJOR, qkv, nqkv, nullptr, 0,
                      dec ? nullptr : W(SP_T_BQKV), T, nqkv, dm, 0};
         SP_OP(e, SP_OP_GEMM_QKV, spk_launch_gemm(st, EPI_BF16, g));
-        // b3: attention.  With a cache the new keys/values are stored first; a decode step then
-        // attends its single query per sequence to the cached positions 0..pos.
-        if (kv)
-            SP_OP(e, SP_OP_ATTENTION, spk_launch_kv_append(st, qkv, nqkv, kv->kt, kv->v, B, S, kv->pos >= 0 ? kv->pos : 0, d.n_q_heads,
-                                           d.n_kv_heads, d.head_dim, kv->max_len));
+        // b3: attention.  A prompt's keys/values are stored in the cache; a decode step attends its
+        // single query per sequence to the positions 0..pos and stores position pos itself.
         if (kv && kv->pos >= 0) {
-            SP_OP(e, SP_OP_ATTENTION, spk_launch_decode_attention(st, qkv, nqkv, kv->kt, kv->v, o, nq, B, kv->pos + 1, kv->max_len,
-                                                  d.n_q_heads, d.n_kv_heads, d.head_dim));
-        } else {
-            SP_OP(e, SP_OP_ATTENTION, spk_launch_attention(st, qkv, o, nullptr, as));
+            as.kt = kv->kt; as.v = kv->v; as.max_len = kv->max_len; as.pos = kv->pos;
+            as.part = e->wsp<float>(e->ws.z);
+        } else if (kv) {
+            SP_OP(e, SP_OP_ATTENTION, spk_launch_kv_append(st, qkv, nqkv, kv->kt, kv->v, B, S, 0, d.n_q_heads, d.n_kv_heads,
+                                                           d.head_dim, kv->max_len));
         }
+        SP_OP(e, SP_OP_ATTENTION, spk_launch_attention(st, qkv, o, nullptr, as));
         // b4: h += o Wo^T (+ b)
         g = GemmArgs{o, nq, OP_KMAJOR, W(dec ? SP_T_WO : SP_T_E_WO), nq, OP_KMAJOR, h, dm, h, dm,
                      dec ? nullptr : W(SP_T_BO), T, dm, nq, 0};

@@ -83,7 +83,11 @@ void make_workspace(const sp_stack_desc* d, const Layout& lay, int training, Wor
     // [gate | up] resp. the MLP pre-activation: only the backward needs them in memory (the
     // forward applies SwiGLU / GELU in the producing GEMM's epilogue and stores z alone)
     ws->gu = training ? take(Tp * (d->arch == SP_DECODER_SWIGLU_RMS ? 2 * f : f) * 2) : off;
-    ws->z = take(Tp * f * 2);
+    // z is idle while the attention runs: a decode step keeps its partial results there
+    size_t zb = Tp * f * 2;
+    if (!training && d->arch == SP_DECODER_SWIGLU_RMS && d->causal && (d->head_dim == 64 || d->head_dim == 128))
+        zb = std::max(zb, decode_scratch_floats(d->n_q_heads, d->n_kv_heads, d->head_dim) * 4);
+    ws->z = take(zb);
     if (training) {
         ws->m = take(Tp * dm * 2);
         ws->h1 = take(T * dm * 4);

@@ -73,11 +73,19 @@ hipError_t spk_launch_swiglu(hipStream_t st, const bf16_t* gu, bf16_t* z, int T,
 struct AttnShape {
     int B, S, Hq, Hkv, hd, causal;
     int ld_qkv;      // row stride (elements) of the fused [q | k | v] activation
+    // A decode step (kt != nullptr; S == 1): one query per sequence against the cache of one layer, whose
+    // position `pos` is taken from qkv and stored.  part: decode_scratch_floats() floats.
+    bf16_t* kt = nullptr;
+    bf16_t* v = nullptr;
+    float* part = nullptr;
+    int pos = 0, max_len = 0;
 };
 
 // o bf16 [B*S, Hq*hd] = softmax(q k^T / sqrt(hd) + mask) v per (batch, head);
 // lse (nullable) fp32 [B, Hq, S] = log of the softmax denominator incl. the row max.
+// With a.kt set: the decode step above (lse is not written).
 hipError_t spk_launch_attention(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, const AttnShape& a);
+hipError_t spk_launch_decode_step(hipStream_t st, const bf16_t* qkv, bf16_t* o, const AttnShape& a);
 
 // ---- decode (key/value cache) ---------------------------------------------------------
 // One layer's cache: kt bf16 [B][Hkv][hd][max_len], v bf16 [B][Hkv][max_len][hd].

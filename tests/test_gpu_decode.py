@@ -190,3 +190,18 @@ def test_decode_argument_errors(gen):
         ee.decode(xe, xe, cache, 1, 0, 16)
     assert ex.value.code == sp.SP_ERR_STATE
     ee.destroy()
+
+
+@pytest.mark.parametrize("B,S,s0,Hq,Hkv,hd", [
+    (1, 1030, 1021, 4, 1, 128),     # from 1024 cached positions on in two splits; one group of four
+    (2, 1540, 1534, 6, 2, 64),      # three splits, a group of three (padded to four)
+    (1, 1090, 1087, 16, 1, 64),     # a group of sixteen: two head blocks read the cache, one stores
+    (1, 515, 509, 8, 1, 128),       # one split, a group of eight
+    (2, 10, 0, 2, 2, 128),          # the first positions: waves without any
+])
+def test_decode_splits_and_groups(B, S, s0, Hq, Hkv, hd):
+    """Decode attention around the sizes where the positions are split, for every number of query heads
+    per work-group, against the oracle's causal forward."""
+    g = Gen(synth.Workload("gen_split", "decoder", 1, Hq * hd, Hq, Hkv, hd, 128, True, B, S))
+    out, _ = g.run(1, 1, s0=s0, max_len=(S + 7) // 8 * 8)
+    assert both(out[:, s0:], g.ref[:, s0:], g.x[:, s0:]) <= TOL
