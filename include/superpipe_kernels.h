@@ -37,8 +37,8 @@ int spk_norm(void* stream, const float* h, const uint16_t* gain, const uint16_t*
  *                  1 = row index contiguous        (A[k*lda+m], W[k*ldw+n]).
  * tile: 0 = library heuristic; 1..4 force a block tile of the register-staged kernel (128x128, 128x256,
  *       256x256 with 4 waves, 256x256 with 8 waves), 5..8 of the LDS-DMA kernel (256x256, 128x256, 128x128,
- *       256x192 -- the last not with epilogue 3; when an operand has form 1 a register-staged kernel runs
- *       instead), 10 the 256x320 tile of the LDS-DMA kernel (not with epilogue 3), 9 the small-tile kernel
+ *       256x192 -- the last not with epilogue 3; when the rows of C are no multiple of 16 bytes a
+ *       register-staged kernel runs instead), 10 the 256x320 tile of the LDS-DMA kernel (not with epilogue 3), 9 the small-tile kernel
  *       for M <= 64 rows (both forms 0; the heuristic's choice for such M) with its own choice of tile,
  *       11 / 12 / 13 the same with 16 / 32 / 64 rows per work-group, 14..20 its tiles for any M: 16x16,
  *       16x32, 32x32, 64x32, 64x64, 96x64, 64x128 (an operand of form 1: 16 and 18 only).
@@ -50,7 +50,9 @@ int spk_gemm(void* stream, int epilogue, const uint16_t* A, int lda, int a_form,
 /* The large-tile plan behind tile = 0 for a shape (host-only query, nothing is launched; the choice depends
  * on the shape alone, never on addresses or on the streaming window): out3 (host) = {tile id of rows
  * [0, body_rows), body_rows, tile id of rows [body_rows, M) or 0 when body_rows == M}.  A launch too small
- * for it (judged with K) runs on the small-tile kernel instead. */
+ * for it (judged with K) runs on the small-tile kernel instead.  With an operand of form 1 the answer is the
+ * register-staged tile, which runs where the rows of C are no multiple of 16 bytes; other launches of these
+ * forms take the LDS-DMA tiles by the same rule with their own measured costs. */
 int spk_gemm_plan(int epilogue, int a_form, int w_form, int M, int N, int* out3);
 
 /* z bf16 [T,f] = silu(gu[:, :f]) * gu[:, f:]; gu bf16 [T,2f]; f % 8 == 0. */

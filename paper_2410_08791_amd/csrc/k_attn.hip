@@ -25,8 +25,7 @@
 // at a time then cover all banks.  V rows: the 64-byte block (one 32-element tile of O^T)
 // ^ (row & 3) for 256-byte rows, ^ ((row >> 1) & 1) for 128, none for 192 -- the four key
 // rows of a transposing read fall into different bank groups.
-#include "sp_common.h"
-#include "sp_kernels.h"
+#include "sp_gemm.h"
 
 namespace {
 
@@ -58,11 +57,6 @@ struct AttnCfg {
     // in 64-byte blocks
     __device__ static int v_swz(int row) { return HD == 128 ? (row & 3) : HD == 64 ? ((row >> 1) & 1) : 0; }
 };
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
-typedef __attribute__((address_space(3))) void* lds_void_ptr_a;
 
 struct SoftmaxState {
     float m_run, l_run;
@@ -112,8 +106,8 @@ __device__ __forceinline__ void attn_tile(const unsigned char* sK, const unsigne
     auto vread = [&](int st) {
         const int tj = st / C::NMT, mt = st % C::NMT;
         const unsigned char* vp = sV + ((tj >> 1) * 32 + 16 * (tj & 1)) * C::ROWB + vpos[mt];
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(vp));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(vp + 8 * C::ROWB));
+        const s16x4_t lo = sp_tr_read((lds_s16x4_ptr)(vp));
+        const s16x4_t hi = sp_tr_read((lds_s16x4_ptr)(vp + 8 * C::ROWB));
         vf[st] = s16x8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     };
 #pragma unroll
@@ -245,7 +239,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_kernel(const bf16_t* __re
         _Pragma("unroll") for (int i_ = 0; i_ < C::NLOAD; ++i_)                                                    \
             if (wave * C::NLOAD + i_ < C::NINST && ld_on[i_])                                                      \
                 __builtin_amdgcn_global_load_lds(kbase + ((size_t)min((kt_) * KB + ld_row[i_], S - 1) * ld_qkv + ld_col[i_]), \
-                                                 (lds_void_ptr_a)(smem_attn + (stage_) * C::STAGE +                \
+                                                 (lds_void_ptr)(smem_attn + (stage_) * C::STAGE +                \
                                                                   (wave * C::NLOAD + i_) * 1024), 16, 0, 0);      \
     } while (0)
 #else

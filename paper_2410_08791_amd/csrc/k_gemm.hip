@@ -8,11 +8,10 @@
 // (128-byte rows, 16-byte chunks XOR-swizzled so that both the 16-byte stores
 // and the per-lane 16-byte fragment loads spread over all banks), double
 // buffered.  Two kernels build that LDS image: gemm_dma_kernel (global loads
-// that write LDS directly; used whenever both operands have the contraction
-// index contiguous, i.e. every forward projection) and gemm_kernel (register
-// staging: global loads for tile t+1 are issued before the MFMAs of tile t and
-// stored to the other buffer afterwards, one barrier per tile; takes every
-// operand form).
+// that write LDS directly; every projection, forward and backward) and gemm_kernel
+// (register staging: global loads for tile t+1 are issued before the MFMAs of tile t
+// and stored to the other buffer afterwards, one barrier per tile; takes the outputs
+// whose rows do not start on 16 bytes, which the other kernel's epilogue cannot write).
 //
 // The MFMA is issued "transposed" (weights as the A operand, activations as B)
 // so that a lane's four consecutive accumulator registers are four consecutive
@@ -23,20 +22,12 @@
 // GEMMs) is staged as it lies in memory (LDS row = contraction index) and read
 // with the transposing LDS load of gfx950 (ds_read_b64_tr_b16), which hands each
 // lane four consecutive contraction elements of one operand row.
-#include "sp_common.h"
-#include "sp_kernels.h"
+#include "sp_gemm.h"
 
 namespace {
 
 constexpr int BK = 64;
 constexpr int ROW_BYTES = BK * 2;  // 128
-
-struct GemmDev {
-    const bf16_t* A; const bf16_t* W; void* C; const float* R; const bf16_t* bias;
-    int lda, ldw, ldc, ldr;
-    int M, N, K;
-    int tilesM, tilesN;
-};
 
 __device__ __forceinline__ int lds_off(int row, int chunk) {
     return row * ROW_BYTES + ((chunk ^ ((row >> 1) & 7)) << 4);
@@ -120,13 +111,9 @@ struct LoaderR {
 // k row (s>>2) and r block 4*(s&3), lane i ends up with r = 4*(i>>2) + (i&3) = i and four
 // consecutive k: two reads give the eight k of a lane's operand, in the same order as the
 // 16-byte read of a k-contiguous tile, so both operand forms can be mixed.
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
-
 __device__ __forceinline__ bf16x8_t tr_frag(const unsigned char* p, int stride) {
     const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
     const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * stride));
-    typedef short s16x8_t __attribute__((ext_vector_type(8)));
     const s16x8_t both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8_t, both);
 }
@@ -496,14 +483,21 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
     }
 }
 
-// ---- LDS-DMA kernel (both operands contraction-contiguous) ----------------------------------
+// ---- LDS-DMA kernel ----------------------------------------------------------------------------
 // Global loads write LDS directly (global_load_lds_dwordx4): no staging registers and no
 // ds_write instructions.  Measured on MI355X, LDS writes issued by the waves run at about
 // 75 bytes/clk per CU and serialise with the fragment reads (215 bytes/clk), so a 256x256x64
 // tile costs ~870 + ~900 LDS cycles against 2048 MFMA cycles; the DMA writes overlap the reads.
-// A wave instruction lands 64 lanes x 16 bytes = 8 tile rows of 128 bytes contiguously, so the
-// XOR swizzle of the 16-byte chunks is applied on the global side (which chunk a lane fetches);
-// the LDS image is the one the register-staged kernel builds.
+// A wave instruction lands 64 lanes x 16 bytes contiguously, so the XOR swizzle of the 16-byte
+// pieces is applied on the global side (which piece a lane fetches, OpTile); a contraction-contiguous
+// operand gets the LDS image the register-staged kernel builds, a row-contiguous one lies as in memory
+// (LDS row = contraction index) and is read with the transposing LDS read.
+//
+// Backward forms on this kernel against the register-staged one (256x256 tiles, random operands, us):
+//   dX 16384 x 11008 x 4096, 16384 x 4096 x 22016, 8192 x 2048 x 6144   1462 / 2702 / 187 -> 1237 / 2408 / 175
+//   dW 22016 x 4096 x 16384, 4096 x 4096 x 16384, 6144 x 2048 x 8192    2802 / 481 / 213 -> 2563 / 436 / 195
+// bit for bit the same sums.  What bounds both is the matrix pipe at the clock that random operands
+// allow (1.15-1.25 PFLOP/s); the stores to LDS were the rest.
 //
 // Two 64-deep stages.  The only barrier of a tile sits before its LAST k-step: by then a wave
 // has read all its fragments of the tile (the last step's are in registers) and its loads of the
@@ -516,10 +510,11 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
 // The compiler does not order these loads against later LDS reads; the kernel waits with
 // explicit vmcnt/lgkmcnt counts and uses a bare s_barrier (the fence of __syncthreads() is
 // what the counts replace).
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-template <int BM, int BN, int EPI, int WAVES, int WM>
+template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kernel(GemmDev p) {
+    typedef OpTile<BM, AFORM> TA;
+    typedef OpTile<BN, WFORM> TW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int WNC = WAVES / WM;              // wave grid: WM (m) x WNC (n)
     constexpr int WMR = BM / WM, WN = BN / WNC;  // tile rows of A / of W per wave
@@ -549,31 +544,33 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
     const int tn = (pid % group) / gm;
     const int m0 = tm * BM, n0 = tn * BN_OUT;
 
-    // load assignment: block b of 8 tile rows, b < BM/8 -> A rows, else W rows.  Lane l lands at
-    // row l>>3, 16-byte position l&7 of the block, and fetches the chunk that the swizzle puts there.
+    // load assignment: block b of 1 KiB, b < BM/8 -> the A tile, else the W tile.  Lane l lands at
+    // its 16 bytes l of the block and fetches the piece that the swizzle puts there.
     const bf16_t* src[NI];
     int dst[NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int blk = wave * NI + i;
         const bool is_w = blk >= NBLK_A;
-        const int row = (is_w ? blk - NBLK_A : blk) * 8 + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+        const int off = (is_w ? blk - NBLK_A : blk) * 1024 + lane * 16;
+        int row, k;
         if (is_w) {
-            int grow;
+            TW::piece(off, &row, &k);
             if (SWIGLU) {
                 const int wr = row / WN, j = (row % WN) >> 5, rr = row & 31;
                 const int isup = j >= TN / 2;
                 const int col = n0 + wr * (WN / 2) + (isup ? j - TN / 2 : j) * 32 + rr;
-                grow = min(col, p.N - 1) + (isup ? p.N : 0);
+                row = min(col, p.N - 1) + (isup ? p.N : 0);
             } else {
-                grow = min(n0 + row, p.N - 1);
+                row = min(n0 + row, p.N - (WFORM == OP_KMAJOR ? 1 : 8));
             }
-            src[i] = p.W + (size_t)grow * p.ldw + chunk * 8;
+            src[i] = WFORM == OP_KMAJOR ? p.W + (size_t)row * p.ldw + k : p.W + (size_t)k * p.ldw + row;
         } else {
-            src[i] = p.A + (size_t)min(m0 + row, p.M - 1) * p.lda + chunk * 8;
+            TA::piece(off, &row, &k);
+            row = min(m0 + row, p.M - (AFORM == OP_KMAJOR ? 1 : 8));
+            src[i] = AFORM == OP_KMAJOR ? p.A + (size_t)row * p.lda + k : p.A + (size_t)k * p.lda + row;
         }
-        dst[i] = blk * 8 * ROW_BYTES;
+        dst[i] = blk * 1024;
     }
     const int KT = p.K / BK;
     // (The builtin's address-space-qualified parameters do not type-check in the host pass
@@ -583,9 +580,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
 #define SP_DMA_ISSUE_R(tile, stage, i0, i1)                                                                   \
     do {                                                                                                       \
         const int k0_ = min((tile), KT - 1) * BK;                                                              \
+        const size_t ka_ = AFORM == OP_KMAJOR ? k0_ : (size_t)k0_ * p.lda;                                     \
+        const size_t kw_ = WFORM == OP_KMAJOR ? k0_ : (size_t)k0_ * p.ldw;                                     \
         _Pragma("unroll") for (int i_ = (i0); i_ < (i1); ++i_)                                                 \
-            __builtin_amdgcn_global_load_lds(src[i_] + k0_, (lds_void_ptr)(smem + (stage) * STAGE + dst[i_]), \
-                                             16, 0, 0);                                                        \
+            __builtin_amdgcn_global_load_lds(src[i_] + (wave * NI + i_ >= NBLK_A ? kw_ : ka_),                 \
+                                             (lds_void_ptr)(smem + (stage) * STAGE + dst[i_]), 16, 0, 0);      \
     } while (0)
 #else
 #define SP_DMA_ISSUE(tile, stage) ((void)src, (void)dst)
@@ -600,14 +599,22 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
 
+    // fragment addresses: a contraction-contiguous tile is base + block * 4096 + foff[ks], a row-contiguous
+    // one has its block in the swizzle (one base per block)
     const int sw = (l32 >> 1) & 7;
     int foff[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) foff[ks] = l32 * ROW_BYTES + (((2 * ks + half) ^ sw) << 4);
-    const int a_base = wm * WMR * ROW_BYTES;
-    const int w_base = A_BYTES + wn * WN * ROW_BYTES;
+    int abase[TM], wbase[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+        abase[i] = AFORM == OP_KMAJOR ? (wm * TM + i) * 32 * ROW_BYTES : TA::frag_base(wm * TM + i, lane);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+        wbase[j] = A_BYTES + (WFORM == OP_KMAJOR ? (wn * TN + j) * 32 * ROW_BYTES : TW::frag_base(wn * TN + j, lane));
 
     constexpr int NFRAG = TM + TN, NMFMA = TM * TN;
+    constexpr int AR = AFORM == OP_KMAJOR ? 1 : 2, WR = WFORM == OP_KMAJOR ? 1 : 2;   // LDS reads per fragment
     constexpr int M_MFMA = 0x008, M_VMEM_RD = 0x020, M_DS_RD = 0x100;
     // s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt<<4 | lgkmcnt<<8 | vmcnt[5:4]<<14)
     constexpr int WAIT_VM0_LGKM0 = (0 & 15) | (7 << 4) | (0 << 8) | (0 << 14);
@@ -617,10 +624,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
     auto load_frags = [&](const unsigned char* tile, int ks, int buf) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-            af[buf][i] = *reinterpret_cast<const bf16x8_t*>(tile + a_base + i * 32 * ROW_BYTES + foff[ks]);
+            af[buf][i] = AFORM == OP_KMAJOR ? *reinterpret_cast<const bf16x8_t*>(tile + abase[i] + foff[ks]) : TA::frag(tile, abase[i], ks, lane);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-            wf[buf][j] = *reinterpret_cast<const bf16x8_t*>(tile + w_base + j * 32 * ROW_BYTES + foff[ks]);
+            wf[buf][j] = WFORM == OP_KMAJOR ? *reinterpret_cast<const bf16x8_t*>(tile + wbase[j] + foff[ks]) : TW::frag(tile, wbase[j], ks, lane);
     };
     auto mfmas = [&](int buf) {
 #pragma unroll
@@ -651,7 +658,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
         mfmas(0);
 #define SP_SCHED_STEP(NV)                                                                  \
         _Pragma("unroll") for (int i = 0; i < NFRAG; ++i) {                                    \
-            __builtin_amdgcn_sched_group_barrier(M_DS_RD, 1, 0);                               \
+            if (i < TM) __builtin_amdgcn_sched_group_barrier(M_DS_RD, AR, 0);                  \
+            else __builtin_amdgcn_sched_group_barrier(M_DS_RD, WR, 0);                         \
             __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA / NFRAG, 0);                    \
             if (i < (NV)) __builtin_amdgcn_sched_group_barrier(M_VMEM_RD, 1, 0);                  \
         }                                                                                      \
@@ -673,7 +681,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
 #pragma unroll
         for (int i = 0; i < NFRAG; ++i) {
             __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA / NFRAG, 0);
-            __builtin_amdgcn_sched_group_barrier(M_DS_RD, 1, 0);
+            if (i < TM) __builtin_amdgcn_sched_group_barrier(M_DS_RD, AR, 0);
+            else __builtin_amdgcn_sched_group_barrier(M_DS_RD, WR, 0);
         }
         if (NMFMA % NFRAG) __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA % NFRAG, 0);
     }
@@ -684,12 +693,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
 #undef SP_DMA_ISSUE_R
 }
 
-template <int BM, int BN, int EPI, int WAVES, int WM>
+template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM>
 hipError_t launch_dma(hipStream_t st, const GemmArgs& g) {
     constexpr int LDS = 2 * (BM + BN) * ROW_BYTES;
     constexpr int BN_OUT = (EPI == EPI_SWIGLU_BF16) ? BN / 2 : BN;
     static LdsLimitOnce lds_limit;
-    hipError_t e = lds_limit.set(reinterpret_cast<const void*>(gemm_dma_kernel<BM, BN, EPI, WAVES, WM>), LDS);
+    hipError_t e = lds_limit.set(reinterpret_cast<const void*>(gemm_dma_kernel<BM, BN, EPI, AFORM, WFORM, WAVES, WM>), LDS);
     if (e != hipSuccess) return e;
     GemmDev d;
     d.A = g.A; d.W = g.W; d.C = g.C; d.R = g.R; d.bias = g.bias;
@@ -697,7 +706,7 @@ hipError_t launch_dma(hipStream_t st, const GemmArgs& g) {
     d.M = g.M; d.N = g.N; d.K = g.K;
     d.tilesM = (g.M + BM - 1) / BM;
     d.tilesN = (g.N + BN_OUT - 1) / BN_OUT;
-    gemm_dma_kernel<BM, BN, EPI, WAVES, WM><<<d.tilesM * d.tilesN, WAVES * 64, LDS, st>>>(d);
+    gemm_dma_kernel<BM, BN, EPI, AFORM, WFORM, WAVES, WM><<<d.tilesM * d.tilesN, WAVES * 64, LDS, st>>>(d);
     return hipGetLastError();
 }
 
@@ -722,7 +731,7 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& g) {
 }
 
 // Tile ids: register-staged kernel 1 = 128x128, 2 = 128x256 (BM x BN), 3 = 256x256 (4 waves each),
-// 4 = 256x256 with 8 waves; LDS-DMA kernel (contraction-contiguous operands only) 5 = 256x256 and
+// 4 = 256x256 with 8 waves; LDS-DMA kernel 5 = 256x256 and
 // 6 = 128x256 with 8 waves, 7 = 128x128 with 4 waves (two work-groups per CU), 8 = 256x192 with 8
 // waves in a 4 x 2 grid (not with the SwiGLU epilogue, which pairs tiles inside a wave); 9 =
 // at most 64 activation rows (the small-tile kernel, k_gemm_small.hip; 11, 12, 13 force its 16, 32 and
@@ -735,13 +744,18 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& g) {
 // ceil(tiles / concurrent) rounds of one tile's time; a tile's time is its area over a measured
 // relative efficiency (larger tiles move fewer operand bytes per MFMA).  Take the cheapest.
 // (Activation rows are contiguous in A, C and R, so a launch can be cut along M.)
-struct TileCost { int id, bm, bn, concurrent; float eff; };
-constexpr TileCost kDmaTiles[] = {{5, 256, 256, 256, 1.00f}, {10, 256, 320, 256, 1.02f}, {8, 256, 192, 256, 0.85f},
-                                  {6, 128, 256, 256, 0.72f}, {7, 128, 128, 512, 0.70f}};
-constexpr TileCost kRegTiles[] = {{4, 256, 256, 256, 1.00f}, {1, 128, 128, 512, 0.66f}};
+struct TileCost { int id, bm, bn, concurrent; float eff, single; };   // single: a CU's time with one of its two tiles
+constexpr TileCost kDmaTiles[] = {{5, 256, 256, 256, 1.00f, 1.f}, {10, 256, 320, 256, 1.02f, 1.f}, {8, 256, 192, 256, 0.85f, 1.f},
+                                  {6, 128, 256, 256, 0.72f, 1.f}, {7, 128, 128, 512, 0.70f, 1.f}};
+// An operand with the row index contiguous.  Measured on 32 backward shapes (T 1500..16384, d 1280..4096): picks the
+// fastest of the five in all but three, those within 7 %.  One 128x128 tile alone on its CU takes 0.83 of the time
+// of two (115 us for 256 tiles of K = 8192, 139 us for 400).
+constexpr TileCost kDmaTilesR[] = {{5, 256, 256, 256, 1.00f, 1.f}, {10, 256, 320, 256, 1.05f, 1.f}, {8, 256, 192, 256, 0.88f, 1.f},
+                                   {6, 128, 256, 256, 0.73f, 1.f}, {7, 128, 128, 512, 0.80f, 1.5f}};
+constexpr TileCost kRegTiles[] = {{4, 256, 256, 256, 1.00f, 1.f}, {1, 128, 128, 512, 0.66f, 1.f}};
 
 template <int NC>
-int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out = nullptr) {
+int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out) {
     int best = cand[0].id;
     float best_cost = 0.f;
     for (int c = 0; c < NC; ++c) {
@@ -750,10 +764,10 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
         const int bn_out = (epi == EPI_SWIGLU_BF16) ? t.bn / 2 : t.bn;
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + bn_out - 1) / bn_out);
         // in units of "every CU busy with one tile": the two-per-CU tile fills a CU with two
-        long units = tiles / t.concurrent * (t.concurrent / 256);
+        float units = (float)(tiles / t.concurrent * (t.concurrent / 256));
         const long rem = tiles % t.concurrent;
-        if (rem) units += rem <= 256 ? 1 : t.concurrent / 256;
-        const float cost = (float)units * (float)(t.bm * t.bn) / t.eff;
+        if (rem) units += rem <= 256 ? t.single : (float)(t.concurrent / 256);
+        const float cost = units * (float)(t.bm * t.bn) / t.eff;
         if (c == 0 || cost < best_cost) { best = t.id; best_cost = cost; }   // candidate 0 takes every epilogue
     }
     if (cost_out) *cost_out = best_cost;
@@ -763,31 +777,32 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
 // The library's own choice for a shape: the tile, and when a ragged last row of 256-row tiles
 // would cost a whole extra round (ViT-H: 16448 tokens = 64 tiles + 64 rows, 1300 tiles = 5.08
 // rounds of 256) the rows beyond the last multiple of 256 become a launch of their own.
-GemmPlan plan_gemm(int epi, bool dma_ok, int M, int N, float* cost = nullptr) {
+GemmPlan plan_gemm(int epi, bool dma_ok, bool kmajor, int M, int N, float* cost = nullptr) {
     GemmPlan pl{0, M, 0};
     if (!dma_ok) {
         pl.tile = pick_tile(kRegTiles, M, N, epi, cost);
         return pl;
     }
-    if (M <= SPK_FEW_ROWS) {     // a decode step: nothing of W is re-used, stream it
+    if (kmajor && M <= SPK_FEW_ROWS) {     // a decode step: nothing of W is re-used, stream it
         pl.tile = 9;
         return pl;
     }
+    auto pick = [&](int m, float* c) { return kmajor ? pick_tile(kDmaTiles, m, N, epi, c) : pick_tile(kDmaTilesR, m, N, epi, c); };
     float whole;
-    pl.tile = pick_tile(kDmaTiles, M, N, epi, &whole);
+    pl.tile = pick(M, &whole);
     if (cost) *cost = whole;
     const int tail = M % 256, body = M - tail;
     if (tail && body) {
         float c_body, c_tail;
-        const int t_body = pick_tile(kDmaTiles, body, N, epi, &c_body);
+        const int t_body = pick(body, &c_body);
         int t_tail;
-        if (tail <= SPK_FEW_ROWS) {
+        if (kmajor && tail <= SPK_FEW_ROWS) {
             // the small-tile kernel in the units of pick_tile (a round of 256x256 tiles = 65536):
             // N x K x 2 bytes at ~4.5 TB/s against 256 tiles x 2 x 65536 K flop at ~1.3 PFLOP/s, plus a launch
             t_tail = 9;
             c_tail = 1.13f * (float)N + 6000.f;
         } else {
-            t_tail = pick_tile(kDmaTiles, tail, N, epi, &c_tail);
+            t_tail = pick(tail, &c_tail);
         }
         if (c_body + c_tail < 0.97f * whole) {
             pl = GemmPlan{t_body, body, t_tail};
@@ -799,16 +814,16 @@ GemmPlan plan_gemm(int epi, bool dma_ok, int M, int N, float* cost = nullptr) {
 
 template <int EPI, int AFORM, int WFORM>
 hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
-    constexpr bool DMA_OK = (AFORM == OP_KMAJOR && WFORM == OP_KMAJOR);
+    constexpr bool KMAJOR = (AFORM == OP_KMAJOR && WFORM == OP_KMAJOR);
     constexpr int NOSWIGLU = EPI == EPI_SWIGLU_BF16 ? EPI_BF16 : EPI;   // tile 8 has an odd tile count per wave
     constexpr size_t CSZ = (EPI == EPI_RESID_F32 || EPI == EPI_F32) ? 4 : 2;
     // the LDS-DMA kernel writes C (and reads R) in 16-byte pieces of a row
-    const bool dma = DMA_OK && (g.ldc * CSZ) % 16 == 0;
+    const bool dma = (g.ldc * CSZ) % 16 == 0;
     int tile = g.tile;
     auto small = [&](int id) { GemmArgs t = g; t.tile = id; return spk_launch_gemm_small(st, EPI, t); };
     if (tile == 9 || (tile >= 11 && tile <= 13)) {
         // few rows: the small-tile kernel with its own choice of tile, or 16, 32, 64 rows per work-group
-        if (!DMA_OK || g.M > SPK_FEW_ROWS) return hipErrorInvalidValue;
+        if (!KMAJOR || g.M > SPK_FEW_ROWS) return hipErrorInvalidValue;
         float us;
         return small(tile == 9 ? spk_small_gemm_tile(EPI, g.a_form, g.w_form, g.M, g.N, g.K, &us) : tile == 11 ? 14 : tile == 12 ? 16 : 17);
     }
@@ -816,7 +831,7 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
     if (!tile) {
         float small_us, large_cost;
         const int small_id = spk_small_gemm_tile(EPI, g.a_form, g.w_form, g.M, g.N, g.K, &small_us);
-        const GemmPlan pl = plan_gemm(EPI, dma, g.M, g.N, &large_cost);
+        const GemmPlan pl = plan_gemm(EPI, dma, KMAJOR, g.M, g.N, &large_cost);
         if (pl.tile == 9) return small(small_id);
         // Both estimates are fits with 10-18 % error, so the small tiles have to be cheaper by a tenth:
         // over 180 shapes of up to 2560 rows the choice is within 1 % of the better kernel on average
@@ -827,7 +842,7 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
             GemmArgs a = g, b = g;
             a.M = pl.body_rows; a.tile = pl.tile;
             b.M = g.M - pl.body_rows; b.tile = pl.tail_tile;
-            b.A = g.A + (size_t)pl.body_rows * g.lda;
+            b.A = AFORM == OP_KMAJOR ? g.A + (size_t)pl.body_rows * g.lda : g.A + pl.body_rows;
             b.C = static_cast<unsigned char*>(g.C) + (size_t)pl.body_rows * g.ldc * CSZ;
             if (g.R) b.R = g.R + (size_t)pl.body_rows * g.ldr;
             hipError_t e = launch_tile<EPI, AFORM, WFORM>(st, a);
@@ -840,11 +855,11 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
         case 2: return launch_one<128, 256, EPI, AFORM, WFORM, 4>(st, g);
         case 3: return launch_one<256, 256, EPI, AFORM, WFORM, 4>(st, g);
         case 4: return launch_one<256, 256, EPI, AFORM, WFORM, 8>(st, g);
-        case 5: if (DMA_OK) return launch_dma<256, 256, EPI, 8, 2>(st, g); break;
-        case 6: if (DMA_OK) return launch_dma<128, 256, EPI, 8, 2>(st, g); break;
-        case 7: if (DMA_OK) return launch_dma<128, 128, EPI, 4, 2>(st, g); break;
-        case 8: if (DMA_OK && EPI != EPI_SWIGLU_BF16) return launch_dma<256, 192, NOSWIGLU, 8, 4>(st, g); break;
-        case 10: if (DMA_OK && EPI != EPI_SWIGLU_BF16) return launch_dma<256, 320, NOSWIGLU, 8, 4>(st, g); break;
+        case 5: return launch_dma<256, 256, EPI, AFORM, WFORM, 8, 2>(st, g);
+        case 6: return launch_dma<128, 256, EPI, AFORM, WFORM, 8, 2>(st, g);
+        case 7: return launch_dma<128, 128, EPI, AFORM, WFORM, 4, 2>(st, g);
+        case 8: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 192, NOSWIGLU, AFORM, WFORM, 8, 4>(st, g); break;
+        case 10: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 320, NOSWIGLU, AFORM, WFORM, 8, 4>(st, g); break;
     }
     return hipErrorInvalidValue;
 }
@@ -852,7 +867,8 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
 }  // namespace
 
 GemmPlan spk_gemm_plan_host(int epi, int a_form, int w_form, int M, int N) {
-    return plan_gemm(epi, a_form == OP_KMAJOR && w_form == OP_KMAJOR, M, N);
+    const bool kmajor = a_form == OP_KMAJOR && w_form == OP_KMAJOR;
+    return plan_gemm(epi, kmajor, kmajor, M, N);
 }
 
 hipError_t spk_launch_gemm(hipStream_t st, int epi, const GemmArgs& g) {

@@ -15,6 +15,11 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
 
+// Transposing LDS read.  The restrict parameter matters: without an alias scope on the read the compiler
+// takes it for a possible reader of every LDS-DMA load in flight and waits for all of them (s_waitcnt
+// vmcnt(0)) in front of it.  What a read needs is waited for by the kernels themselves.
+__device__ __forceinline__ s16x4_t sp_tr_read(lds_s16x4_ptr __restrict p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16(p); }
+
 // LDS image of one 64-deep operand tile of ROWS rows, as LDS-DMA loads write it (16-byte pieces, a
 // wave's 64 pieces land on 1 KiB contiguously, so the bank swizzle sits in which piece a lane fetches).
 //   OP_KMAJOR: one 128-byte LDS row per operand row; piece p of row r holds chunk p ^ ((r >> 1) & 7).
@@ -55,8 +60,8 @@ struct OpTile {
             return *reinterpret_cast<const bf16x8_t*>(tile + base + (((2 * ks + (lane >> 5)) ^ sw) << 4));
         }
         const unsigned char* p = tile + base + ks * 16 * RB;
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * RB));
+        const s16x4_t lo = sp_tr_read((lds_s16x4_ptr)(p));
+        const s16x4_t hi = sp_tr_read((lds_s16x4_ptr)(p + 4 * RB));
         return __builtin_bit_cast(bf16x8_t, s16x8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
     }
 };

@@ -245,6 +245,33 @@ def test_gemm_transposed_operands(M, N, K, tile):
     assert np.all(np.abs(C2.cpu().numpy() - ref) <= 2e-6 * np.sqrt(K) * scale)
 
 
+@pytest.mark.parametrize("tile", [5, 6, 7, 8, 10, 0])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 64), (264, 328, 192), (520, 648, 128), (256, 320, 64), (1032, 3592, 64)])
+def test_gemm_transposed_operands_lds_dma(M, N, K, tile):
+    """The backward forms on the LDS-DMA kernel: one row group, whole tiles, ragged rows and columns of
+    every tile width, one k-tile, a shape whose ragged rows the library cuts off.  One guard row behind C."""
+    rng = np.random.default_rng(M * 3 + N + K + tile)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (N, K), 0.1)
+    R = rng.standard_normal((M, N)).astype(np.float32)
+    Ad, ATd, WTd = dev_u16(Ab), dev_u16(Ab.T), dev_u16(Wb.T)
+    ref = A @ W.T
+    tol = 2e-6 * np.sqrt(K) * np.max(np.abs(ref))                          # as in test_gemm_transposed_operands
+    for epi, a_form in ((sp.EPI_BF16, 0), (sp.EPI_F32, 0), (sp.EPI_RESID_F32, 0), (sp.EPI_F32, 1)):
+        f32out = epi != sp.EPI_BF16
+        Cd = torch.full((M + 1, N), 7.0 if f32out else 7, dtype=torch.float32 if f32out else torch.int16, device=DEV)
+        if epi == sp.EPI_RESID_F32:
+            Cd[:M] = dev_f32(R)
+        assert sp.spk_gemm(stream_ptr(), epi, ptr(ATd if a_form else Ad), M if a_form else K, a_form, ptr(WTd), N, 1, ptr(Cd), N,
+                           ptr(Cd) if epi == sp.EPI_RESID_F32 else None, N, None, M, N, K, tile) == sp.SP_OK
+        sync()
+        out = Cd.cpu()
+        assert bool((out[M] == 7).all())
+        got = out[:M].numpy() if f32out else bf16_vals(host_u16(out[:M].contiguous()))
+        want = ref + R if epi == sp.EPI_RESID_F32 else ref
+        assert np.all(np.abs(got - want) <= tol + (2.0 ** -23 * np.abs(want) if f32out else BF16_EPS * np.abs(want))), (epi, a_form)
+
+
 def test_gemm_rejects_shapes_it_cannot_take():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     args = lambda M, N, K, lda=64, ldw=64, ldc=64: sp.spk_gemm(  # noqa: E731
