@@ -499,19 +499,21 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
 // bit for bit the same sums.  What bounds both is the matrix pipe at the clock that random operands
 // allow (1.15-1.25 PFLOP/s); the stores to LDS were the rest.
 //
-// Two 64-deep stages.  The only barrier of a tile sits before its LAST k-step: by then a wave
+// NST 64-deep stages: two, where more do not fit, three for the 128x256 tile, whose 1024 MFMA cycles per k-tile
+// are too few for a load that misses the L2 to come back under one tile (cold operands, two -> three stages, us:
+// 2048 x 4096 x 11008 229 -> 183, dW 1280 x 5120 x 8256 160 -> 125, dW 2048 x 2048 x 8192 144 -> 104).  The only barrier of a tile sits before its LAST k-step: by then a wave
 // has read all its fragments of the tile (the last step's are in registers) and its loads of the
-// next tile, issued one tile earlier, have landed, so after the barrier the other stage is
+// next tile, issued NST - 1 tiles earlier, have landed, so after the barrier the next stage is
 // readable and this stage is free.  The last step then runs with the first fragments of the
 // next tile being read under its MFMAs: nothing that follows the barrier waits on memory.
-// The loads of a tile are spread over three k-steps (after the barrier, then steps 0 and 1 of
-// the next tile): issued in one burst they fill the address unit's queue and stall the
+// The loads of a tile are spread over three k-steps (after a barrier, then steps 0 and 1 of
+// the tile after it): issued in one burst they fill the address unit's queue and stall the
 // wave's MFMAs behind them (253 -> 231 us on the gate/up shape with zero operands).
 // The compiler does not order these loads against later LDS reads; the kernel waits with
 // explicit vmcnt/lgkmcnt counts and uses a bare s_barrier (the fence of __syncthreads() is
 // what the counts replace).
 
-template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM>
+template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM, int NST>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kernel(GemmDev p) {
     typedef OpTile<BM, AFORM> TA;
     typedef OpTile<BN, WFORM> TW;
@@ -616,9 +618,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
     constexpr int NFRAG = TM + TN, NMFMA = TM * TN;
     constexpr int AR = AFORM == OP_KMAJOR ? 1 : 2, WR = WFORM == OP_KMAJOR ? 1 : 2;   // LDS reads per fragment
     constexpr int M_MFMA = 0x008, M_VMEM_RD = 0x020, M_DS_RD = 0x100;
-    // s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt<<4 | lgkmcnt<<8 | vmcnt[5:4]<<14)
-    constexpr int WAIT_VM0_LGKM0 = (0 & 15) | (7 << 4) | (0 << 8) | (0 << 14);
-    constexpr int WAIT_VM_AFTER = (N_AFTER & 15) | (7 << 4) | (15 << 8) | ((N_AFTER >> 4) << 14);
+    // loads of later tiles that may still be in flight when a tile is needed
+    constexpr int LATER = (NST - 2) * NI;
+    static_assert(LATER + N_AFTER < 64, "fits the load counter");
 
     bf16x8_t af[2][TM], wf[2][TN];
     auto load_frags = [&](const unsigned char* tile, int ks, int buf) {
@@ -637,21 +639,25 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
                 acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][j], af[buf][i], acc[j][i], 0, 0, 0);
     };
 
-    SP_DMA_ISSUE(0, 0);
-    SP_DMA_ISSUE_R(1, 1, 0, N_AFTER);
-    __builtin_amdgcn_s_waitcnt(WAIT_VM_AFTER);      // this thread's loads of tile 0 have landed
+#pragma unroll
+    for (int t = 0; t < NST - 1; ++t) SP_DMA_ISSUE(t, t);
+    SP_DMA_ISSUE_R(NST - 1, NST - 1, 0, N_AFTER);
+    __builtin_amdgcn_s_waitcnt(sp_waitcnt(LATER + N_AFTER, 15));      // this thread's loads of tile 0 have landed
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     load_frags(smem, 0, 0);
+    int st = 0;                                        // stage of tile kt
     for (int kt = 0; kt < KT; ++kt) {
-        unsigned char* cur = smem + (kt & 1) * STAGE;
-        unsigned char* nxt = smem + ((kt + 1) & 1) * STAGE;
-        // the rest of tile kt+1's loads (its first N_AFTER went out after the last barrier)
-        SP_DMA_ISSUE_R(kt + 1, (kt + 1) & 1, N_AFTER, N_AFTER + N_STEP0);
+        const int st1 = st + 1 == NST ? 0 : st + 1;
+        [[maybe_unused]] const int st_last = st == 0 ? NST - 1 : st - 1;
+        unsigned char* cur = smem + st * STAGE;
+        unsigned char* nxt = smem + st1 * STAGE;
+        // the rest of tile kt+NST-1's loads (its first N_AFTER went out after the last barrier)
+        SP_DMA_ISSUE_R(kt + NST - 1, st_last, N_AFTER, N_AFTER + N_STEP0);
         load_frags(cur, 1, 1);
         mfmas(0);
-        SP_DMA_ISSUE_R(kt + 1, (kt + 1) & 1, N_AFTER + N_STEP0, NI);
+        SP_DMA_ISSUE_R(kt + NST - 1, st_last, N_AFTER + N_STEP0, NI);
         load_frags(cur, 2, 0);
         mfmas(1);
         load_frags(cur, 3, 1);
@@ -668,14 +674,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
         SP_SCHED_STEP(NI - N_AFTER - N_STEP0)
         SP_SCHED_STEP(0)
 #undef SP_SCHED_STEP
-        // This wave's reads of tile kt are complete and its loads of tile kt+1 (issued one tile
-        // ago) have landed; after the barrier that holds for every wave, so the other stage is
+        // This wave's reads of tile kt are complete and its loads of tile kt+1 (issued NST-1 tiles
+        // ago) have landed; after the barrier that holds for every wave, so the next stage is
         // readable and this stage may be refilled.
-        __builtin_amdgcn_s_waitcnt(WAIT_VM0_LGKM0);
+        __builtin_amdgcn_s_waitcnt(sp_waitcnt(LATER, 0));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        SP_DMA_ISSUE_R(kt + 2, kt & 1, 0, N_AFTER);
+        SP_DMA_ISSUE_R(kt + NST, st, 0, N_AFTER);
         load_frags(nxt, 0, 0);
         mfmas(1);
 #pragma unroll
@@ -685,20 +691,22 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
             else __builtin_amdgcn_sched_group_barrier(M_DS_RD, WR, 0);
         }
         if (NMFMA % NFRAG) __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA % NFRAG, 0);
+        st = st1;
     }
-    __builtin_amdgcn_s_waitcnt(WAIT_VM0_LGKM0);   // drain the tail's idle loads
-    gemm_epilogue_staged<EPI, TM, TN, BM, BN_OUT, WAVES * 64, 2 * STAGE>(p, acc, smem, m0, n0, wm * WMR,
+    __builtin_amdgcn_s_waitcnt(sp_waitcnt(0, 0));   // drain the tail's idle loads
+    gemm_epilogue_staged<EPI, TM, TN, BM, BN_OUT, WAVES * 64, NST * STAGE>(p, acc, smem, m0, n0, wm * WMR,
                                                                          SWIGLU ? wn * (WN / 2) : wn * WN, l32, half);
 #undef SP_DMA_ISSUE
 #undef SP_DMA_ISSUE_R
 }
 
-template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM>
+template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM, int NST = 2>
 hipError_t launch_dma(hipStream_t st, const GemmArgs& g) {
-    constexpr int LDS = 2 * (BM + BN) * ROW_BYTES;
+    constexpr int LDS = NST * (BM + BN) * ROW_BYTES;
+    static_assert(LDS <= 160 * 1024, "the stages fit a CU's LDS");
     constexpr int BN_OUT = (EPI == EPI_SWIGLU_BF16) ? BN / 2 : BN;
     static LdsLimitOnce lds_limit;
-    hipError_t e = lds_limit.set(reinterpret_cast<const void*>(gemm_dma_kernel<BM, BN, EPI, AFORM, WFORM, WAVES, WM>), LDS);
+    hipError_t e = lds_limit.set(reinterpret_cast<const void*>(gemm_dma_kernel<BM, BN, EPI, AFORM, WFORM, WAVES, WM, NST>), LDS);
     if (e != hipSuccess) return e;
     GemmDev d;
     d.A = g.A; d.W = g.W; d.C = g.C; d.R = g.R; d.bias = g.bias;
@@ -706,7 +714,7 @@ hipError_t launch_dma(hipStream_t st, const GemmArgs& g) {
     d.M = g.M; d.N = g.N; d.K = g.K;
     d.tilesM = (g.M + BM - 1) / BM;
     d.tilesN = (g.N + BN_OUT - 1) / BN_OUT;
-    gemm_dma_kernel<BM, BN, EPI, AFORM, WFORM, WAVES, WM><<<d.tilesM * d.tilesN, WAVES * 64, LDS, st>>>(d);
+    gemm_dma_kernel<BM, BN, EPI, AFORM, WFORM, WAVES, WM, NST><<<d.tilesM * d.tilesN, WAVES * 64, LDS, st>>>(d);
     return hipGetLastError();
 }
 
@@ -746,12 +754,12 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& g) {
 // (Activation rows are contiguous in A, C and R, so a launch can be cut along M.)
 struct TileCost { int id, bm, bn, concurrent; float eff, single; };   // single: a CU's time with one of its two tiles
 constexpr TileCost kDmaTiles[] = {{5, 256, 256, 256, 1.00f, 1.f}, {10, 256, 320, 256, 1.02f, 1.f}, {8, 256, 192, 256, 0.85f, 1.f},
-                                  {6, 128, 256, 256, 0.72f, 1.f}, {7, 128, 128, 512, 0.70f, 1.f}};
-// An operand with the row index contiguous.  Measured on 32 backward shapes (T 1500..16384, d 1280..4096): picks the
-// fastest of the five in all but three, those within 7 %.  One 128x128 tile alone on its CU takes 0.83 of the time
-// of two (115 us for 256 tiles of K = 8192, 139 us for 400).
+                                  {6, 128, 256, 256, 0.84f, 1.f}, {7, 128, 128, 512, 0.70f, 1.f}};
+// An operand with the row index contiguous.  Against 32 measured backward shapes (T 1500..16384, d 1280..4096) this
+// picks the fastest of the five or one within 7 %.  One 128x128 tile alone on its CU takes 0.83 of the time of two
+// (115 us for 256 tiles of K = 8192, 139 us for 400), the 128x256 tile less than either (104 us, 125 us).
 constexpr TileCost kDmaTilesR[] = {{5, 256, 256, 256, 1.00f, 1.f}, {10, 256, 320, 256, 1.05f, 1.f}, {8, 256, 192, 256, 0.88f, 1.f},
-                                   {6, 128, 256, 256, 0.73f, 1.f}, {7, 128, 128, 512, 0.80f, 1.5f}};
+                                   {6, 128, 256, 256, 0.84f, 1.f}, {7, 128, 128, 512, 0.80f, 2.f}};
 constexpr TileCost kRegTiles[] = {{4, 256, 256, 256, 1.00f, 1.f}, {1, 128, 128, 512, 0.66f, 1.f}};
 
 template <int NC>
@@ -856,7 +864,7 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
         case 3: return launch_one<256, 256, EPI, AFORM, WFORM, 4>(st, g);
         case 4: return launch_one<256, 256, EPI, AFORM, WFORM, 8>(st, g);
         case 5: return launch_dma<256, 256, EPI, AFORM, WFORM, 8, 2>(st, g);
-        case 6: return launch_dma<128, 256, EPI, AFORM, WFORM, 8, 2>(st, g);
+        case 6: return launch_dma<128, 256, EPI, AFORM, WFORM, 8, 2, 3>(st, g);
         case 7: return launch_dma<128, 128, EPI, AFORM, WFORM, 4, 2>(st, g);
         case 8: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 192, NOSWIGLU, AFORM, WFORM, 8, 4>(st, g); break;
         case 10: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 320, NOSWIGLU, AFORM, WFORM, 8, 4>(st, g); break;
