@@ -5,6 +5,7 @@
 // and across window settings.
 #include "sp_common.h"
 #include "sp_kernels.h"
+#include "sp_norm_bwd.h"
 
 namespace {
 
@@ -72,8 +73,9 @@ __global__ __launch_bounds__(TH) void swiglu_bwd_kernel(const bf16_t* __restrict
 
 // ---- RMSNorm backward -----------------------------------------------------------------
 // a = h r g, r = rsqrt(mean(h^2)+eps).  Given da:  dh_io += r (da g) - h r^3 mean(da g h);
-// dgain = sum_t da h r.  Block b owns rows b, b+G, ...; each thread keeps the gain
-// gradient of its columns in registers and writes one partial row per block.
+// dgain = sum_t da h r.  Few rows: block b owns rows b, b+G, ...; each thread keeps the gain
+// gradient of its columns in registers and writes one partial row per block.  (Many rows:
+// norm_bwd_rows_kernel.)
 constexpr int NB_MAXV = 8;   // float4 per thread -> d <= 8192
 
 __global__ __launch_bounds__(TH) void rmsnorm_bwd_kernel(const float* __restrict__ da, const float* __restrict__ h,
@@ -141,99 +143,6 @@ __global__ __launch_bounds__(TH) void rmsnorm_bwd_kernel(const float* __restrict
 }
 
 
-// The same for rows of at most 2048 elements with ONE WAVE PER ROW: a lane holds d/64 elements of
-// the row (at most eight float4), the two row sums are wave shuffles, and no barrier separates
-// the rows, so a work-group of eight waves keeps eight rows' loads in flight (the
-// row-per-work-group form above spends most of its time in its four barriers per row: 2.4 TB/s on
-// 8192 x 2048).  The waves' gain-gradient partials are added into LDS in wave order at the end:
-// one partial row per work-group.
-constexpr int NW_MAXV = 8;    // float4 per lane -> d <= 2048
-constexpr int NW_WAVES = 8;
-
-__global__ __launch_bounds__(NW_WAVES * 64) void rmsnorm_bwd_wave_kernel(
-    const float* __restrict__ da, const float* __restrict__ h, const bf16_t* __restrict__ gain, float* __restrict__ dh_io,
-    bf16_t* __restrict__ dhb, float* __restrict__ part, int T, int d, float eps) {
-    __shared__ float4 lds[64 * NW_MAXV];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nv = d >> 2;
-    float4 gacc[NW_MAXV], gv[NW_MAXV];
-#pragma unroll
-    for (int i = 0; i < NW_MAXV; ++i) {
-        gacc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int idx = lane + i * 64;
-        if (idx < nv) {
-            const uint2 g = reinterpret_cast<const uint2*>(gain)[idx];
-            gv[i] = make_float4(bf_lo(g.x), bf_hi(g.x), bf_lo(g.y), bf_hi(g.y));
-        }
-    }
-    for (int row = blockIdx.x * NW_WAVES + wave; row < T; row += gridDim.x * NW_WAVES) {
-        const float4* hp = reinterpret_cast<const float4*>(h + (size_t)row * d);
-        const float4* ap = reinterpret_cast<const float4*>(da + (size_t)row * d);
-        float4* op = reinterpret_cast<float4*>(dh_io + (size_t)row * d);
-        float4 hv[NW_MAXV], av[NW_MAXV], ov[NW_MAXV];
-#pragma unroll
-        for (int i = 0; i < NW_MAXV; ++i) {
-            const int idx = lane + i * 64;
-            if (idx < nv) { hv[i] = hp[idx]; av[i] = ap[idx]; ov[i] = op[idx]; }
-        }
-        float ss = 0.f, dot = 0.f;
-#pragma unroll
-        for (int i = 0; i < NW_MAXV; ++i) {
-            const int idx = lane + i * 64;
-            if (idx < nv) {
-                ss += (hv[i].x * hv[i].x + hv[i].y * hv[i].y) + (hv[i].z * hv[i].z + hv[i].w * hv[i].w);
-                dot += (av[i].x * gv[i].x * hv[i].x + av[i].y * gv[i].y * hv[i].y) +
-                       (av[i].z * gv[i].z * hv[i].z + av[i].w * gv[i].w * hv[i].w);
-            }
-        }
-        ss = wave_sum(ss);
-        dot = wave_sum(dot);
-        const float r = rsqrtf(ss / (float)d + eps);
-        const float c = r * r * r * dot / (float)d;
-        uint2* bp = reinterpret_cast<uint2*>(dhb + (size_t)row * d);
-#pragma unroll
-        for (int i = 0; i < NW_MAXV; ++i) {
-            const int idx = lane + i * 64;
-            if (idx < nv) {
-                float4 o = ov[i];
-                o.x += r * av[i].x * gv[i].x - hv[i].x * c;
-                o.y += r * av[i].y * gv[i].y - hv[i].y * c;
-                o.z += r * av[i].z * gv[i].z - hv[i].z * c;
-                o.w += r * av[i].w * gv[i].w - hv[i].w * c;
-                op[idx] = o;
-                bp[idx] = make_uint2(pack_bf2(o.x, o.y), pack_bf2(o.z, o.w));
-                gacc[i].x += av[i].x * hv[i].x * r;
-                gacc[i].y += av[i].y * hv[i].y * r;
-                gacc[i].z += av[i].z * hv[i].z * r;
-                gacc[i].w += av[i].w * hv[i].w * r;
-            }
-        }
-    }
-    // wave 0 stores its partial, waves 1 .. 7 add theirs one after the other: a fixed order
-    for (int w = 0; w < NW_WAVES; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int i = 0; i < NW_MAXV; ++i) {
-                float4 g = gacc[i];
-                if (w) {
-                    const float4 o = lds[i * 64 + lane];
-                    g.x += o.x; g.y += o.y; g.z += o.z; g.w += o.w;
-                }
-                lds[i * 64 + lane] = g;
-            }
-        }
-        __syncthreads();
-    }
-    if (wave == 0) {
-        float4* pp = reinterpret_cast<float4*>(part + (size_t)blockIdx.x * d);
-#pragma unroll
-        for (int i = 0; i < NW_MAXV; ++i) {
-            const int idx = lane + i * 64;
-            if (idx < nv) pp[idx] = lds[i * 64 + lane];
-        }
-    }
-}
-
 __global__ __launch_bounds__(TH) void colsum_final_kernel(const float* __restrict__ part, int nparts, int d,
                                                           float* __restrict__ out) {
     __shared__ float lds[256];
@@ -247,25 +156,27 @@ __global__ __launch_bounds__(TH) void f32_to_bf16_kernel(const float4* __restric
     }
 }
 
-// delta[b,h,s] = sum_e dO[t, h*hd+e] * O[t, h*hd+e]: one wave per (token, head)
+// delta[b,h,s] = sum_e dO[t, h*hd+e] * O[t, h*hd+e]: 16 lanes per (token, head), 16 bytes of each per lane
+// (V = 8; 4 bytes where rows or pointers do not allow more).  HBM-bound; with one wave per (token, head) and 4 bytes per lane 106 us for 16384 x 4096 (2.5 TB/s).
+template <int V>
 __global__ __launch_bounds__(TH) void attn_delta_kernel(const bf16_t* __restrict__ dO, const bf16_t* __restrict__ O,
                                                         float* __restrict__ delta, int B, int S, int Hq, int hd) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int sub = threadIdx.x & 15;
     const size_t total = (size_t)B * S * Hq;
-    for (size_t it = (size_t)blockIdx.x * 4 + wave; it < total; it += (size_t)gridDim.x * 4) {
-        const size_t tok = it / Hq;
-        const int hh = (int)(it - tok * Hq);
-        const size_t base = tok * (size_t)Hq * hd + (size_t)hh * hd;
+    for (size_t it = (size_t)blockIdx.x * (TH / 16) + (threadIdx.x >> 4); it < total; it += (size_t)gridDim.x * (TH / 16)) {
         float s = 0.f;
-        for (int e = lane * 2; e < hd; e += 128) {
-            const uint32_t a = *reinterpret_cast<const uint32_t*>(dO + base + e);
-            const uint32_t b = *reinterpret_cast<const uint32_t*>(O + base + e);
-            s += bf_lo(a) * bf_lo(b) + bf_hi(a) * bf_hi(b);
+        for (int e = sub * V; e < hd; e += 16 * V) {
+            typedef uint32_t vec_t __attribute__((ext_vector_type(V / 2)));
+            const vec_t a = *reinterpret_cast<const vec_t*>(dO + it * hd + e);
+            const vec_t b = *reinterpret_cast<const vec_t*>(O + it * hd + e);
+#pragma unroll
+            for (int k = 0; k < V / 2; ++k) s += bf_lo(a[k]) * bf_lo(b[k]) + bf_hi(a[k]) * bf_hi(b[k]);
         }
-        s = wave_sum(s);
-        if (lane == 0) {
-            const size_t bb = tok / S, ss = tok - bb * S;
-            delta[(bb * Hq + hh) * S + ss] = s;
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (sub == 0) {
+            const size_t tok = it / Hq, bb = tok / S;
+            delta[(bb * Hq + it - tok * Hq) * S + tok - bb * S] = s;
         }
     }
 }
@@ -300,11 +211,9 @@ hipError_t spk_launch_rmsnorm_bwd(hipStream_t st, const float* da, const float* 
                                   bf16_t* dhb, float* part, float* dgain, int T, int d, float eps) {
     if (T <= 0) return hipSuccess;
     if (d <= 0 || (d & 3) || d > TH * NB_MAXV * 4) return hipErrorInvalidValue;
-    // which form runs depends on the row length and the row count only
-    const bool per_wave = d <= 64 * NW_MAXV * 4 && T >= 4 * SPK_NORM_BWD_BLOCKS;   // enough rows for every wave
-    const int nb = per_wave ? SPK_NORM_BWD_BLOCKS : std::min(T, SPK_NORM_BWD_BLOCKS);
-    if (per_wave)
-        rmsnorm_bwd_wave_kernel<<<nb, NW_WAVES * 64, 0, st>>>(da, h, gain, dh_io, dhb, part, T, d, eps);
+    const int nb = std::min(T, SPK_NORM_BWD_BLOCKS);
+    if (norm_bwd_rows_fit<false>(T, d))
+        launch_norm_bwd_rows<false>(st, da, h, gain, dh_io, dhb, part, T, d, eps);
     else
         rmsnorm_bwd_kernel<<<nb, TH, 0, st>>>(da, h, gain, dh_io, dhb, part, T, d, eps);
     hipError_t e = hipGetLastError();
@@ -325,6 +234,10 @@ hipError_t spk_launch_attn_delta(hipStream_t st, const bf16_t* dO, const bf16_t*
                                  int Hq, int hd) {
     if (B <= 0 || S <= 0) return hipSuccess;
     if (hd & 1) return hipErrorInvalidValue;
-    attn_delta_kernel<<<grid_for((size_t)B * S * Hq, 4), TH, 0, st>>>(dO, O, delta, B, S, Hq, hd);
+    const int grid = grid_for((size_t)B * S * Hq, TH / 16);
+    if (hd % 8 == 0 && (((uintptr_t)dO | (uintptr_t)O) & 15) == 0)
+        attn_delta_kernel<8><<<grid, TH, 0, st>>>(dO, O, delta, B, S, Hq, hd);
+    else
+        attn_delta_kernel<2><<<grid, TH, 0, st>>>(dO, O, delta, B, S, Hq, hd);
     return hipGetLastError();
 }

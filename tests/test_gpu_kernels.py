@@ -492,6 +492,14 @@ def test_layernorm_backward(T, d):
     assert np.all(np.abs(bf16_vals(host_u16(dhb)) - got) <= BF16_EPS * np.abs(got) + 1e-12)
 
 
+@pytest.mark.parametrize("T,d", [(1024, 64), (1501, 2048), (1100, 2052), (1030, 4096), (2050, 4100), (1025, 8192)])
+def test_norm_backward_many_rows(T, d):
+    """1024 rows and more: a row held by one, two or four waves (RMSNorm; LayerNorm up to 4096 elements), at
+    and past each limit, row counts that leave the last work-groups short."""
+    test_rmsnorm_backward(T, d)
+    test_layernorm_backward(T, d)
+
+
 @pytest.mark.parametrize("n", [8, 4096 * 33, 5120 * 7])
 def test_gelu_and_its_backward(n):
     rng = np.random.default_rng(n)
@@ -524,3 +532,11 @@ def test_column_sums(T, n, ld):
     ref = s[:, :n].sum(axis=0)
     assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5 * np.sqrt(T) * max(np.max(np.abs(ref)), 1.0)
     assert sp.spk_colsum_bf16(stream_ptr(), ptr(sd), ld, T, 3, ptr(scratch), ptr(out)) == sp.SP_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("T,n,ld", [(8224, 1280, 1280), (4100, 264, 264), (31, 1280, 1280), (33, 520, 1040), (1, 8, 8),
+                                    (257, 40, 48), (1000, 3844, 3844), (700, 264, 266)])
+def test_column_sums_sixteen_byte_rows(T, n, ld):
+    """Rows on 16 bytes: one and several column blocks, a ragged last one, fewer rows than a load round; widths
+    and strides that are no multiple of eight stay with the 4-byte kernel."""
+    test_column_sums(T, n, ld)
