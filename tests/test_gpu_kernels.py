@@ -467,6 +467,19 @@ def test_attention_backward(B, S, Hq, Hkv, hd, causal):
         assert err <= 1.5e-2, (name, err)
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,hd,causal", [
+    (1, 2, 2, 1, 128, 1), (1, 31, 2, 2, 128, 0), (1, 64, 2, 2, 128, 1), (1, 65, 2, 1, 128, 0), (2, 129, 2, 2, 128, 1),
+    (1, 257, 4, 2, 128, 1), (1, 191, 2, 2, 128, 0),
+    (1, 2, 2, 2, 80, 0), (1, 129, 2, 2, 80, 1), (1, 64, 2, 2, 80, 0), (2, 161, 2, 1, 80, 0),
+    (1, 2, 2, 2, 64, 1), (1, 193, 4, 2, 64, 1), (1, 160, 2, 2, 64, 0), (1, 384, 2, 2, 64, 1),
+])
+def test_attention_backward_tile_edges(B, S, Hq, Hkv, hd, causal):
+    """Around the 32-row halves, 64-row tiles and 128-row blocks: a last tile of 1, 31, 32, 33, 63, 64 rows, key
+    blocks with idle key groups, fewer rows than a tile (the second half of the keys clamped), several heads per
+    key head."""
+    test_attention_backward(B, S, Hq, Hkv, hd, causal)
+
+
 @pytest.mark.parametrize("T,d", [(300, 256), (37, 1280), (5, 8192), (700, 320)])
 def test_layernorm_backward(T, d):
     rng = np.random.default_rng(T * 5 + d)
