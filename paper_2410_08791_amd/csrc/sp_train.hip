@@ -115,6 +115,11 @@ float* saved_input(sp_engine* e, int layer, int T) {
     return e->wsp<float>(e->ws.xs) + (size_t)layer * T * e->desc.d_model;
 }
 
+// Whether a layer's backward finds its activations as the forward left them: when every layer keeps its own
+// set, and for the last layer in any case -- only the loss runs between its forward and its backward, on other
+// buffers.  (7B-shaped layers, 16384 tokens: its recomputation was 5.0 of a three-layer step's 95 ms.)
+bool activations_in_place(const sp_engine* e, int layer) { return e->ws.set_stride || layer + 1 == e->desc.n_layers; }
+
 }  // namespace
 
 int sp_train_begin(sp_engine* e, const float* x_dev, int B, int S) {
@@ -148,8 +153,8 @@ int sp_layer_forward_train(sp_engine* e, int layer, const unsigned char* w, int 
     // loss kernel then turns into dy in place)
     float* out = layer + 1 < L ? saved_input(e, layer + 1, T) : (e->y_out ? e->y_out : e->wsp<float>(e->ws.dh));
     const ActSet as_ = act_set(e, layer);
-    // with kept activations the forward also produces what the backward needs (log-sum-exp)
-    LayerBufs b{saved_input(e, layer, T), as_.h1, out, e->ws.set_stride ? as_.lse : nullptr};
+    // where the backward will find the activations in place it needs the log-sum-exp too
+    LayerBufs b{saved_input(e, layer, T), as_.h1, out, activations_in_place(e, layer) ? as_.lse : nullptr};
     return layer_keep(e, w, as_, b, B, S);
 }
 
@@ -194,8 +199,8 @@ int sp_layer_backward(sp_engine* e, int layer, const unsigned char* w, int B, in
     AttnShape as{B, S, d.n_q_heads, d.n_kv_heads, d.head_dim, d.causal, nqkv};
     GemmArgs g;
 
-    // recompute a, qkv, o, lse, h1, m, gu, z from the saved input -- unless the forward kept them
-    if (!e->ws.set_stride) {
+    // recompute a, qkv, o, lse, h1, m, gu, z from the saved input -- unless they are in place
+    if (!activations_in_place(e, layer)) {
         LayerBufs lb{x_l, h1, nullptr, lse};
         int rc = layer_keep(e, w, as_, lb, B, S);
         if (rc != SP_OK) return rc;
