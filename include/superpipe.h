@@ -22,12 +22,15 @@
  *  - Calls enqueue work and return; outputs are valid after the caller
  *    synchronises compute_stream (gradient blobs: d2h_stream).  Three places
  *    block the host, none for longer than the work already enqueued: (1) the
- *    run-ahead bound -- when about 1400 kernel launches and event records of a
- *    handle are still unfinished on its compute stream, the next layer's enqueue
- *    waits until about 350 are left (every call kind; a deep stack reaches the
- *    bound inside one call; beyond it this HIP runtime was measured to run whole
- *    passes 30-60 % slower); (2) sp_forward_backward waits at entry for the
- *    previous step's last gradient; (3) sp_wait_gradient, sp_get_stats with a
+ *    run-ahead bound -- when about 450 kernel launches and event records of a
+ *    forward handle (1400 of a training handle) are still unfinished on its
+ *    compute stream, the next layer's enqueue waits until about 200 (350) are
+ *    left (every call kind; a deep stack reaches the bound inside one call;
+ *    beyond about 1500 this HIP runtime was measured to run whole passes 30-60 %
+ *    slower); (2) sp_forward_backward waits at entry for the last gradient of the
+ *    previous step, its own and that of any other handle of the device that the
+ *    same host thread called (gradient copies submitted while others execute run
+ *    at a fraction of the link rate); (3) sp_wait_gradient, sp_get_stats with a
  *    timing flag, and sp_destroy wait for what they name.
  *  - Kernel and tile choice depend on the shapes in sp_stack_desc and on B, S only:
  *    never on the window, the slot address or the process environment (the library
@@ -207,7 +210,7 @@ typedef struct {
     sp_plan plan;
     uint64_t calls;             /* completed sp_forward / sp_forward_backward calls   */
     uint64_t h2d_copies, h2d_bytes;   /* totals since create                            */
-    uint64_t d2h_copies, d2h_bytes;
+    uint64_t d2h_copies, d2h_bytes;   /* layers whose gradients were sent (a large one in three pieces), bytes */
     uint64_t last_h2d_copies, last_h2d_bytes;  /* issued by the most recent call        */
     /* SP_FLAG_TIMING only; describe the most recent call, valid after its streams
      * are synchronised.  Times in ms relative to the call's first enqueued op.        */
@@ -372,7 +375,9 @@ int sp_decode(sp_handle h, const float* x_dev, float* y_dev, void* kv_cache_dev,
  * The call returns once the step is enqueued.  At most one training step is in
  * flight per handle: a call first blocks the host until the previous step's
  * last gradient has landed (the point its consumer, the host-side optimizer,
- * has to wait for anyway before the weights of the next step exist). */
+ * has to wait for anyway before the weights of the next step exist), and, of the
+ * handles that one host thread drives on one device, one step's gradients are in
+ * flight. */
 int sp_forward_backward(sp_handle h, const float* x_dev, const float* target_dev, float* y_dev,
                         float* loss_dev, float* dx_dev, void* const* grad_host_blobs, int B, int S);
 

@@ -2,12 +2,15 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <memory>
 #include <set>
 #include <string>
 #include <vector>
 
 #include "sp_host.h"
 #include "sp_kernels.h"
+
+struct sp_pass_end;
 
 struct sp_engine {
     sp_stack_desc desc;
@@ -53,7 +56,9 @@ struct sp_engine {
     std::vector<hipEvent_t> thr_ev;
     std::vector<uint64_t> thr_at;
     uint64_t thr_head = 0, thr_tail = 0, thr_packets = 0;
-    hipEvent_t pass_end_c = nullptr, pass_end_d = nullptr;   // end of the latest training pass on compute / d2h
+    hipEvent_t pass_end_c = nullptr;             // end of the latest training pass on compute ...
+    std::shared_ptr<sp_pass_end> pass_end;       // ... and on d2h
+    int device = 0;
     bool pass_pending = false;
     int frozen = 0;                             // training: layers below this get no weight gradients
     hipEvent_t grad_ready[sp::kGradSlots] = {}, gslot_free[sp::kGradSlots] = {};

@@ -21,6 +21,7 @@
 #include <unistd.h>
 
 #include <algorithm>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <set>
@@ -58,8 +59,10 @@ int sp_fail(sp_engine* e, int code, const char* fmt, ...) {
 // more than roughly 1500 packets (kernels and event records) wait on the compute stream,
 // passes take 30-60 % longer in bursts; below that every pass runs at its steady time.  A
 // host-side wait is not free either (the copies of the next layers are enqueued late), so
-// waits are made rare: when more than kMaxQueuedPackets are unfinished the host sleeps
-// until kResumePackets are left, then runs ahead again.
+// waits are made rare: when more than max_packets may be unfinished the host sleeps
+// until resume_packets are left, then runs ahead again.  Forward passes wait at 450: the 1500
+// are a process's, and three ViT-H handles called in turn stayed at 29.5-33 ms a pass with 1400
+// each, 26.2 with 450 (one handle: 26.4-27.0 and 26.2; the link-bound 7B stack equal).
 //
 // Gradient copies add a second rule, also measured: a device-to-host copy that is
 // submitted while an earlier one of the same stream is executing runs at a quarter of
@@ -70,16 +73,19 @@ int sp_fail(sp_engine* e, int code, const char* fmt, ...) {
 // submitted before the first one starts), and when a wait inside a backward pass cannot
 // be avoided the host also lets the gradient stream drain before it goes on.
 // Per-op packet counts are estimates; the ring is longer than any window they allow.
-constexpr uint64_t kMaxQueuedPackets = 1400;
-constexpr uint64_t kResumePackets = 350;
+constexpr uint64_t kMaxQueuedForward = 450, kResumeForward = 200;
+constexpr uint64_t kMaxQueuedTraining = 1400, kResumeTraining = 350;
 constexpr size_t kThrottleRing = 256;
 constexpr unsigned kPacketsForward = 16, kPacketsForwardTrain = 14, kPacketsBackward = 44;
 
 static int throttle_before(sp_engine* e) {
+    const bool training = e->flags & SP_FLAG_TRAINING;
+    const uint64_t max_packets = training ? kMaxQueuedTraining : kMaxQueuedForward;
+    const uint64_t resume_packets = training ? kResumeTraining : kResumeForward;
     auto left_after = [&](uint64_t i) { return e->thr_packets - e->thr_at[i % kThrottleRing]; };
     if (e->thr_tail < e->thr_head &&
-        (left_after(e->thr_tail) > kMaxQueuedPackets || e->thr_head - e->thr_tail >= kThrottleRing)) {
-        while (e->thr_tail + 1 < e->thr_head && left_after(e->thr_tail + 1) > kResumePackets) e->thr_tail++;
+        (left_after(e->thr_tail) > max_packets || e->thr_head - e->thr_tail >= kThrottleRing)) {
+        while (e->thr_tail + 1 < e->thr_head && left_after(e->thr_tail + 1) > resume_packets) e->thr_tail++;
         SP_HIP(e, hipEventSynchronize(e->thr_ev[e->thr_tail % kThrottleRing]));
         e->thr_tail++;
         if (e->last_grad_copy) SP_HIP(e, hipEventSynchronize(e->last_grad_copy));
@@ -95,6 +101,26 @@ static int throttle_after(sp_engine* e, unsigned packets) {
     e->thr_head++;
     return SP_OK;
 }
+
+// The same rule between handles: gradient copies submitted while another handle's are executing on the
+// device take the slow path too (three handles trained in turn: 1.3B-shaped steps 51-60 ms instead of 32,
+// ViT-H steps 14-19 instead of 13).  A training step therefore also waits for the gradients of the latest
+// step that this host thread enqueued on the device through another handle.  Per thread: handles driven by
+// threads of their own never wait for each other.
+struct sp_pass_end {
+    hipEvent_t d2h = nullptr;
+    ~sp_pass_end() { if (d2h) (void)hipEventDestroy(d2h); }
+};
+static thread_local std::vector<std::pair<int, std::shared_ptr<sp_pass_end>>> t_last_pass;   // one per device
+
+static std::shared_ptr<sp_pass_end>& last_pass_on(int device) {
+    for (auto& p : t_last_pass) if (p.first == device) return p.second;
+    t_last_pass.emplace_back(device, nullptr);
+    return t_last_pass.back().second;
+}
+// the device of an allocation (the host-only stand-in of the tests knows one device and has no such field)
+template <class A> static auto device_of(const A& at, int) -> decltype(at.device) { return at.device; }
+template <class A> static int device_of(const A&, long) { return 0; }
 
 // ---- debug delays (SP_FLAG_DELAY) -----------------------------------------------------
 // Before an operation is enqueued the host sleeps and the operation's stream idles, each for a
@@ -381,7 +407,13 @@ extern "C" int sp_create(sp_handle* out, const sp_stack_desc* desc, const void* 
     e->thr_at.assign(kThrottleRing, 0);
     for (size_t i = 0; i < kThrottleRing && he == hipSuccess; ++i) he = mk(&e->thr_ev[i], hipEventDisableTiming);
     if (he == hipSuccess && training) he = mk(&e->pass_end_c, hipEventDisableTiming);
-    if (he == hipSuccess && training) he = mk(&e->pass_end_d, hipEventDisableTiming);
+    if (he == hipSuccess && training) {
+        e->pass_end = std::make_shared<sp_pass_end>();
+        he = mk(&e->pass_end->d2h, hipEventDisableTiming);
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, e->arena) == hipSuccess) e->device = device_of(at, 0);
+        else (void)hipGetLastError();
+    }
     for (int i = 0; i < kGradSlots && he == hipSuccess; ++i) {
         he = mk(&e->grad_ready[i], hipEventDisableTiming);
         if (he == hipSuccess) he = mk(&e->gslot_free[i], hipEventDisableTiming);
@@ -577,10 +609,13 @@ static int enqueue_training_step(sp_engine* e, const float* x_dev, const float* 
     // point anyway, and copies enqueued more than a pass ahead were measured to drop
     // the device-to-host engine to a fraction of the link rate.
     if (e->pass_pending) {
-        SP_HIP(e, hipEventSynchronize(e->pass_end_d));
+        SP_HIP(e, hipEventSynchronize(e->pass_end->d2h));
         SP_HIP(e, hipEventSynchronize(e->pass_end_c));
         e->pass_pending = false;
+        e->thr_tail = e->thr_head;                   // nothing of the previous pass is unfinished
     }
+    std::shared_ptr<sp_pass_end>& last = last_pass_on(e->device);
+    if (last && last != e->pass_end) SP_HIP(e, hipEventSynchronize(last->d2h));
     if ((rc = begin_call(e)) != SP_OK) return rc;
     std::fill(e->grad_sent.begin(), e->grad_sent.end(), 0);
     e->grad_blobs = grad_host_blobs;
@@ -597,8 +632,9 @@ static int enqueue_training_step(sp_engine* e, const float* x_dev, const float* 
     if ((rc = e->sched.run_pass(-1, false, sink, dx_dev ? 0 : e->frozen)) != SP_OK) return rc;
     if ((rc = sp_train_end(e, dx_dev, B, S)) != SP_OK) return rc;
     SP_HIP(e, hipEventRecord(e->pass_end_c, e->compute));
-    SP_HIP(e, hipEventRecord(e->pass_end_d, e->d2h));
+    SP_HIP(e, hipEventRecord(e->pass_end->d2h, e->d2h));
     e->pass_pending = true;
+    last = e->pass_end;
     e->calls++;
     return SP_OK;
 }
@@ -738,7 +774,7 @@ static int destroy_engine(sp_engine* e) {
     kill(e->ev_sync_h);
     for (auto ev : e->thr_ev) kill(ev);
     kill(e->pass_end_c);
-    kill(e->pass_end_d);
+    for (auto& p : t_last_pass) if (p.second == e->pass_end) p.second.reset();
     kill(e->t0);
     for (int i = 0; i < kGradSlots; ++i) { kill(e->grad_ready[i]); kill(e->gslot_free[i]); }
     for (auto ev : e->grad_landed) kill(ev);
