@@ -5,13 +5,15 @@
 // fp32 weight gradients are written into one of a few device gradient slots (same
 // tensor order as the weight blob, offsets doubled) and streamed to the caller's
 // pinned host blob on the device-to-host stream, fenced by one event pair per slot:
-//   grad_ready[g]  compute -> d2h   (gradients of a layer complete)
+//   grad_ready[g]  compute -> d2h   (gradients of a layer, or of a part of a large one, complete)
 //   gslot_free[g]  d2h -> compute   (slot g has been copied out, may be rewritten)
 #include "sp_engine.h"
 
 using namespace sp;
 
 namespace {
+
+constexpr size_t kSplitGradBytes = (size_t)16 << 20;
 
 struct LayerBufs {
     const float* h_in;   // layer input  fp32 [T,d]
@@ -216,11 +218,28 @@ int sp_layer_backward(sp_engine* e, int layer, const unsigned char* w, int B, in
     };
     int rc;
 
+    // A large layer's gradients leave in the three parts of the blob, last first, each as soon as it is complete:
+    // sent in one piece they wait for the whole layer, and the copy of the lowest layer runs with nothing beside it
+    // (7B-shaped layers: 14.7 of a three-layer step's 86 ms).  Below kSplitGradBytes a copy is too short for that
+    // to matter beside its own start-up of some 10 us.
+    const bool split = L.grad_bytes >= kSplitGradBytes;
+    auto send_part = [&](int part) -> int {
+        if (frozen || (part && !split)) return SP_OK;
+        size_t off = 0, len = L.blob_bytes;
+        if (split) unit_range(&d, L, 3, part, &off, &len);
+        SP_HIP(e, hipEventRecord(e->grad_ready[gs], st));
+        SP_HIP(e, hipStreamWaitEvent(e->d2h, e->grad_ready[gs], 0));
+        SP_HIP(e, hipMemcpyAsync(static_cast<unsigned char*>(e->grad_blobs[layer]) + 2 * off, gslot + 2 * off, 2 * len,
+                                 hipMemcpyDeviceToHost, e->d2h));
+        return SP_OK;
+    };
+
     // ---- FFN.  dh is dL/d(layer output); dhb its bf16 copy.
     if (dec) {
         // dWd[d,f] = dh^T z       (contraction over tokens: both operands transposed on the way in)
         g = GemmArgs{dhb, dm, OP_RMAJOR, z, f, OP_RMAJOR, G(SP_T_WD), f, nullptr, 0, nullptr, dm, f, Tp, 0};
         if (!frozen) SP_OP(e, SP_OP_GEMM_DW, spk_launch_gemm(st, EPI_F32, g));
+        if ((rc = send_part(2)) != SP_OK) return rc;
         // dz[T,f] = dh Wd         (Wd is [d,f]: its row index f is contiguous)
         g = GemmArgs{dhb, dm, OP_KMAJOR, W(SP_T_WD), f, OP_RMAJOR, dz, f, nullptr, 0, nullptr, T, f, dm, 0};
         SP_OP(e, SP_OP_GEMM_DX, spk_launch_gemm(st, EPI_BF16, g));
@@ -240,6 +259,7 @@ int sp_layer_backward(sp_engine* e, int layer, const unsigned char* w, int B, in
         // dW2[d,f] = dh^T z
         g = GemmArgs{dhb, dm, OP_RMAJOR, z, f, OP_RMAJOR, G(SP_T_W2), f, nullptr, 0, nullptr, dm, f, Tp, 0};
         if (!frozen) SP_OP(e, SP_OP_GEMM_DW, spk_launch_gemm(st, EPI_F32, g));
+        if ((rc = send_part(2)) != SP_OK) return rc;
         // dz[T,f] = dh W2
         g = GemmArgs{dhb, dm, OP_KMAJOR, W(SP_T_W2), f, OP_RMAJOR, dz, f, nullptr, 0, nullptr, T, f, dm, 0};
         SP_OP(e, SP_OP_GEMM_DX, spk_launch_gemm(st, EPI_BF16, g));
@@ -256,6 +276,8 @@ int sp_layer_backward(sp_engine* e, int layer, const unsigned char* w, int B, in
         SP_OP(e, SP_OP_NORM_BWD, spk_launch_layernorm_bwd(st, da, h1, W(SP_T_LN2_G), dh, dhb, part, G(SP_T_LN2_G), G(SP_T_LN2_B), T,
                                            dm, d.norm_eps));
     }
+
+    if ((rc = send_part(1)) != SP_OK) return rc;
 
     // ---- attention block.  dh is now dL/dh1.
     if (!dec && (rc = bias_grad(dhb, dm, SP_T_BO)) != SP_OK) return rc;
@@ -284,10 +306,8 @@ int sp_layer_backward(sp_engine* e, int layer, const unsigned char* w, int B, in
                                            dm, d.norm_eps));
 
     if (frozen) return SP_OK;
-    // ---- hand the gradient slot to the device-to-host stream
-    SP_HIP(e, hipEventRecord(e->grad_ready[gs], st));
-    SP_HIP(e, hipStreamWaitEvent(e->d2h, e->grad_ready[gs], 0));
-    SP_HIP(e, hipMemcpyAsync(e->grad_blobs[layer], gslot, L.grad_bytes, hipMemcpyDeviceToHost, e->d2h));
+    // ---- the rest of the gradient slot to the device-to-host stream
+    if ((rc = send_part(0)) != SP_OK) return rc;
     SP_HIP(e, hipEventRecord(e->gslot_free[gs], e->d2h));
     SP_HIP(e, hipEventRecord(e->grad_landed[layer], e->d2h));
     e->grad_sent[layer] = 1;

@@ -89,6 +89,22 @@ def test_training_step_matches_oracle(small):
     assert st.h2d_copies == 3          # 3 layers, 3 slots: each layer crosses the link once
 
 
+@pytest.mark.parametrize("arch", ["decoder", "encoder"])
+def test_gradients_of_large_layers_leave_in_parts(arch):
+    """Layers of more than 16 MB of gradients, whose blob goes to the host in three copies: every tensor of it
+    against the oracle, and equal bits from a second step into the same blobs and with a frozen layer below."""
+    c = TrainCase(synth.Workload("train_parts", arch, 2, 768, 12, 12, 64, 2304, arch == "decoder", 1, 72, training=True))
+    assert c.gbytes > 16 << 20
+    got = c.run(1, 1)
+    check_against_oracle(got, c.oracle(), "train_parts " + arch)
+    assert got["stats"].d2h_copies == 2 and got["stats"].d2h_bytes == 2 * c.gbytes
+    again = c.run(1, 1, calls=2)
+    frozen = c.run(1, 1, frozen=1, want_dx=False)
+    for n in got["grads"][1]:
+        assert np.array_equal(got["grads"][0][n], again["grads"][0][n]) and np.array_equal(got["grads"][1][n], again["grads"][1][n])
+        assert np.array_equal(got["grads"][1][n], frozen["grads"][1][n])
+
+
 def test_training_bits_do_not_depend_on_the_window(small):
     base = small.run(8, 8)             # resident
     assert base["stats"].plan.fully_resident
