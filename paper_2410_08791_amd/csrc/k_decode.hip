@@ -77,7 +77,11 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict
 // more than one split the unnormalised rows go to `part` (fp32: HD values, reference maximum in base 2,
 // denominator) and combine_kernel adds them in split order.
 // HBM-bound: 4 n Hkv hd bytes per sequence.
+//
+// A score of -inf has weight 0 whichever positions a wave holds: where every score of a wave or split so far
+// is -inf, 0 stands in for the maximum in the differences taken with it (-inf - -inf would make the row NaN).
 constexpr int DEC_WAVES = 8;
+__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
 
 template <int HD, int G>
 __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
@@ -166,13 +170,14 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
             }
 #pragma unroll
             for (int off = 1; off < 16; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-            const float mn = fmaxf(m[g], mx);            // finite: position t0 is valid
-            const float alpha = __builtin_amdgcn_exp2f(m[g] - mn);
-            m[g] = mn;
+            mx = fmaxf(m[g], mx);
+            const float ref = finite_ref(mx);
+            const float alpha = __builtin_amdgcn_exp2f(m[g] - ref);
+            m[g] = mx;
             float sum = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                a[g][e] = __builtin_amdgcn_exp2f(a[g][e] - mn);
+                a[g][e] = __builtin_amdgcn_exp2f(a[g][e] - ref);
                 sum += a[g][e];
             }
             l[g] = l[g] * alpha + sum;                   // of this lane's positions
@@ -190,6 +195,12 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
                 for (int j = 0; j < VBATCH; ++j)
                     vv[j] = *reinterpret_cast<const u32x4_t*>(V + (size_t)min(t0 + r0 + j * RPI + vrow, w1 - 1) * HD + dp);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if (r0 + VBATCH * RPI > rows) {
+                // rows past the run repeat its last one: cleared, since 0 times an infinite value would be NaN
+#pragma unroll
+                for (int j = 0; j < VBATCH; ++j)
+                    if (r0 + j * RPI + vrow >= rows) vv[j] = u32x4_t{0, 0, 0, 0};
             }
 #pragma unroll
             for (int j = 0; j < VBATCH; ++j) {
@@ -213,6 +224,7 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
         const bf16_t* vn = kn + (size_t)Hkv * HD;
         constexpr int EPL = HD / 64;
         const u32x4_t nv = *reinterpret_cast<const u32x4_t*>(vn + dp);
+        const u32x4_t pv = vrow == 0 ? nv : u32x4_t{0, 0, 0, 0};
         bf16_t kb[EPL];
         float kf[EPL];
 #pragma unroll
@@ -223,14 +235,15 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
 #pragma unroll
             for (int e = 0; e < EPL; ++e) s = fmaf(qs[g][lane + 64 * e], kf[e], s);
             s = wave_sum(s);
-            const float mn = fmaxf(m[g], s), alpha = __builtin_amdgcn_exp2f(m[g] - mn), p = __builtin_amdgcn_exp2f(s - mn);
-            m[g] = mn;
+            const float mx = fmaxf(m[g], s), ref = finite_ref(mx);
+            const float alpha = __builtin_amdgcn_exp2f(m[g] - ref), p = __builtin_amdgcn_exp2f(s - ref);
+            m[g] = mx;
             l[g] = l[g] * alpha + (l16 == 0 ? p : 0.f);
             const float pr = vrow == 0 ? p : 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                oa[g][2 * e] = fmaf(pr, bf_lo(nv[e]), oa[g][2 * e] * alpha);
-                oa[g][2 * e + 1] = fmaf(pr, bf_hi(nv[e]), oa[g][2 * e + 1] * alpha);
+                oa[g][2 * e] = fmaf(pr, bf_lo(pv[e]), oa[g][2 * e] * alpha);
+                oa[g][2 * e + 1] = fmaf(pr, bf_hi(pv[e]), oa[g][2 * e + 1] * alpha);
             }
         }
         if (h0 == 0) {
@@ -266,10 +279,11 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
         float M = wm[0][g];
 #pragma unroll
         for (int k = 1; k < DEC_WAVES; ++k) M = fmaxf(M, wm[k][g]);
+        const float ref = finite_ref(M);
         float L = 0.f, acc = 0.f;
 #pragma unroll
         for (int k = 0; k < DEC_WAVES; ++k) {
-            const float f = __builtin_amdgcn_exp2f(wm[k][g] - M);      // 0 for a wave without positions
+            const float f = __builtin_amdgcn_exp2f(wm[k][g] - ref);      // 0 for a wave without positions
             L = fmaf(f, wl[k][g], L);
             acc = fmaf(f, buf[(k * G + g) * HD + d], acc);
         }
@@ -296,7 +310,7 @@ __global__ __launch_bounds__(HD) void combine_kernel(const float* __restrict__ p
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = j < splits ? p[j * (HD + 2) + d] : 0.f;
-    const float M = wave_max(ml.x);
+    const float M = finite_ref(wave_max(ml.x));
     const float f = on ? __builtin_amdgcn_exp2f(ml.x - M) : 0.f;
     const float L = wave_sum(f * ml.y);
     float acc = 0.f;

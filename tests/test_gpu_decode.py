@@ -69,6 +69,40 @@ def test_append_and_single_query_attention(B, n, max_len, Hq, Hkv, hd):
     assert err <= 8e-3          # one bf16 rounding of the output
 
 
+@pytest.mark.parametrize("B,n,max_len,Hq,Hkv,hd,lo,hi", [
+    (*c, lo, hi) for c in ((1, 700, 704, 2, 1, 64), (2, 1500, 1504, 4, 4, 128), (1, 900, 904, 8, 1, 128))
+    for lo, hi in ((0, 129), (300, 560), (0, 39), (1, 699))
+] + [(1, 40, 48, 3, 1, 64, 0, 39), (1, 40, 48, 3, 1, 64, 5, 30)])
+def test_decode_attention_infinite_keys_and_values(B, n, max_len, Hq, Hkv, hd, lo, hi):
+    """Positions whose score is -inf (an infinite key element against a positive query element) have weight 0,
+    also where they are all that a wave holds; an infinite value of the last position reaches its own element
+    of the output and no other."""
+    rng = np.random.default_rng(n + lo)
+    q = np.abs(rng.standard_normal((B, Hq, hd))) * 0.5
+    k, v = rng.standard_normal((B, Hkv, n, hd)), rng.standard_normal((B, Hkv, n, hd))
+    rnd = lambda a: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(a.astype(np.float32))).astype(np.float64)  # noqa: E731
+    q, k, v = rnd(q), rnd(k), rnd(v)
+    s = np.einsum("bgrd,bgnd->bgrn", q.reshape(B, Hkv, Hq // Hkv, hd), k) / np.sqrt(hd)
+    s[..., lo:hi] = -np.inf
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    ref = np.einsum("bgrn,bgnd->bgrd", p, v).reshape(B, Hq, hd)
+    k[:, :, lo:hi, 5] = -np.inf
+    v[:, :, n - 1, 9] = np.inf
+    kc, vc = np.full((B, Hkv, hd, max_len), np.nan), np.full((B, Hkv, max_len, hd), np.nan)
+    kc[..., :n], vc[:, :, :n] = k.transpose(0, 1, 3, 2), v
+    bits = lambda a: dev_u16(synth.f32_to_bf16_bits(a.astype(np.float32)).reshape(-1))  # noqa: E731
+    qd = bits(np.concatenate([q.reshape(B, -1), np.zeros((B, 2 * Hkv * hd))], axis=1))
+    kd, vd = bits(kc), bits(vc)
+    o = torch.zeros(B * Hq * hd, dtype=torch.int16, device=DEV)
+    assert sp.spk_decode_attention(stream_ptr(), ptr(qd), ptr(kd), ptr(vd), ptr(o), B, n, max_len, Hq, Hkv, hd) == sp.SP_OK
+    torch.cuda.synchronize()
+    got = bf16_vals(host_u16(o)).reshape(B, Hq, hd)
+    assert np.all(got[..., 9] == np.inf)
+    keep = np.arange(hd) != 9
+    assert max_rel(got[..., keep], ref[..., keep]) <= 8e-3          # one bf16 rounding of the output
+
+
 def test_decode_kernel_argument_errors():
     t = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     s = stream_ptr()
