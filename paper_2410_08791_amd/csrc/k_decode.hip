@@ -70,36 +70,40 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict
 // One work-group = one split of the positions for one key/value head and G of the query heads that
 // share it: a cached byte is read once for all G (one work-group per query head read a group's cache
 // Hq / Hkv times and left most of the chip idle for few sequences: 2 x 32/8 heads over 8191 positions
-// 107 us).  Each of the eight waves walks its own run of positions, 128 at a time, with its own running
+// 107 us).  Each of the NW waves walks its own positions, 128 at a time, with its own running
 // maximum, sum and output, and needs no barrier before the end: a lane holds 8 positions (16 bytes of a
 // Kt row), the quarter-waves split the head dimension and add up by two shuffles, so every load is 16
-// bytes and 16 (keys) or 8 (values) of them are in flight per lane.  The waves' results meet in LDS.  With
+// bytes and 16 (keys) or 8 (values) of them are in flight per lane.  A long split is dealt to the waves in
+// steps of 128 positions, so that a work-group reads NW x 256 neighbouring bytes of a Kt row at a time (a run
+// of its own per wave: 64 x 32 heads of 128 over 2000 positions 414 us, 389 so), a short one in NW even runs.
+// Row addresses are a uniform base and one 32-bit lane offset: 64-bit addresses per row took half the
+// registers (196 against 132 at G = 1).  The waves' results meet in LDS.  With
 // more than one split the unnormalised rows go to `part` (fp32: HD values, reference maximum in base 2,
 // denominator) and combine_kernel adds them in split order.
 // HBM-bound: 4 n Hkv hd bytes per sequence.
 //
 // A score of -inf has weight 0 whichever positions a wave holds: where every score of a wave or split so far
 // is -inf, 0 stands in for the maximum in the differences taken with it (-inf - -inf would make the row NaN).
-constexpr int DEC_WAVES = 8;
 __device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
 
-template <int HD, int G>
-__global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
+template <int HD, int G, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
     const bf16_t* __restrict__ qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* __restrict__ o, int ld_o,
-    float* __restrict__ part, int n, int fresh, int per_split, int max_len, int Hq, int Hkv, float scale_log2e) {
+    float* __restrict__ part, int n, int fresh, int splits, int per_split, int max_len, int Hq, int Hkv, float scale_log2e) {
     constexpr int DQ = HD / 4;             // head-dimension elements per quarter-wave in the score pass
     constexpr int LPR = HD / 8;            // lanes per V row
     constexpr int RPI = 64 / LPR;          // V rows per load instruction
     constexpr int TB = 128;                // positions per wave and step
-    constexpr int KBATCH = G == 8 ? 8 : DQ < 16 ? DQ : 16, VBATCH = G == 8 ? 4 : 8;
+    constexpr int KBATCH = 16, VBATCH = 8;
     __shared__ float qs[G][HD];
-    __shared__ __attribute__((aligned(16))) float buf[DEC_WAVES * G * TB];   // a wave's probabilities, then its output rows
-    __shared__ float wm[DEC_WAVES][G], wl[DEC_WAVES][G];
+    __shared__ __attribute__((aligned(16))) float buf[NW * G * TB];   // a wave's probabilities, then its output rows
+    __shared__ float wm[NW][G], wl[NW][G];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = Hq / Hkv, ngb = (grp + G - 1) / G;
-    const int split = blockIdx.x, hk = blockIdx.y / ngb, h0 = (blockIdx.y % ngb) * G, b = blockIdx.z;
+    const int split = blockIdx.x % splits, hb = blockIdx.x / splits % (Hkv * ngb), b = blockIdx.x / splits / (Hkv * ngb);
+    const int hk = hb / ngb, h0 = (hb % ngb) * G;
     const bf16_t* row = qkv + (size_t)b * ld_qkv;
-    for (int i = threadIdx.x; i < G * HD; i += DEC_WAVES * 64) {
+    for (int i = threadIdx.x; i < G * HD; i += NW * 64) {
         const int g = i / HD, h = min(h0 + g, grp - 1);       // heads past the group repeat its last one and are not stored
         qs[g][i % HD] = bf2f(row[(size_t)(hk * grp + h) * HD + i % HD]) * scale_log2e;
     }
@@ -107,11 +111,12 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
 
     bf16_t* K = kt + (size_t)(b * Hkv + hk) * HD * max_len;
     bf16_t* V = v + (size_t)(b * Hkv + hk) * max_len * HD;
-    const int per_wave = (per_split / DEC_WAVES + 7) & ~7;
-    const int s1 = min(n, (split + 1) * per_split);
-    const int w0 = split * per_split + w * per_wave, w1 = min(s1, w0 + per_wave);
     const int qw = lane >> 4, l16 = lane & 15;
     const int vrow = lane / LPR, dp = 8 * (lane % LPR);
+    const int per_wave = (per_split / NW + 7) & ~7;
+    const int s1 = min(n, (split + 1) * per_split);
+    const bool dealt = per_split >= NW * TB;
+    const int w0 = split * per_split + w * (dealt ? TB : per_wave), wend = dealt ? s1 : min(s1, w0 + per_wave);
     float m[G], l[G], oa[G][8];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -120,7 +125,8 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
         for (int e = 0; e < 8; ++e) oa[g][e] = 0.f;
     }
     float* ps = buf + w * G * TB;          // [position][G]
-    for (int t0 = w0; t0 < w1; t0 += TB) {
+    for (int t0 = w0; t0 < wend; t0 += dealt ? NW * TB : TB) {
+        const int w1 = min(wend, t0 + TB);
         // scores.  max_len is a multiple of 8, so a lane's 8 positions lie inside the cache row.
         const int t = t0 + l16 * 8;
         float a[G][8];
@@ -129,12 +135,13 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
 #pragma unroll
             for (int e = 0; e < 8; ++e) a[g][e] = 0.f;
         if (t < w1) {
+            const unsigned kofs = qw * DQ * max_len + t;
 #pragma unroll
             for (int d0 = 0; d0 < DQ; d0 += KBATCH) {
                 u32x4_t kk[KBATCH];
 #pragma unroll
                 for (int d = 0; d < KBATCH; ++d)
-                    kk[d] = *reinterpret_cast<const u32x4_t*>(K + (size_t)(qw * DQ + d0 + d) * max_len + t);
+                    kk[d] = *reinterpret_cast<const u32x4_t*>(K + (size_t)(d0 + d) * max_len + kofs);
                 __builtin_amdgcn_sched_barrier(0);      // all loads first: paired with their uses each would be waited for
 #pragma unroll
                 for (int d = 0; d < KBATCH; ++d)
@@ -151,11 +158,11 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
             }
         }
         // this step's first value rows are fetched under the softmax
-        const int rows = min(TB, w1 - t0);
+        const int rows = w1 - t0;
         u32x4_t vv[VBATCH];
 #pragma unroll
         for (int j = 0; j < VBATCH; ++j)
-            vv[j] = *reinterpret_cast<const u32x4_t*>(V + (size_t)min(t0 + j * RPI + vrow, w1 - 1) * HD + dp);
+            vv[j] = *reinterpret_cast<const u32x4_t*>(V + (unsigned)(min(t0 + j * RPI + vrow, w1 - 1) * HD + dp));
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             float mx = -INFINITY;
@@ -180,7 +187,7 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
                 a[g][e] = __builtin_amdgcn_exp2f(a[g][e] - ref);
                 sum += a[g][e];
             }
-            l[g] = l[g] * alpha + sum;                   // of this lane's positions
+            l[g] = fmaf(l[g], alpha, sum);               // of this lane's positions
 #pragma unroll
             for (int e = 0; e < 8; ++e) oa[g][e] *= alpha;
             if (qw == (g & 3))
@@ -193,7 +200,7 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
             if (r0) {
 #pragma unroll
                 for (int j = 0; j < VBATCH; ++j)
-                    vv[j] = *reinterpret_cast<const u32x4_t*>(V + (size_t)min(t0 + r0 + j * RPI + vrow, w1 - 1) * HD + dp);
+                    vv[j] = *reinterpret_cast<const u32x4_t*>(V + (unsigned)(min(t0 + r0 + j * RPI + vrow, w1 - 1) * HD + dp));
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (r0 + VBATCH * RPI > rows) {
@@ -218,7 +225,7 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
         }
         __builtin_amdgcn_wave_barrier();
     }
-    if (fresh && split == (int)gridDim.x - 1 && w == DEC_WAVES - 1) {
+    if (fresh && split == splits - 1 && w == NW - 1) {
         // the new position: scored and added like a run of one, and stored (by the first head block)
         const bf16_t* kn = row + (size_t)(Hq + hk) * HD;
         const bf16_t* vn = kn + (size_t)Hkv * HD;
@@ -238,7 +245,7 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
             const float mx = fmaxf(m[g], s), ref = finite_ref(mx);
             const float alpha = __builtin_amdgcn_exp2f(m[g] - ref), p = __builtin_amdgcn_exp2f(s - ref);
             m[g] = mx;
-            l[g] = l[g] * alpha + (l16 == 0 ? p : 0.f);
+            l[g] = fmaf(l[g], alpha, l16 == 0 ? p : 0.f);
             const float pr = vrow == 0 ? p : 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -273,25 +280,25 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
 #pragma unroll
         for (int g = 0; g < G; ++g) { wm[w][g] = m[g]; wl[w][g] = l[g]; }
     __syncthreads();
-    for (int i = threadIdx.x; i < G * HD; i += DEC_WAVES * 64) {
+    for (int i = threadIdx.x; i < G * HD; i += NW * 64) {
         const int g = i / HD, d = i % HD;
         if (h0 + g >= grp) continue;
         float M = wm[0][g];
 #pragma unroll
-        for (int k = 1; k < DEC_WAVES; ++k) M = fmaxf(M, wm[k][g]);
+        for (int k = 1; k < NW; ++k) M = fmaxf(M, wm[k][g]);
         const float ref = finite_ref(M);
         float L = 0.f, acc = 0.f;
 #pragma unroll
-        for (int k = 0; k < DEC_WAVES; ++k) {
+        for (int k = 0; k < NW; ++k) {
             const float f = __builtin_amdgcn_exp2f(wm[k][g] - ref);      // 0 for a wave without positions
             L = fmaf(f, wl[k][g], L);
             acc = fmaf(f, buf[(k * G + g) * HD + d], acc);
         }
         const int hq = hk * grp + h0 + g;
-        if (gridDim.x == 1) {
+        if (splits == 1) {
             o[(size_t)b * ld_o + hq * HD + d] = f2bf(acc / L);
         } else {
-            float* pr = part + ((size_t)(b * Hq + hq) * gridDim.x + split) * (HD + 2);
+            float* pr = part + ((size_t)(b * Hq + hq) * splits + split) * (HD + 2);
             pr[d] = acc;
             if (d == 0) { pr[HD] = M; pr[HD + 1] = L; }
         }
@@ -303,8 +310,8 @@ __global__ __launch_bounds__(DEC_WAVES * 64) void decode_attn_kernel(
 template <int HD>
 __global__ __launch_bounds__(HD) void combine_kernel(const float* __restrict__ part, int splits, bf16_t* __restrict__ o,
                                                      int ld_o, int Hq) {
-    const int hq = blockIdx.x, b = blockIdx.y, d = threadIdx.x, lane = threadIdx.x & 63;
-    const float* p = part + (size_t)(b * Hq + hq) * splits * (HD + 2);
+    const int hq = blockIdx.x % Hq, b = blockIdx.x / Hq, d = threadIdx.x, lane = threadIdx.x & 63;
+    const float* p = part + (size_t)blockIdx.x * splits * (HD + 2);
     const bool on = lane < splits;
     const float2 ml = on ? *reinterpret_cast<const float2*>(p + lane * (HD + 2) + HD) : make_float2(-INFINITY, 0.f);
     float v[8];
@@ -324,35 +331,61 @@ __global__ __launch_bounds__(HD) void combine_kernel(const float* __restrict__ p
     o[(size_t)b * ld_o + hq * HD + d] = f2bf(acc / L);
 }
 
-template <int HD, int G>
-hipError_t launch_decode_g(hipStream_t st, const bf16_t* qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* o, int ld_o,
-                           float* part, int B, int n, int fresh, int max_len, int Hq, int Hkv) {
-    const int ngb = (Hq / Hkv + G - 1) / G;
-    // splits: enough work-groups for the chip, at least 512 positions each (a split saves less than the
-    // second launch costs below that), and no more rows of
-    // partial results than decode_scratch_floats counts
-    int splits = part ? std::min(std::max(kDecodeSplitGroups / (B * Hkv), 1), n / 512) : 1;
-    if (splits < 1) splits = 1;
-    int per = (n + splits - 1) / splits;
-    per = std::max((per + 63) / 64 * 64, 64);
-    splits = std::max((n + per - 1) / per, 1);           // none is empty
+struct DecodeCall {
+    const bf16_t* qkv; int ld_qkv;
+    bf16_t *kt, *v, *o; int ld_o;
+    float* part;
+    int B, n, fresh, max_len, Hq, Hkv;
+};
+
+template <int HD, int G, int NW>
+hipError_t launch_one(hipStream_t st, const DecodeCall& c, int splits, int per) {
     const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
-    decode_attn_kernel<HD, G><<<dim3(splits, Hkv * ngb, B), DEC_WAVES * 64, 0, st>>>(qkv, ld_qkv, kt, v, o, ld_o, part, n, fresh, per,
-                                                                                     max_len, Hq, Hkv, sl2);
+    const long blocks = (long)c.B * c.Hkv * ((c.Hq / c.Hkv + G - 1) / G) * splits;
+    if (blocks * NW * 64 > 0xffffffffL) return hipErrorInvalidValue;     // work-items of a launch
+    decode_attn_kernel<HD, G, NW><<<(unsigned)blocks, NW * 64, 0, st>>>(c.qkv, c.ld_qkv, c.kt, c.v, c.o, c.ld_o, c.part, c.n, c.fresh,
+                                                                        splits, per, c.max_len, c.Hq, c.Hkv, sl2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
-    combine_kernel<HD><<<dim3(Hq, B), HD, 0, st>>>(part, splits, o, ld_o, Hq);
+    combine_kernel<HD><<<c.B * c.Hq, HD, 0, st>>>(c.part, splits, c.o, c.ld_o, c.Hq);
     return hipGetLastError();
 }
 
+// Splits, query heads per work-group and waves, from the shapes alone.
+//   splits: enough work-groups for the chip, at least 512 positions each (a split saves less than the second
+//     launch costs below that), and no more rows of partial results than decode_scratch_floats counts.
+//   G: the fewest heads whose work-groups still fit one round of the chip (256, or 1024 of two waves); a group's
+//     cache is then read again through the L2, which costs less than idle CUs.  Always sharing it cost, us:
+//     1 x 64/8 heads of 128 over 500 positions 34.3 against 9.1, 4 x 64/8 over 800 38.6 against 19.5; never sharing
+//     it 32 x 32/8 over 500 39.5 against 21.  More than four heads per work-group spilled registers and was slower
+//     than two blocks of four (8 x 64/8 over 4096 positions 91 against 43).
+//   NW: a wave with less than a step of 128 positions idles in its loads, and every wave has its part in the
+//     merge: 64 x 32 heads over 16 positions 42.6 us with eight waves, 15.8 with two.  Several rounds of work-groups
+//     of a split launch overlap better in small ones (8 x 64/8 over 4096, G = 4: eight waves 64, two 43).
+// Against 258 shapes (1..64 sequences, groups of 1 to 8, 20..16000 positions) the choice is 3.6 % off the best
+// of all combinations on average.
+struct DecodePlan { int splits, per, G, NW; };
+DecodePlan plan_decode(const DecodeCall& c) {
+    const int heads = c.B * c.Hkv, grp = c.Hq / c.Hkv;
+    DecodePlan p;
+    p.splits = c.part ? std::max(std::min(std::max(kDecodeSplitGroups / heads, 1), c.n / 512), 1) : 1;
+    p.per = std::max(((c.n + p.splits - 1) / p.splits + 63) / 64 * 64, 64);
+    p.splits = std::max((c.n + p.per - 1) / p.per, 1);           // none is empty
+    p.NW = p.per <= 128 ? 2 : p.per <= 400 ? 4 : 8;
+    auto groups = [&](int G) { return (long)heads * ((grp + G - 1) / G) * p.splits; };
+    p.G = 1;
+    while (p.G < 4 && p.G < grp && groups(p.G) > (p.NW == 2 ? 1024 : 256)) p.G *= 2;
+    if (p.splits > 1 && groups(p.G) > 256) p.NW = p.G == 4 && groups(4) > 512 ? 2 : 4;
+    return p;
+}
+
 template <int HD>
-hipError_t launch_decode(hipStream_t st, const bf16_t* qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* o, int ld_o,
-                         float* part, int B, int n, int fresh, int max_len, int Hq, int Hkv) {
-    const int grp = Hq / Hkv;
-    if (grp == 1) return launch_decode_g<HD, 1>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
-    if (grp == 2) return launch_decode_g<HD, 2>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
-    if (grp <= 4) return launch_decode_g<HD, 4>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
-    return launch_decode_g<HD, 8>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+hipError_t launch_decode(hipStream_t st, const DecodeCall& c) {
+    const DecodePlan p = plan_decode(c);
+#define SP_DECODE(g, w) if (p.G == g && p.NW == w) return launch_one<HD, g, w>(st, c, p.splits, p.per);
+    SP_DECODE(1, 2) SP_DECODE(1, 4) SP_DECODE(1, 8) SP_DECODE(2, 2) SP_DECODE(2, 4) SP_DECODE(2, 8) SP_DECODE(4, 2) SP_DECODE(4, 4) SP_DECODE(4, 8)
+#undef SP_DECODE
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -369,13 +402,13 @@ hipError_t spk_launch_kv_append(hipStream_t st, const bf16_t* qkv, int ld_qkv, b
     return hipGetLastError();
 }
 
-static hipError_t decode_step(hipStream_t st, const bf16_t* qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* o, int ld_o,
-                              float* part, int B, int n, int fresh, int max_len, int Hq, int Hkv, int hd) {
-    if (B < 1 || n + fresh < 1 || n + fresh > max_len || (max_len & 7) || max_len > kDecodeMaxLen || Hkv < 1 || Hq % Hkv ||
-        ld_qkv % 8 || B > 65535 || ((uintptr_t)kt & 15) || ((uintptr_t)v & 15) || ((uintptr_t)qkv & 15))
+static hipError_t decode_step(hipStream_t st, const DecodeCall& c, int hd) {
+    const int n = c.n + c.fresh;
+    if (c.B < 1 || n < 1 || n > c.max_len || (c.max_len & 7) || c.max_len > kDecodeMaxLen || c.Hkv < 1 || c.Hq % c.Hkv ||
+        c.ld_qkv % 8 || ((uintptr_t)c.kt & 15) || ((uintptr_t)c.v & 15) || ((uintptr_t)c.qkv & 15))
         return hipErrorInvalidValue;
-    if (hd == 128) return launch_decode<128>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
-    if (hd == 64) return launch_decode<64>(st, qkv, ld_qkv, kt, v, o, ld_o, part, B, n, fresh, max_len, Hq, Hkv);
+    if (hd == 128) return launch_decode<128>(st, c);
+    if (hd == 64) return launch_decode<64>(st, c);
     return hipErrorInvalidValue;
 }
 
@@ -383,9 +416,9 @@ hipError_t spk_launch_decode_attention(hipStream_t st, const bf16_t* qkv, int ld
                                        const bf16_t* v, bf16_t* o, int ld_o, int B, int n, int max_len, int Hq,
                                        int Hkv, int hd) {
     // nothing is stored without a fresh position
-    return decode_step(st, qkv, ld_qkv, const_cast<bf16_t*>(kt), const_cast<bf16_t*>(v), o, ld_o, nullptr, B, n, 0, max_len, Hq, Hkv, hd);
+    return decode_step(st, DecodeCall{qkv, ld_qkv, const_cast<bf16_t*>(kt), const_cast<bf16_t*>(v), o, ld_o, nullptr, B, n, 0, max_len, Hq, Hkv}, hd);
 }
 
 hipError_t spk_launch_decode_step(hipStream_t st, const bf16_t* qkv, bf16_t* o, const AttnShape& a) {
-    return decode_step(st, qkv, a.ld_qkv, a.kt, a.v, o, a.Hq * a.hd, a.part, a.B, a.pos, 1, a.max_len, a.Hq, a.Hkv, a.hd);
+    return decode_step(st, DecodeCall{qkv, a.ld_qkv, a.kt, a.v, o, a.Hq * a.hd, a.part, a.B, a.pos, 1, a.max_len, a.Hq, a.Hkv}, a.hd);
 }

@@ -103,6 +103,99 @@ def test_decode_attention_infinite_keys_and_values(B, n, max_len, Hq, Hkv, hd, l
     assert max_rel(got[..., keep], ref[..., keep]) <= 8e-3          # one bf16 rounding of the output
 
 
+def single_query_ref(q, k, v):
+    """Float64 attention of one query per sequence: q [B, Hq, hd], k and v [B, Hkv, n, hd]."""
+    B, Hq, hd = q.shape
+    Hkv = k.shape[1]
+    s = np.matmul(q.reshape(B, Hkv, Hq // Hkv, hd), k.transpose(0, 1, 3, 2)) / np.sqrt(hd)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    return np.matmul(p / p.sum(-1, keepdims=True), v).reshape(B, Hq, hd)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,hd", [
+    (B, Hq, Hkv, n, hd)
+    for B, Hq, Hkv in ((2, 5, 1), (20, 16, 8), (70, 16, 8), (34, 16, 4), (131, 16, 4), (33, 24, 8))
+    for n in (1, 127, 129, 384, 385, 1021) for hd in (64, 128)
+    if B * Hkv * n * hd <= 1 << 25          # beyond, the float64 reference takes seconds
+])
+def test_decode_attention_heads_and_waves(B, Hq, Hkv, n, hd):
+    """One, two and four query heads per work-group (groups of five, two, four, three) with two, four and eight
+    waves, around the context lengths where their number changes."""
+    rng = np.random.default_rng(B + n + hd)
+    max_len = (n + 7) // 8 * 8
+    qb, q = rand_bf16(rng, (B, (Hq + 2 * Hkv), hd))
+    kb, k = rand_bf16(rng, (B, Hkv, n, hd))
+    vb, v = rand_bf16(rng, (B, Hkv, n, hd))
+    kc, vc = np.full((B, Hkv, hd, max_len), 0x7FC1, np.uint16), np.full((B, Hkv, max_len, hd), 0x7FC1, np.uint16)
+    kc[..., :n], vc[:, :, :n] = kb.transpose(0, 1, 3, 2), vb
+    qd, kd, vd = dev_u16(qb.reshape(-1)), dev_u16(kc.reshape(-1)), dev_u16(vc.reshape(-1))
+    o = torch.full(((B + 1) * Hq * hd,), 7, dtype=torch.int16, device=DEV)
+    assert sp.spk_decode_attention(stream_ptr(), ptr(qd), ptr(kd), ptr(vd), ptr(o), B, n, max_len, Hq, Hkv, hd) == sp.SP_OK
+    torch.cuda.synchronize()
+    out = host_u16(o).reshape(B + 1, Hq, hd)
+    assert np.all(out[B] == 7)                                      # the row behind o
+    assert max_rel(bf16_vals(out[:B]), single_query_ref(q[:, :Hq], k, v)) <= 8e-3      # one bf16 rounding of the output
+
+
+def attention_only_layer(Hq, Hkv, hd, B):
+    """A decoder layer whose q, k and v are the leading elements of the normed input, whose output projection is the
+    identity and whose MLP is zero: y - x is the attention output itself."""
+    w = synth.Workload("attn_only", "decoder", 1, Hq * hd, Hq, Hkv, hd, 128, True, B, 1)
+    desc = sp.make_desc(w)
+    blob = torch.zeros(sp.sp_layer_blob_bytes(C.byref(desc)), dtype=torch.uint8, pin_memory=True)
+    v = sp.blob_views(desc, blob.numpy())
+    d, one = Hq * hd, synth.f32_to_bf16_bits(np.ones(1, np.float32))[0]
+    v["g1"][:] = one
+    v["g2"][:] = one
+    wqkv = v["wqkv"].reshape(-1, d)
+    for r0, n in ((0, d), (d, Hkv * hd), (d + Hkv * hd, Hkv * hd)):
+        wqkv[np.arange(r0, r0 + n), np.arange(n)] = one
+    v["wo"].reshape(d, d)[np.arange(d), np.arange(d)] = one
+    return w, desc, blob
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,hd,pos,max_len", [
+    (1, 1, 1, 64, 4608, 4616),       # nine splits: a second batch of one row in the combination
+    (1, 4, 1, 128, 8191, 8192),      # fifteen, one group of four
+    (1, 2, 1, 64, 32767, 32768),     # sixty-three, the longest cache
+    (16, 16, 8, 64, 4100, 4104),     # four: the number of work-groups sets the limit
+    (2, 64, 8, 64, 8300, 8304),      # groups of eight as two blocks of four, four waves
+    (8, 64, 8, 64, 4100, 4104),      # the same, two waves
+    (1, 32, 32, 64, 8300, 8304),     # one head per work-group, four waves
+    (2, 32, 16, 64, 8300, 8304),     # two heads, four waves
+    (3, 6, 2, 128, 1024, 1032),      # two splits, groups of three
+    (2, 8, 8, 64, 1023, 1024),       # one split
+])
+def test_decode_step_over_a_long_cache(B, Hq, Hkv, hd, pos, max_len):
+    """The attention of a decode step against float64, over a cache of random keys and values, and the cache
+    afterwards: position pos holds the new key and value, every other bit is what it was."""
+    rng = np.random.default_rng(pos + Hq)
+    w, desc, blob = attention_only_layer(Hq, Hkv, hd, B)
+    d = w.d_model
+    x = (rng.standard_normal((B, d)) * 0.7).astype(np.float32)
+    a = bf16_vals(synth.f32_to_bf16_bits((x / np.sqrt(np.mean(x.astype(np.float64) ** 2, -1, keepdims=True) + w.norm_eps)).astype(np.float32)))
+    kb, k = rand_bf16(rng, (B, Hkv, max_len, hd))
+    vb, v = rand_bf16(rng, (B, Hkv, max_len, hd))
+    cache_bits = np.concatenate([np.ascontiguousarray(kb.transpose(0, 1, 3, 2)).reshape(-1), vb.reshape(-1)])
+    cache = dev_u16(cache_bits)
+    assert cache.numel() * 2 == sp.sp_kv_cache_bytes(C.byref(desc), B, max_len)
+    eng = sp.Engine(desc, [blob], 1, 1)
+    xd = dev_f32(x)
+    yd = torch.empty_like(xd)
+    eng.decode(xd, yd, cache, B, pos, max_len)
+    eng.sync()
+    got = yd.cpu().numpy().astype(np.float64) - x
+    eng.destroy()
+    k[:, :, pos], v[:, :, pos] = a[:, :Hkv * hd].reshape(B, Hkv, hd), a[:, :Hkv * hd].reshape(B, Hkv, hd)
+    ref = single_query_ref(a.reshape(B, Hq, hd), k[:, :, :pos + 1], v[:, :, :pos + 1]).reshape(B, d)
+    assert max_rel(got, ref) <= 8e-3          # one bf16 rounding of the output
+    after = host_u16(cache)
+    kc, vc = after[:after.size // 2].reshape(B, Hkv, hd, max_len), after[after.size // 2:].reshape(B, Hkv, max_len, hd)
+    assert np.array_equal(bf16_vals(kc[..., pos]), k[:, :, pos]) and np.array_equal(bf16_vals(vc[:, :, pos]), v[:, :, pos])
+    kc[..., pos], vc[:, :, pos] = kb[:, :, pos], vb[:, :, pos]
+    assert np.array_equal(after, cache_bits)
+
+
 def test_decode_kernel_argument_errors():
     t = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     s = stream_ptr()
