@@ -179,7 +179,8 @@ typedef struct {
     int32_t fully_resident;     /* n_slots == number of units */
     uint64_t slot_bytes;        /* bytes of the largest unit (layer blob, or its largest part) rounded up to 4 KiB */
     uint64_t workspace_bytes;
-    uint64_t arena_bytes_used;  /* workspace + pinned_bytes + (n_slots - n_pinned) * slot_bytes (+ gradient slots) */
+    uint64_t arena_bytes_used;  /* workspace + pinned_bytes + (n_slots - n_pinned) * slot_bytes (gradient slots are
+                                   part of the workspace), + sp_decode_scratch_bytes where the budget leaves them */
     int32_t n_pinned;           /* of the n_slots, those holding units 0..n_pinned-1 for good */
     int32_t units_per_layer;    /* 1 or 3 */
     uint64_t pinned_bytes;      /* what the pinned units occupy: each its own size rounded up to 4 KiB */
@@ -253,6 +254,10 @@ size_t sp_layer_grad_bytes(const sp_stack_desc* desc);
  * (saved layer inputs, backward scratch, gradient slots); 2 = training with
  * SP_FLAG_KEEP_ACTIVATIONS (one activation set per layer). */
 size_t sp_workspace_bytes(const sp_stack_desc* desc, int training);
+/* Bytes beyond the workspace and the slots that let sp_decode split the positions of a long cache over more
+ * work-groups (0 for stacks that do not decode or whose workspace has the room).  A plan takes them from what the
+ * budget leaves after the slots, never instead of one; without them sp_decode computes the same bits more slowly. */
+size_t sp_decode_scratch_bytes(const sp_stack_desc* desc);
 /* The slot-count policy above as a pure function (layer units). */
 int sp_make_plan(const sp_stack_desc* desc, int k, int p, int pinned_layers, uint64_t budget_bytes,
                  int training, sp_plan* out);

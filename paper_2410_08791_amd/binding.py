@@ -101,6 +101,7 @@ _sig = {
     "sp_layer_blob_bytes": (C.c_size_t, [_P(sp_stack_desc)]),
     "sp_layer_grad_bytes": (C.c_size_t, [_P(sp_stack_desc)]),
     "sp_workspace_bytes": (C.c_size_t, [_P(sp_stack_desc), C.c_int]),
+    "sp_decode_scratch_bytes": (C.c_size_t, [_P(sp_stack_desc)]),
     "sp_make_plan": (C.c_int, [_P(sp_stack_desc), C.c_int, C.c_int, C.c_int, C.c_uint64, C.c_int, _P(sp_plan)]),
     "sp_make_plan_units": (C.c_int, [_P(sp_stack_desc), C.c_int, C.c_int, C.c_int, C.c_int, C.c_uint64, C.c_int,
                                      _P(sp_plan)]),
@@ -290,7 +291,7 @@ class Engine:
         slot = (sp_layer_blob_bytes(C.byref(desc)) + 4095) // 4096 * 4096
         if budget_bytes is None:
             nl = budget_layers if budget_layers else min(k + p + max(pinned, 0), desc.n_layers)
-            budget_bytes = ws + nl * slot
+            budget_bytes = ws + nl * slot + (0 if training else sp_decode_scratch_bytes(C.byref(desc)))
         self.budget_bytes = int(budget_bytes)
         self.device = torch.device(device)
         with torch.cuda.device(self.device):

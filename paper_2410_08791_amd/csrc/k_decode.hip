@@ -79,31 +79,63 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict
 // Row addresses are a uniform base and one 32-bit lane offset: 64-bit addresses per row took half the
 // registers (196 against 132 at G = 1).  The waves' results meet in LDS.  With
 // more than one split the unnormalised rows go to `part` (fp32: HD values, reference maximum in base 2,
-// denominator) and combine_kernel adds them in split order.
+// denominator) and combine_kernel adds them in split order.  Without that scratch (KS > 1) one work-group of
+// KS x NW waves takes all splits of a query head, KS at a time, leaves their rows in LDS and adds them in the same
+// order: the same bits from fewer work-groups.
 // HBM-bound: 4 n Hkv hd bytes per sequence.
 //
 // A score of -inf has weight 0 whichever positions a wave holds: where every score of a wave or split so far
 // is -inf, 0 stands in for the maximum in the differences taken with it (-inf - -inf would make the row NaN).
 __device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
 
-template <int HD, int G, int NW>
-__global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
+// Element d of the result from the rows of its splits, by whole waves.  At most 64 splits (kDecodeMaxLen / 512):
+// lane s weighs split s, then every thread adds its element of the rows, eight loads in flight (one dependent
+// chain of loads per split took 10.5 us for 16 splits).
+template <int HD>
+__device__ __forceinline__ float combine_rows(const float* p, int splits, int d) {
+    const int lane = threadIdx.x & 63;
+    const bool on = lane < splits;
+    const float2 ml = on ? *reinterpret_cast<const float2*>(p + lane * (HD + 2) + HD) : make_float2(-INFINITY, 0.f);
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = j < splits ? p[j * (HD + 2) + d] : 0.f;
+    const float M = finite_ref(wave_max(ml.x));
+    const float f = on ? __builtin_amdgcn_exp2f(ml.x - M) : 0.f;
+    const float L = wave_sum(f * ml.y);
+    float acc = 0.f;
+    for (int s0 = 0; s0 < splits; s0 += 8) {
+        if (s0)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = s0 + j < splits ? p[(s0 + j) * (HD + 2) + d] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc = fmaf(__shfl(f, s0 + j, 64), v[j], acc);     // s0 + j <= 63
+    }
+    return acc / L;
+}
+
+template <int HD, int G, int NW, int KS>
+__global__ __launch_bounds__(NW * KS * 64) void decode_attn_kernel(
     const bf16_t* __restrict__ qkv, int ld_qkv, bf16_t* kt, bf16_t* v, bf16_t* __restrict__ o, int ld_o,
     float* __restrict__ part, int n, int fresh, int splits, int per_split, int max_len, int Hq, int Hkv, float scale_log2e) {
     constexpr int DQ = HD / 4;             // head-dimension elements per quarter-wave in the score pass
     constexpr int LPR = HD / 8;            // lanes per V row
     constexpr int RPI = 64 / LPR;          // V rows per load instruction
     constexpr int TB = 128;                // positions per wave and step
-    constexpr int KBATCH = 16, VBATCH = 8;
+    constexpr int KBATCH = KS > 1 ? 8 : 16, VBATCH = 8;         // KS > 1: sixteen waves, 128 registers each
+    constexpr bool SEQ = KS > 1;
+    constexpr int MAX_SPLITS = kDecodeMaxLen / 512;
     __shared__ float qs[G][HD];
-    __shared__ __attribute__((aligned(16))) float buf[NW * G * TB];   // a wave's probabilities, then its output rows
-    __shared__ float wm[NW][G], wl[NW][G];
+    __shared__ __attribute__((aligned(16))) float buf[NW * KS * G * TB];   // a wave's probabilities, then its output rows
+    __shared__ float wm[NW * KS][G], wl[NW * KS][G];
+    __shared__ __attribute__((aligned(16))) float rows_lds[SEQ ? G * MAX_SPLITS * (HD + 2) : 1];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = Hq / Hkv, ngb = (grp + G - 1) / G;
-    const int split = blockIdx.x % splits, hb = blockIdx.x / splits % (Hkv * ngb), b = blockIdx.x / splits / (Hkv * ngb);
+    const int id = SEQ ? blockIdx.x : blockIdx.x / splits, hb = id % (Hkv * ngb), b = id / (Hkv * ngb);
+    const int wi = w % NW, sub = w / NW;   // wave of its split, split of the KS
+    int split = SEQ ? sub : blockIdx.x % splits;
     const int hk = hb / ngb, h0 = (hb % ngb) * G;
     const bf16_t* row = qkv + (size_t)b * ld_qkv;
-    for (int i = threadIdx.x; i < G * HD; i += NW * 64) {
+    for (int i = threadIdx.x; i < G * HD; i += NW * KS * 64) {
         const int g = i / HD, h = min(h0 + g, grp - 1);       // heads past the group repeat its last one and are not stored
         qs[g][i % HD] = bf2f(row[(size_t)(hk * grp + h) * HD + i % HD]) * scale_log2e;
     }
@@ -114,9 +146,11 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
     const int qw = lane >> 4, l16 = lane & 15;
     const int vrow = lane / LPR, dp = 8 * (lane % LPR);
     const int per_wave = (per_split / NW + 7) & ~7;
-    const int s1 = min(n, (split + 1) * per_split);
     const bool dealt = per_split >= NW * TB;
-    const int w0 = split * per_split + w * (dealt ? TB : per_wave), wend = dealt ? s1 : min(s1, w0 + per_wave);
+    float* ps = buf + w * G * TB;          // [position][G]
+    for (;;) {                             // SEQ: KS splits at a time, past the last one a wave has no positions
+    const int s1 = min(n, (split + 1) * per_split);
+    const int w0 = split * per_split + wi * (dealt ? TB : per_wave), wend = dealt ? s1 : min(s1, w0 + per_wave);
     float m[G], l[G], oa[G][8];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -124,7 +158,6 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) oa[g][e] = 0.f;
     }
-    float* ps = buf + w * G * TB;          // [position][G]
     for (int t0 = w0; t0 < wend; t0 += dealt ? NW * TB : TB) {
         const int w1 = min(wend, t0 + TB);
         // scores.  max_len is a multiple of 8, so a lane's 8 positions lie inside the cache row.
@@ -225,7 +258,7 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
         }
         __builtin_amdgcn_wave_barrier();
     }
-    if (fresh && split == splits - 1 && w == NW - 1) {
+    if (fresh && split == splits - 1 && wi == NW - 1) {
         // the new position: scored and added like a run of one, and stored (by the first head block)
         const bf16_t* kn = row + (size_t)(Hq + hk) * HD;
         const bf16_t* vn = kn + (size_t)Hkv * HD;
@@ -280,55 +313,48 @@ __global__ __launch_bounds__(NW * 64) void decode_attn_kernel(
 #pragma unroll
         for (int g = 0; g < G; ++g) { wm[w][g] = m[g]; wl[w][g] = l[g]; }
     __syncthreads();
-    for (int i = threadIdx.x; i < G * HD; i += NW * 64) {
-        const int g = i / HD, d = i % HD;
-        if (h0 + g >= grp) continue;
-        float M = wm[0][g];
+    for (int i = threadIdx.x - sub * NW * 64; i < G * HD; i += NW * 64) {
+        const int g = i / HD, d = i % HD, k0 = sub * NW;
+        if (h0 + g >= grp || split >= splits) continue;
+        float M = wm[k0][g];
 #pragma unroll
-        for (int k = 1; k < NW; ++k) M = fmaxf(M, wm[k][g]);
+        for (int k = 1; k < NW; ++k) M = fmaxf(M, wm[k0 + k][g]);
         const float ref = finite_ref(M);
         float L = 0.f, acc = 0.f;
 #pragma unroll
         for (int k = 0; k < NW; ++k) {
-            const float f = __builtin_amdgcn_exp2f(wm[k][g] - ref);      // 0 for a wave without positions
-            L = fmaf(f, wl[k][g], L);
-            acc = fmaf(f, buf[(k * G + g) * HD + d], acc);
+            const float f = __builtin_amdgcn_exp2f(wm[k0 + k][g] - ref);      // 0 for a wave without positions
+            L = fmaf(f, wl[k0 + k][g], L);
+            acc = fmaf(f, buf[((k0 + k) * G + g) * HD + d], acc);
         }
         const int hq = hk * grp + h0 + g;
-        if (splits == 1) {
+        if (!SEQ && splits == 1) {
             o[(size_t)b * ld_o + hq * HD + d] = f2bf(acc / L);
         } else {
-            float* pr = part + ((size_t)(b * Hq + hq) * splits + split) * (HD + 2);
+            float* pr = SEQ ? rows_lds + (g * splits + split) * (HD + 2) : part + ((size_t)(b * Hq + hq) * splits + split) * (HD + 2);
             pr[d] = acc;
             if (d == 0) { pr[HD] = M; pr[HD + 1] = L; }
         }
     }
+    if (!SEQ) break;
+    __syncthreads();                       // the waves' results have been read out of buf
+    split += KS;
+    if (split - sub >= splits) break;
+    }
+    if (SEQ) {
+        for (int i = threadIdx.x; i < G * HD; i += NW * KS * 64) {     // whole waves per head
+            const int g = i / HD, d = i % HD;
+            if (h0 + g < grp)
+                o[(size_t)b * ld_o + (hk * grp + h0 + g) * HD + d] = f2bf(combine_rows<HD>(rows_lds + g * splits * (HD + 2), splits, d));
+        }
+    }
 }
 
-// At most 64 splits (kDecodeMaxLen / 512): lane s weighs split s, then every thread adds its element of the rows,
-// eight loads in flight (one dependent chain of loads per split took 10.5 us for 16 splits).
 template <int HD>
 __global__ __launch_bounds__(HD) void combine_kernel(const float* __restrict__ part, int splits, bf16_t* __restrict__ o,
                                                      int ld_o, int Hq) {
-    const int hq = blockIdx.x % Hq, b = blockIdx.x / Hq, d = threadIdx.x, lane = threadIdx.x & 63;
-    const float* p = part + (size_t)blockIdx.x * splits * (HD + 2);
-    const bool on = lane < splits;
-    const float2 ml = on ? *reinterpret_cast<const float2*>(p + lane * (HD + 2) + HD) : make_float2(-INFINITY, 0.f);
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = j < splits ? p[j * (HD + 2) + d] : 0.f;
-    const float M = finite_ref(wave_max(ml.x));
-    const float f = on ? __builtin_amdgcn_exp2f(ml.x - M) : 0.f;
-    const float L = wave_sum(f * ml.y);
-    float acc = 0.f;
-    for (int s0 = 0; s0 < splits; s0 += 8) {
-        if (s0)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = s0 + j < splits ? p[(s0 + j) * (HD + 2) + d] : 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc = fmaf(__shfl(f, s0 + j, 64), v[j], acc);     // s0 + j <= 63
-    }
-    o[(size_t)b * ld_o + hq * HD + d] = f2bf(acc / L);
+    const int hq = blockIdx.x % Hq, b = blockIdx.x / Hq;
+    o[(size_t)b * ld_o + hq * HD + threadIdx.x] = f2bf(combine_rows<HD>(part + (size_t)blockIdx.x * splits * (HD + 2), splits, threadIdx.x));
 }
 
 struct DecodeCall {
@@ -336,22 +362,24 @@ struct DecodeCall {
     bf16_t *kt, *v, *o; int ld_o;
     float* part;
     int B, n, fresh, max_len, Hq, Hkv;
+    bool one_split;
 };
 
-template <int HD, int G, int NW>
+template <int HD, int G, int NW, int KS>
 hipError_t launch_one(hipStream_t st, const DecodeCall& c, int splits, int per) {
     const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
-    const long blocks = (long)c.B * c.Hkv * ((c.Hq / c.Hkv + G - 1) / G) * splits;
-    if (blocks * NW * 64 > 0xffffffffL) return hipErrorInvalidValue;     // work-items of a launch
-    decode_attn_kernel<HD, G, NW><<<(unsigned)blocks, NW * 64, 0, st>>>(c.qkv, c.ld_qkv, c.kt, c.v, c.o, c.ld_o, c.part, c.n, c.fresh,
-                                                                        splits, per, c.max_len, c.Hq, c.Hkv, sl2);
+    const long blocks = (long)c.B * c.Hkv * ((c.Hq / c.Hkv + G - 1) / G) * (KS > 1 ? 1 : splits);
+    if (blocks * NW * KS * 64 > 0xffffffffL) return hipErrorInvalidValue;     // work-items of a launch
+    decode_attn_kernel<HD, G, NW, KS><<<(unsigned)blocks, NW * KS * 64, 0, st>>>(c.qkv, c.ld_qkv, c.kt, c.v, c.o, c.ld_o, c.part, c.n,
+                                                                                 c.fresh, splits, per, c.max_len, c.Hq, c.Hkv, sl2);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
+    if (e != hipSuccess || KS > 1 || splits == 1) return e;
     combine_kernel<HD><<<c.B * c.Hq, HD, 0, st>>>(c.part, splits, c.o, c.ld_o, c.Hq);
     return hipGetLastError();
 }
 
-// Splits, query heads per work-group and waves, from the shapes alone.
+// Splits, query heads per work-group and waves.  Splits and waves, which the order of the sums depends on, follow
+// from the shapes alone; without a scratch for the splits' rows G is 1.
 //   splits: enough work-groups for the chip, at least 512 positions each (a split saves less than the second
 //     launch costs below that), and no more rows of partial results than decode_scratch_floats counts.
 //   G: the fewest heads whose work-groups still fit one round of the chip (256, or 1024 of two waves); a group's
@@ -368,7 +396,7 @@ struct DecodePlan { int splits, per, G, NW; };
 DecodePlan plan_decode(const DecodeCall& c) {
     const int heads = c.B * c.Hkv, grp = c.Hq / c.Hkv;
     DecodePlan p;
-    p.splits = c.part ? std::max(std::min(std::max(kDecodeSplitGroups / heads, 1), c.n / 512), 1) : 1;
+    p.splits = c.one_split ? 1 : std::max(std::min(std::max(kDecodeSplitGroups / heads, 1), c.n / 512), 1);
     p.per = std::max(((c.n + p.splits - 1) / p.splits + 63) / 64 * 64, 64);
     p.splits = std::max((c.n + p.per - 1) / p.per, 1);           // none is empty
     p.NW = p.per <= 128 ? 2 : p.per <= 400 ? 4 : 8;
@@ -382,7 +410,10 @@ DecodePlan plan_decode(const DecodeCall& c) {
 template <int HD>
 hipError_t launch_decode(hipStream_t st, const DecodeCall& c) {
     const DecodePlan p = plan_decode(c);
-#define SP_DECODE(g, w) if (p.G == g && p.NW == w) return launch_one<HD, g, w>(st, c, p.splits, p.per);
+    if (p.splits > 1 && !c.part)
+        return p.NW == 2 ? launch_one<HD, 1, 2, 8>(st, c, p.splits, p.per) : p.NW == 4 ? launch_one<HD, 1, 4, 4>(st, c, p.splits, p.per)
+                                                                                       : launch_one<HD, 1, 8, 2>(st, c, p.splits, p.per);
+#define SP_DECODE(g, w) if (p.G == g && p.NW == w) return launch_one<HD, g, w, 1>(st, c, p.splits, p.per);
     SP_DECODE(1, 2) SP_DECODE(1, 4) SP_DECODE(1, 8) SP_DECODE(2, 2) SP_DECODE(2, 4) SP_DECODE(2, 8) SP_DECODE(4, 2) SP_DECODE(4, 4) SP_DECODE(4, 8)
 #undef SP_DECODE
     return hipErrorInvalidValue;
@@ -415,10 +446,11 @@ static hipError_t decode_step(hipStream_t st, const DecodeCall& c, int hd) {
 hipError_t spk_launch_decode_attention(hipStream_t st, const bf16_t* qkv, int ld_qkv, const bf16_t* kt,
                                        const bf16_t* v, bf16_t* o, int ld_o, int B, int n, int max_len, int Hq,
                                        int Hkv, int hd) {
-    // nothing is stored without a fresh position
-    return decode_step(st, DecodeCall{qkv, ld_qkv, const_cast<bf16_t*>(kt), const_cast<bf16_t*>(v), o, ld_o, nullptr, B, n, 0, max_len, Hq, Hkv}, hd);
+    // nothing is stored without a fresh position; no scratch, and no other form whose bits it would have to match
+    return decode_step(st, DecodeCall{qkv, ld_qkv, const_cast<bf16_t*>(kt), const_cast<bf16_t*>(v), o, ld_o, nullptr, B, n, 0, max_len, Hq, Hkv,
+                                      true}, hd);
 }
 
 hipError_t spk_launch_decode_step(hipStream_t st, const bf16_t* qkv, bf16_t* o, const AttnShape& a) {
-    return decode_step(st, DecodeCall{qkv, a.ld_qkv, a.kt, a.v, o, a.Hq * a.hd, a.part, a.B, a.pos, 1, a.max_len, a.Hq, a.Hkv}, a.hd);
+    return decode_step(st, DecodeCall{qkv, a.ld_qkv, a.kt, a.v, o, a.Hq * a.hd, a.part, a.B, a.pos, 1, a.max_len, a.Hq, a.Hkv, false}, a.hd);
 }

@@ -27,6 +27,7 @@ struct sp_engine {
     int units = 1, n_units = 0;
     size_t unit_off[3] = {0, 0, 0}, unit_len[3] = {0, 0, 0};
     std::vector<unsigned char*> slot_addr;
+    float* decode_part = nullptr;     // partial results of decode attention; nullptr: the budget leaves no room
     hipStream_t compute = nullptr, h2d = nullptr, d2h = nullptr;
     std::vector<const void*> blobs;   // pinned host weight blobs (never written)
     // Cross-stream fences.  Every copy and every layer compute of a call records

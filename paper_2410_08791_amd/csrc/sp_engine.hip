@@ -260,7 +260,7 @@ int sp_layer_forward(sp_engine* e, const unsigned char* w, float* h, int B, int 
         // single query per sequence to the positions 0..pos and stores position pos itself.
         if (kv && kv->pos >= 0) {
             as.kt = kv->kt; as.v = kv->v; as.max_len = kv->max_len; as.pos = kv->pos;
-            as.part = e->wsp<float>(e->ws.z);
+            as.part = e->decode_part;
         } else if (kv) {
             SP_OP(e, SP_OP_ATTENTION, spk_launch_kv_append(st, qkv, nqkv, kv->kt, kv->v, B, S, 0, d.n_q_heads, d.n_kv_heads,
                                                            d.head_dim, kv->max_len));
@@ -375,6 +375,9 @@ extern "C" int sp_create(sp_handle* out, const sp_stack_desc* desc, const void* 
             e->slot_addr[s] = at;
             at += s < plan.n_pinned ? align_up(e->unit_len[s % units], kSlotAlign) : plan.slot_bytes;
         }
+        const size_t extra = decode_scratch_extra(desc);
+        if (!extra) e->decode_part = e->wsp<float>(e->ws.z);
+        else if (at + extra == e->arena + plan.arena_bytes_used) e->decode_part = reinterpret_cast<float*>(at);
     }
     e->compute = static_cast<hipStream_t>(cfg->compute_stream);
     e->h2d = static_cast<hipStream_t>(cfg->h2d_stream);

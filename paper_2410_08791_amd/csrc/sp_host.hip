@@ -83,11 +83,7 @@ void make_workspace(const sp_stack_desc* d, const Layout& lay, int training, Wor
     // [gate | up] resp. the MLP pre-activation: only the backward needs them in memory (the
     // forward applies SwiGLU / GELU in the producing GEMM's epilogue and stores z alone)
     ws->gu = training ? take(Tp * (d->arch == SP_DECODER_SWIGLU_RMS ? 2 * f : f) * 2) : off;
-    // z is idle while the attention runs: a decode step keeps its partial results there
-    size_t zb = Tp * f * 2;
-    if (!training && d->arch == SP_DECODER_SWIGLU_RMS && d->causal && (d->head_dim == 64 || d->head_dim == 128))
-        zb = std::max(zb, decode_scratch_floats(d->n_q_heads, d->n_kv_heads, d->head_dim) * 4);
-    ws->z = take(zb);
+    ws->z = take(Tp * f * 2);
     if (training) {
         ws->m = take(Tp * dm * 2);
         ws->h1 = take(T * dm * 4);
@@ -115,6 +111,13 @@ void make_workspace(const sp_stack_desc* d, const Layout& lay, int training, Wor
         for (int i = 0; i < kGradSlots; ++i) ws->gslot[i] = take(align_up(lay.grad_bytes, kSlotAlign));
     }
     ws->total = align_up(off, kSlotAlign);
+}
+
+// z is idle while the attention runs: a decode step keeps its partial results there where they fit.
+size_t decode_scratch_extra(const sp_stack_desc* d) {
+    if (d->arch != SP_DECODER_SWIGLU_RMS || !d->causal || (d->head_dim != 64 && d->head_dim != 128)) return 0;
+    const size_t need = decode_scratch_floats(d->n_q_heads, d->n_kv_heads, d->head_dim) * 4;
+    return need <= (size_t)d->max_batch * d->max_seq * d->d_ffn * 2 ? 0 : align_up(need, kSlotAlign);
 }
 
 int unit_range(const sp_stack_desc* d, const Layout& lay, int units, int part, size_t* off, size_t* len) {
@@ -180,6 +183,9 @@ int make_plan(const sp_stack_desc* d, int units, int k, int p, int pinned, uint6
     out->k_eff = (int)std::max<int64_t>(ring - out->p_eff, 1);
     out->fully_resident = n == L;
     out->arena_bytes_used = ws.total + pinned_bytes + (uint64_t)ring * out->slot_bytes;
+    // last of all, and only out of what no slot could use: a decode step does without
+    const uint64_t extra = training ? 0 : decode_scratch_extra(d);
+    if (extra <= budget - out->arena_bytes_used) out->arena_bytes_used += extra;
     return SP_OK;
 }
 
@@ -328,6 +334,10 @@ extern "C" size_t sp_workspace_bytes(const sp_stack_desc* desc, int training) {
     Workspace ws;
     make_workspace(desc, lay, training, &ws);
     return ws.total;
+}
+
+extern "C" size_t sp_decode_scratch_bytes(const sp_stack_desc* desc) {
+    return validate_desc(desc, nullptr) == SP_OK ? decode_scratch_extra(desc) : 0;
 }
 
 extern "C" int sp_make_plan(const sp_stack_desc* desc, int k, int p, int pinned_layers, uint64_t budget_bytes,

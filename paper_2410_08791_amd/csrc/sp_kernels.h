@@ -74,7 +74,8 @@ struct AttnShape {
     int B, S, Hq, Hkv, hd, causal;
     int ld_qkv;      // row stride (elements) of the fused [q | k | v] activation
     // A decode step (kt != nullptr; S == 1): one query per sequence against the cache of one layer, whose
-    // position `pos` is taken from qkv and stored.  part: decode_scratch_floats() floats.
+    // position `pos` is taken from qkv and stored.  part: decode_scratch_floats() floats, or nullptr (the
+    // same bits, by fewer work-groups).
     bf16_t* kt = nullptr;
     bf16_t* v = nullptr;
     float* part = nullptr;

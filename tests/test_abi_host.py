@@ -102,6 +102,34 @@ def test_forward_workspace_holds_no_gate_up_buffer():
     assert pl.arena_bytes_used <= got + 4 * slot
 
 
+def test_decode_scratch_takes_no_slot_and_refuses_no_budget():
+    """A stack sized for decode steps only: its workspace is the activations alone, a budget of that and one slot is
+    accepted, and the room for decode attention's partial results comes out of what the slots leave."""
+    w = synth.WORKLOADS["llama70b"]
+    d = sp.make_desc(w, max_batch=2, max_seq=1, n_layers=8)
+    al = lambda v, a: (v + a - 1) // a * a  # noqa: E731
+    dm, nq, nkv, f = w.d_model, w.n_q_heads * w.head_dim, w.n_kv_heads * w.head_dim, w.d_ffn
+    ws = sp.sp_workspace_bytes(C.byref(d), 0)
+    assert ws == al(sum(al(2 * 2 * cols, 256) for cols in (dm, nq + 2 * nkv, nq, f)), 4096)
+    extra = sp.sp_decode_scratch_bytes(C.byref(d))
+    assert extra == al(w.n_q_heads // w.n_kv_heads * 512 * (w.head_dim + 2) * 4, 4096)
+    slot = al(sp.sp_layer_blob_bytes(C.byref(d)), 4096)
+    for k, p, pin in ((1, 1, 0), (2, 1, 0), (1, 1, sp.SP_PIN_AUTO), (8, 1, 0)):
+        for n in (1, 2, 3, 8):
+            for left, used in ((0, 0), (extra - 1, 0), (extra, extra), (slot - 1, extra)):
+                rc, pl = sp.plan(d, k, p, ws + n * slot + left, pinned=pin)
+                rc0, pl0 = sp.plan(d, k, p, ws + n * slot, pinned=pin)
+                assert rc == rc0 == sp.SP_OK and (pl.n_slots, pl.n_pinned) == (pl0.n_slots, pl0.n_pinned)
+                if pl.n_slots == n:
+                    assert pl.arena_bytes_used == ws + n * slot + used
+                assert pl.arena_bytes_used <= ws + n * slot + left and pl.workspace_bytes == ws
+    assert sp.plan(d, 1, 1, ws + slot - 1)[0] == sp.SP_ERR_BUDGET
+    # none beside the workspace: enough tokens per call, no causal decoder, head_dim 80
+    assert sp.sp_decode_scratch_bytes(C.byref(sp.make_desc(w))) == 0
+    assert sp.sp_decode_scratch_bytes(C.byref(sp.make_desc(synth.WORKLOADS["vith"]))) == 0
+    assert sp.sp_decode_scratch_bytes(None) == 0
+
+
 def test_slot_count_policy():
     w = synth.WORKLOADS["llama7b"]
     d = sp.make_desc(w)

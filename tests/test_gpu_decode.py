@@ -177,19 +177,26 @@ def test_decode_step_over_a_long_cache(B, Hq, Hkv, hd, pos, max_len):
     kb, k = rand_bf16(rng, (B, Hkv, max_len, hd))
     vb, v = rand_bf16(rng, (B, Hkv, max_len, hd))
     cache_bits = np.concatenate([np.ascontiguousarray(kb.transpose(0, 1, 3, 2)).reshape(-1), vb.reshape(-1)])
-    cache = dev_u16(cache_bits)
-    assert cache.numel() * 2 == sp.sp_kv_cache_bytes(C.byref(desc), B, max_len)
-    eng = sp.Engine(desc, [blob], 1, 1)
+    assert cache_bits.size * 2 == sp.sp_kv_cache_bytes(C.byref(desc), B, max_len)
     xd = dev_f32(x)
-    yd = torch.empty_like(xd)
-    eng.decode(xd, yd, cache, B, pos, max_len)
-    eng.sync()
-    got = yd.cpu().numpy().astype(np.float64) - x
-    eng.destroy()
+    out = []
+    slot = (blob.numel() + 4095) // 4096 * 4096
+    for budget in (None, sp.sp_workspace_bytes(C.byref(desc), 0) + slot):
+        cache = dev_u16(cache_bits)
+        eng = sp.Engine(desc, [blob], 1, 1, budget_bytes=budget)
+        yd = torch.empty_like(xd)
+        eng.decode(xd, yd, cache, B, pos, max_len)
+        eng.sync()
+        out.append((yd.cpu().numpy(), host_u16(cache), eng.stats().plan.arena_bytes_used))
+        eng.destroy()
+    # a budget without room for the splits' partial results: the same bits
+    assert out[0][2] - out[1][2] == sp.sp_decode_scratch_bytes(C.byref(desc)) > 0
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    got = out[0][0].astype(np.float64) - x
     k[:, :, pos], v[:, :, pos] = a[:, :Hkv * hd].reshape(B, Hkv, hd), a[:, :Hkv * hd].reshape(B, Hkv, hd)
     ref = single_query_ref(a.reshape(B, Hq, hd), k[:, :, :pos + 1], v[:, :, :pos + 1]).reshape(B, d)
     assert max_rel(got, ref) <= 8e-3          # one bf16 rounding of the output
-    after = host_u16(cache)
+    after = out[0][1]
     kc, vc = after[:after.size // 2].reshape(B, Hkv, hd, max_len), after[after.size // 2:].reshape(B, Hkv, max_len, hd)
     assert np.array_equal(bf16_vals(kc[..., pos]), k[:, :, pos]) and np.array_equal(bf16_vals(vc[:, :, pos]), v[:, :, pos])
     kc[..., pos], vc[:, :, pos] = kb[:, :, pos], vb[:, :, pos]
