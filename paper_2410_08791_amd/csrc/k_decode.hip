@@ -436,8 +436,10 @@ hipError_t spk_launch_kv_append(hipStream_t st, const bf16_t* qkv, int ld_qkv, b
 static hipError_t decode_step(hipStream_t st, const DecodeCall& c, int hd) {
     const int n = c.n + c.fresh;
     if (c.B < 1 || n < 1 || n > c.max_len || (c.max_len & 7) || c.max_len > kDecodeMaxLen || c.Hkv < 1 || c.Hq % c.Hkv ||
-        c.ld_qkv % 8 || ((uintptr_t)c.kt & 15) || ((uintptr_t)c.v & 15) || ((uintptr_t)c.qkv & 15))
+        ((uintptr_t)c.kt & 15) || ((uintptr_t)c.v & 15))
         return hipErrorInvalidValue;
+    // queries are read one by one; the new value row, which only a step has, by 16 bytes
+    if (c.fresh && (c.ld_qkv % 8 || ((uintptr_t)c.qkv & 15))) return hipErrorInvalidValue;
     if (hd == 128) return launch_decode<128>(st, c);
     if (hd == 64) return launch_decode<64>(st, c);
     return hipErrorInvalidValue;

@@ -137,6 +137,24 @@ def test_decode_attention_heads_and_waves(B, Hq, Hkv, n, hd):
     assert max_rel(bf16_vals(out[:B]), single_query_ref(q[:, :Hq], k, v)) <= 8e-3      # one bf16 rounding of the output
 
 
+@pytest.mark.parametrize("shift", [1, 4])
+def test_decode_attention_takes_queries_at_any_element(shift):
+    """The fused activation may start at any bf16 element: only the cache is read by 16 bytes."""
+    rng = np.random.default_rng(shift)
+    B, Hq, Hkv, n, hd = 2, 4, 2, 96, 64
+    qb, q = rand_bf16(rng, (B, Hq + 2 * Hkv, hd))
+    kb, k = rand_bf16(rng, (B, Hkv, n, hd))
+    vb, v = rand_bf16(rng, (B, Hkv, n, hd))
+    qd = dev_u16(np.concatenate([np.zeros(shift, np.uint16), qb.reshape(-1)]))[shift:]
+    assert qd.data_ptr() % 16
+    kd, vd = dev_u16(kb.transpose(0, 1, 3, 2)), dev_u16(vb)
+    o = torch.zeros(B * Hq * hd, dtype=torch.int16, device=DEV)
+    assert sp.spk_decode_attention(stream_ptr(), ptr(qd), ptr(kd), ptr(vd), ptr(o), B, n, n, Hq, Hkv, hd) == sp.SP_OK
+    torch.cuda.synchronize()
+    got = bf16_vals(host_u16(o)).reshape(B, Hq, hd)
+    assert max_rel(got, single_query_ref(q[:, :Hq], k, v)) <= 8e-3      # one bf16 rounding of the output
+
+
 def attention_only_layer(Hq, Hkv, hd, B):
     """A decoder layer whose q, k and v are the leading elements of the normed input, whose output projection is the
     identity and whose MLP is zero: y - x is the attention output itself."""
