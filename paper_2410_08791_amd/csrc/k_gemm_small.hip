@@ -46,7 +46,11 @@ struct SmallCfg {
     static_assert(NI * (NST - 1) < 63 && (RG == KG || KG % 2 == 0) && LDS <= 160 * 1024 && THREADS <= 1024, "fits the counters, the LDS and a work-group");
 };
 
-template <class C, int EPI, int AFORM, int WFORM>
+// NACC: accumulator sets, taken in turn by a k-tile's steps and added at the end.  Two with four contraction groups,
+// at most SPK_FEW_ROWS rows and an fp32 output: the sums are then as short as with eight groups, which such launches
+// always had (relative error of 64 x 8192 x 28672 3.6e-7, with one set 5.1e-7; of a bf16 output the rounding is
+// 1.7e-3 either way).  Costs 0 to 0.7 us of a launch.
+template <class C, int EPI, int AFORM, int WFORM, int NACC>
 __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr bool SWIGLU = (EPI == EPI_SWIGLU_BF16);
@@ -114,13 +118,15 @@ __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
 
     constexpr int ACC = C::ROW16 ? 4 : 16;             // accumulator registers per tile: ACC / 4 groups of four columns
     typedef float acc_t __attribute__((ext_vector_type(ACC)));
-    acc_t acc[TN][TM];
+    acc_t sums[NACC][TN][TM];
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int a = 0; a < NACC; ++a)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < ACC; ++e) acc[j][i][e] = 0.f;
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int e = 0; e < ACC; ++e) sums[a][j][i][e] = 0.f;
     constexpr int KS = C::ROW16 ? 2 : 4;               // MFMA steps per k-tile
     int abase[TM], wbase[TN];
     if constexpr (C::ROW16) {
@@ -158,8 +164,9 @@ __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
-                    if constexpr (C::ROW16) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], af[ks][i], acc[j][i], 0, 0, 0);
-                    else acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks][j], af[ks][i], acc[j][i], 0, 0, 0);
+                    acc_t& s = sums[ks % NACC][j][i];
+                    if constexpr (C::ROW16) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], af[ks][i], s, 0, 0, 0);
+                    else s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks][j], af[ks][i], s, 0, 0, 0);
                 }
     };
     constexpr int NMFMA = KS * TM * TN;
@@ -216,6 +223,12 @@ __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
     }
     }
 #undef SP_SMALL_ISSUE
+    acc_t (&acc)[TN][TM] = sums[0];
+    if constexpr (NACC == 2)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[j][i] += sums[1][j][i];
     sp_lds_barrier();     // every load has been waited for, every fragment read is done: the LDS is free
 
     float* red = reinterpret_cast<float*>(smem);
@@ -300,11 +313,11 @@ __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
     }
 }
 
-template <class C, int EPI, int AFORM, int WFORM>
-hipError_t launch_small(hipStream_t st, const GemmArgs& g) {
+template <class C, int EPI, int AFORM, int WFORM, int NACC>
+hipError_t launch_acc(hipStream_t st, const GemmArgs& g) {
     constexpr int BN_OUT = (EPI == EPI_SWIGLU_BF16) ? C::BN / 2 : C::BN;
     static LdsLimitOnce lds_limit;
-    auto kern = gemm_small_kernel<C, EPI, AFORM, WFORM>;
+    auto kern = gemm_small_kernel<C, EPI, AFORM, WFORM, NACC>;
     hipError_t e = lds_limit.set(reinterpret_cast<const void*>(kern), C::LDS);
     if (e != hipSuccess) return e;
     GemmDev d;
@@ -313,8 +326,16 @@ hipError_t launch_small(hipStream_t st, const GemmArgs& g) {
     d.M = g.M; d.N = g.N; d.K = g.K;
     d.tilesM = (g.M + C::BM - 1) / C::BM;
     d.tilesN = (g.N + BN_OUT - 1) / BN_OUT;
-    gemm_small_kernel<C, EPI, AFORM, WFORM><<<d.tilesM * d.tilesN, C::THREADS, C::LDS, st>>>(d);
+    gemm_small_kernel<C, EPI, AFORM, WFORM, NACC><<<d.tilesM * d.tilesN, C::THREADS, C::LDS, st>>>(d);
     return hipGetLastError();
+}
+
+template <class C, int EPI, int AFORM, int WFORM>
+hipError_t launch_small(hipStream_t st, const GemmArgs& g) {
+    constexpr bool F32OUT = EPI == EPI_RESID_F32 || EPI == EPI_F32;
+    if constexpr (F32OUT && C::KG == 4 && C::BM <= SPK_FEW_ROWS && AFORM == OP_KMAJOR && WFORM == OP_KMAJOR)
+        if (g.M <= SPK_FEW_ROWS) return launch_acc<C, EPI, AFORM, WFORM, 2>(st, g);
+    return launch_acc<C, EPI, AFORM, WFORM, 1>(st, g);
 }
 
 // Tile ids 14..20.  32x32 and 16x32 leave room for two work-groups per CU.

@@ -162,6 +162,24 @@ def test_gemm_small_tiles_transposed_operands(M, N, K, tile):
         assert np.all(np.abs(C_.cpu().numpy() - ref) <= tol)
 
 
+@pytest.mark.parametrize("M", [1, 16, 17, 33, 64])
+@pytest.mark.parametrize("N,K", [(8192, 8192), (1280, 5120)])
+def test_gemm_few_rows_fp32_sums_are_short(M, N, K):
+    """The fp32 result of at most 64 rows against float64: eight partial sums per element.  With sums of K products the
+    error of such a product of independent normals is about c sqrt(K / parts) 2^-24 of it; c = 0.089 was measured for
+    eight parts (1.68e-7 at K = 8192); four parts exceed the bound below by a tenth or more."""
+    rng = np.random.default_rng(M + N)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (N, K), 0.02)
+    Ad, Wd = dev_u16(Ab), dev_u16(Wb)
+    R = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    assert sp.spk_gemm(stream_ptr(), sp.EPI_RESID_F32, ptr(Ad), K, 0, ptr(Wd), K, 0, ptr(R), N, ptr(R), N, None, M, N, K, 0) == sp.SP_OK
+    sync()
+    ref = torch.from_numpy(A).to(DEV) @ torch.from_numpy(W).to(DEV).t().contiguous()
+    err = float((R.double() - ref).norm() / ref.norm())
+    assert err <= 1.2 * 0.089 * np.sqrt(K / 8) * 2.0 ** -24, err
+
+
 def test_gemm_few_rows_kernel_refuses_what_it_cannot_take():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     f = torch.zeros(1 << 14, dtype=torch.float32, device=DEV)
