@@ -130,10 +130,9 @@ __global__ __launch_bounds__(NW * KS * 64) void decode_attn_kernel(
     __shared__ __attribute__((aligned(16))) float rows_lds[SEQ ? G * MAX_SPLITS * (HD + 2) : 1];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = Hq / Hkv, ngb = (grp + G - 1) / G;
-    const int id = SEQ ? blockIdx.x : blockIdx.x / splits, hb = id % (Hkv * ngb), b = id / (Hkv * ngb);
     const int wi = w % NW, sub = w / NW;   // wave of its split, split of the KS
-    int split = SEQ ? sub : blockIdx.x % splits;
-    const int hk = hb / ngb, h0 = (hb % ngb) * G;
+    int split = SEQ ? sub : blockIdx.x;
+    const int hk = blockIdx.y / ngb, h0 = (blockIdx.y % ngb) * G, b = blockIdx.z;
     const bf16_t* row = qkv + (size_t)b * ld_qkv;
     for (int i = threadIdx.x; i < G * HD; i += NW * KS * 64) {
         const int g = i / HD, h = min(h0 + g, grp - 1);       // heads past the group repeat its last one and are not stored
@@ -353,8 +352,8 @@ __global__ __launch_bounds__(NW * KS * 64) void decode_attn_kernel(
 template <int HD>
 __global__ __launch_bounds__(HD) void combine_kernel(const float* __restrict__ part, int splits, bf16_t* __restrict__ o,
                                                      int ld_o, int Hq) {
-    const int hq = blockIdx.x % Hq, b = blockIdx.x / Hq;
-    o[(size_t)b * ld_o + hq * HD + threadIdx.x] = f2bf(combine_rows<HD>(part + (size_t)blockIdx.x * splits * (HD + 2), splits, threadIdx.x));
+    const int hq = blockIdx.x, b = blockIdx.y;
+    o[(size_t)b * ld_o + hq * HD + threadIdx.x] = f2bf(combine_rows<HD>(part + (size_t)(b * Hq + hq) * splits * (HD + 2), splits, threadIdx.x));
 }
 
 struct DecodeCall {
@@ -368,13 +367,12 @@ struct DecodeCall {
 template <int HD, int G, int NW, int KS>
 hipError_t launch_one(hipStream_t st, const DecodeCall& c, int splits, int per) {
     const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
-    const long blocks = (long)c.B * c.Hkv * ((c.Hq / c.Hkv + G - 1) / G) * (KS > 1 ? 1 : splits);
-    if (blocks * NW * KS * 64 > 0xffffffffL) return hipErrorInvalidValue;     // work-items of a launch
-    decode_attn_kernel<HD, G, NW, KS><<<(unsigned)blocks, NW * KS * 64, 0, st>>>(c.qkv, c.ld_qkv, c.kt, c.v, c.o, c.ld_o, c.part, c.n,
-                                                                                 c.fresh, splits, per, c.max_len, c.Hq, c.Hkv, sl2);
+    const dim3 grid(KS > 1 ? 1 : splits, c.Hkv * ((c.Hq / c.Hkv + G - 1) / G), c.B);
+    decode_attn_kernel<HD, G, NW, KS><<<grid, NW * KS * 64, 0, st>>>(c.qkv, c.ld_qkv, c.kt, c.v, c.o, c.ld_o, c.part, c.n, c.fresh, splits,
+                                                                     per, c.max_len, c.Hq, c.Hkv, sl2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || KS > 1 || splits == 1) return e;
-    combine_kernel<HD><<<c.B * c.Hq, HD, 0, st>>>(c.part, splits, c.o, c.ld_o, c.Hq);
+    combine_kernel<HD><<<dim3(c.Hq, c.B), HD, 0, st>>>(c.part, splits, c.o, c.ld_o, c.Hq);
     return hipGetLastError();
 }
 
