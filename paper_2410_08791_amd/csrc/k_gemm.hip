@@ -752,15 +752,10 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& g) {
 // ceil(tiles / concurrent) rounds of one tile's time; a tile's time is its area over a measured
 // relative efficiency (larger tiles move fewer operand bytes per MFMA).  Take the cheapest.
 // (Activation rows are contiguous in A, C and R, so a launch can be cut along M.)
-struct TileCost { int id, bm, bn, concurrent; float eff, single; };   // single: a CU's time with one of its two tiles
-constexpr TileCost kDmaTiles[] = {{5, 256, 256, 256, 1.00f, 1.f}, {10, 256, 320, 256, 1.02f, 1.f}, {8, 256, 192, 256, 0.85f, 1.f},
-                                  {6, 128, 256, 256, 0.84f, 1.f}, {7, 128, 128, 512, 0.70f, 1.f}};
-// An operand with the row index contiguous.  Against 32 measured backward shapes (T 1500..16384, d 1280..4096) this
-// picks the fastest of the five or one within 7 %.  One 128x128 tile alone on its CU takes 0.83 of the time of two
-// (115 us for 256 tiles of K = 8192, 139 us for 400), the 128x256 tile less than either (104 us, 125 us).
-constexpr TileCost kDmaTilesR[] = {{5, 256, 256, 256, 1.00f, 1.f}, {10, 256, 320, 256, 1.05f, 1.f}, {8, 256, 192, 256, 0.88f, 1.f},
-                                   {6, 128, 256, 256, 0.84f, 1.f}, {7, 128, 128, 512, 0.80f, 2.f}};
-constexpr TileCost kRegTiles[] = {{4, 256, 256, 256, 1.00f, 1.f}, {1, 128, 128, 512, 0.66f, 1.f}};
+struct TileCost { int id, bm, bn, concurrent; float eff; };
+constexpr TileCost kDmaTiles[] = {{5, 256, 256, 256, 1.00f}, {10, 256, 320, 256, 1.02f}, {8, 256, 192, 256, 0.85f},
+                                  {6, 128, 256, 256, 0.84f}, {7, 128, 128, 512, 0.70f}};
+constexpr TileCost kRegTiles[] = {{4, 256, 256, 256, 1.00f}, {1, 128, 128, 512, 0.66f}};
 
 template <int NC>
 int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out) {
@@ -774,7 +769,7 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
         // in units of "every CU busy with one tile": the two-per-CU tile fills a CU with two
         float units = (float)(tiles / t.concurrent * (t.concurrent / 256));
         const long rem = tiles % t.concurrent;
-        if (rem) units += rem <= 256 ? t.single : (float)(t.concurrent / 256);
+        if (rem) units += rem <= 256 ? 1.f : (float)(t.concurrent / 256);
         const float cost = units * (float)(t.bm * t.bn) / t.eff;
         if (c == 0 || cost < best_cost) { best = t.id; best_cost = cost; }   // candidate 0 takes every epilogue
     }
@@ -782,41 +777,88 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
     return best;
 }
 
-// The library's own choice for a shape: the tile, and when a ragged last row of 256-row tiles
-// would cost a whole extra round (ViT-H: 16448 tokens = 64 tiles + 64 rows, 1300 tiles = 5.08
-// rounds of 256) the rows beyond the last multiple of 256 become a launch of their own.
-GemmPlan plan_gemm(int epi, bool dma_ok, bool kmajor, int M, int N, float* cost = nullptr) {
-    GemmPlan pl{0, M, 0};
-    if (!dma_ok) {
-        pl.tile = pick_tile(kRegTiles, M, N, epi, cost);
-        return pl;
+// Operands with the row index contiguous: the estimated time in us of a tile, as fitted to 764 launches (T 64..8192,
+// widths 256..4096, operands not in the caches; rms 4-12 %): launch and prologue a, per unit (one work-group on every
+// CU) b and c per 1000 of K, w per MB of output.  A last round of the two-per-CU tiles that fills one half of the slots
+// counts `half` units.  The LDS-DMA tiles and the small ones (16, 18; not with the residual epilogue) stand in one
+// table, so that every pair is compared by measured time: the choice is 0.5 % off the best tile on average.  Estimates
+// from tile area and a rate, without the output's share, were 2.7 % off and up to 1.9 times with few tokens (dW
+// 1024 x 4096 over 64 tokens 16.5 us on 32x32 tiles, 8.5 on 128x128).
+struct TileTime { int id, bm, bn, concurrent; float a, b, c, w, half; };
+constexpr TileTime kTimesKR[] = {{5, 256, 256, 256, 4.245f, 1.305f, 20.73f, 0.417f, 1.f}, {10, 256, 320, 256, 0.335f, 6.826f, 23.81f, 0.326f, 1.f},
+                                 {8, 256, 192, 256, 3.847f, 0.f, 18.25f, 0.448f, 1.f},    {6, 128, 256, 256, 1.256f, 2.700f, 11.91f, 0.443f, 1.f},
+                                 {7, 128, 128, 512, 2.006f, 0.f, 7.214f, 0.495f, 1.764f}, {16, 32, 32, 512, 2.321f, 0.f, 2.340f, 0.422f, 1.f},
+                                 {18, 64, 64, 256, 1.670f, 1.554f, 3.881f, 0.718f, 1.f}};
+constexpr TileTime kTimesRR[] = {{5, 256, 256, 256, 2.697f, 5.682f, 20.57f, 0.173f, 1.f}, {10, 256, 320, 256, 2.748f, 8.311f, 23.87f, 0.154f, 1.f},
+                                 {8, 256, 192, 256, 4.663f, 1.246f, 17.92f, 0.218f, 1.f}, {6, 128, 256, 256, 3.889f, 0.785f, 11.85f, 0.261f, 1.f},
+                                 {7, 128, 128, 512, 3.809f, 0.f, 7.698f, 0.230f, 1.625f}, {16, 32, 32, 512, 2.238f, 0.f, 2.507f, 0.462f, 1.184f},
+                                 {18, 64, 64, 256, 2.078f, 1.246f, 4.123f, 0.380f, 1.f}};
+
+int quickest_tile(int epi, int a_form, int M, int N, int K, float* us) {
+    const bool small_ok = epi != EPI_RESID_F32;
+    const float out_mb = (float)M * (float)N * (epi == EPI_BF16 ? 2e-6f : 4e-6f);
+    int best = 0;
+    for (const TileTime& t : a_form == OP_KMAJOR ? kTimesKR : kTimesRR) {
+        if (t.id >= 14 && !small_ok) continue;
+        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rem = tiles % t.concurrent;
+        const float units = (float)(tiles / t.concurrent * (t.concurrent / 256)) + (rem == 0 ? 0.f : rem <= 256 ? t.half : (float)(t.concurrent / 256));
+        const float c = t.a + units * (t.b + t.c * (float)K * 1e-3f) + t.w * out_mb;
+        if (!best || c < *us) { best = t.id; *us = c; }
     }
-    if (kmajor && M <= SPK_FEW_ROWS) {     // a decode step: nothing of W is re-used, stream it
-        pl.tile = 9;
-        return pl;
-    }
-    auto pick = [&](int m, float* c) { return kmajor ? pick_tile(kDmaTiles, m, N, epi, c) : pick_tile(kDmaTilesR, m, N, epi, c); };
-    float whole;
-    pl.tile = pick(M, &whole);
-    if (cost) *cost = whole;
+    return best;
+}
+
+// Cuts a launch along M where the ragged rows beyond the last multiple of 256 cost less as a launch of their own
+// (ViT-H: 16448 tokens = 64 tiles + 64 rows, 1300 tiles = 5.08 rounds of 256).  pick(rows, &cost) -> tile.
+template <class PICK, class TAIL>
+GemmPlan cut_plan(int M, PICK pick, TAIL tail_pick, float* cost) {
+    float whole, c_body, c_tail;
+    GemmPlan pl{pick(M, &whole), M, 0};
     const int tail = M % 256, body = M - tail;
     if (tail && body) {
-        float c_body, c_tail;
-        const int t_body = pick(body, &c_body);
-        int t_tail;
-        if (kmajor && tail <= SPK_FEW_ROWS) {
-            // the small-tile kernel in the units of pick_tile (a round of 256x256 tiles = 65536):
-            // N x K x 2 bytes at ~4.5 TB/s against 256 tiles x 2 x 65536 K flop at ~1.3 PFLOP/s, plus a launch
-            t_tail = 9;
-            c_tail = 1.13f * (float)N + 6000.f;
-        } else {
-            t_tail = pick(tail, &c_tail);
-        }
+        const int t_body = pick(body, &c_body), t_tail = tail_pick(tail, &c_tail);
         if (c_body + c_tail < 0.97f * whole) {
             pl = GemmPlan{t_body, body, t_tail};
-            if (cost) *cost = c_body + c_tail;
+            whole = c_body + c_tail;
         }
     }
+    if (cost) *cost = whole;
+    return pl;
+}
+
+// The large-tile plan of operands with the contraction index contiguous, from M and N alone.
+GemmPlan plan_large(int epi, int M, int N, float* cost = nullptr) {
+    if (M <= SPK_FEW_ROWS) return GemmPlan{9, M, 0};     // a decode step: nothing of W is re-used, stream it
+    auto pick = [&](int m, float* c) { return pick_tile(kDmaTiles, m, N, epi, c); };
+    auto tail = [&](int m, float* c) {
+        if (m > SPK_FEW_ROWS) return pick(m, c);
+        // the small-tile kernel in the units of pick_tile (a round of 256x256 tiles = 65536):
+        // N x K x 2 bytes at ~4.5 TB/s against 256 tiles x 2 x 65536 K flop at ~1.3 PFLOP/s, plus a launch
+        *c = 1.13f * (float)N + 6000.f;
+        return 9;
+    };
+    return cut_plan(M, pick, tail, cost);
+}
+
+// What a launch with tile = 0 runs, for every operand form: rows [0, body_rows) on `tile`, the others on `tail_tile`
+// (tile ids of launch_tile, 9 resolved).  `wide`: the rows of C start on 16 bytes.
+GemmPlan resolve_gemm(int epi, bool wide, int a_form, int w_form, int M, int N, int K) {
+    const bool kmajor = a_form == OP_KMAJOR && w_form == OP_KMAJOR;
+    float small_us, cost;
+    if (!kmajor && wide) {
+        auto pick = [&](int m, float* c) { return quickest_tile(epi, a_form, m, N, K, c); };
+        return cut_plan(M, pick, pick, nullptr);
+    }
+    const int small_id = spk_small_gemm_tile(epi, a_form, w_form, M, N, K, &small_us);
+    GemmPlan pl{0, M, 0};
+    if (wide) pl = plan_large(epi, M, N, &cost);
+    else pl.tile = pick_tile(kRegTiles, M, N, epi, &cost);
+    if (pl.tile == 9) return GemmPlan{small_id, M, 0};
+    // Both estimates are fits with 10-18 % error, so the small tiles have to be cheaper by a tenth:
+    // over 180 shapes of up to 2560 rows the choice is within 1 % of the better kernel on average
+    // (2.1 times as fast as the large tiles alone) and in one of them slower than the large tiles.
+    if (small_id && small_us < 0.9f * (4.5f + cost * (float)K * 4.55e-7f)) return GemmPlan{small_id, M, 0};
+    if (pl.tail_tile == 9) pl.tail_tile = spk_small_gemm_tile(epi, a_form, w_form, M - pl.body_rows, N, K, &small_us);
     return pl;
 }
 
@@ -835,16 +877,8 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
         float us;
         return small(tile == 9 ? spk_small_gemm_tile(EPI, g.a_form, g.w_form, g.M, g.N, g.K, &us) : tile == 11 ? 14 : tile == 12 ? 16 : 17);
     }
-    if (tile >= 14) return small(tile);
     if (!tile) {
-        float small_us, large_cost;
-        const int small_id = spk_small_gemm_tile(EPI, g.a_form, g.w_form, g.M, g.N, g.K, &small_us);
-        const GemmPlan pl = plan_gemm(EPI, dma, KMAJOR, g.M, g.N, &large_cost);
-        if (pl.tile == 9) return small(small_id);
-        // Both estimates are fits with 10-18 % error, so the small tiles have to be cheaper by a tenth:
-        // over 180 shapes of up to 2560 rows the choice is within 1 % of the better kernel on average
-        // (2.1 times as fast as the large tiles alone) and in one of them slower than the large tiles.
-        if (small_id && small_us < 0.9f * (4.5f + large_cost * (float)g.K * 4.55e-7f)) return small(small_id);
+        const GemmPlan pl = resolve_gemm(EPI, dma, AFORM, WFORM, g.M, g.N, g.K);
         tile = pl.tile;
         if (pl.body_rows < g.M) {
             GemmArgs a = g, b = g;
@@ -857,6 +891,7 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
             return e != hipSuccess ? e : launch_tile<EPI, AFORM, WFORM>(st, b);
         }
     }
+    if (tile >= 14) return small(tile);
     if (!dma && ((tile >= 5 && tile <= 8) || tile == 10)) tile = tile == 6 ? 2 : tile == 7 ? 1 : 4;   // register-staged instead
     switch (tile) {
         case 1: return launch_one<128, 128, EPI, AFORM, WFORM, 4>(st, g);
@@ -875,8 +910,8 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
 }  // namespace
 
 GemmPlan spk_gemm_plan_host(int epi, int a_form, int w_form, int M, int N) {
-    const bool kmajor = a_form == OP_KMAJOR && w_form == OP_KMAJOR;
-    return plan_gemm(epi, kmajor, kmajor, M, N);
+    if (a_form == OP_KMAJOR && w_form == OP_KMAJOR) return plan_large(epi, M, N);
+    return GemmPlan{pick_tile(kRegTiles, M, N, epi, nullptr), M, 0};
 }
 
 hipError_t spk_launch_gemm(hipStream_t st, int epi, const GemmArgs& g) {

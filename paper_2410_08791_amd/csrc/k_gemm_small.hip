@@ -368,19 +368,15 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
 
 // Estimated time of a tile in us: launch, prologue and epilogue (a, b per unit), operand tiles (c per
 // unit and 1000 of K), the weights from HBM (bw, TB/s).  A unit is one work-group on every CU.
-// Fitted to 180 shapes (M 17..2560, N 256..12288, K 256..11008; 20 with a row-contiguous operand), rms
-// error 7-14 %.
+// Fitted to 160 shapes (M 17..2560, N 256..12288, K 256..11008), rms error 7-14 %.  (Operands with the row index
+// contiguous are compared with the large tiles in one table, k_gemm.hip.)
 struct SmallCost { int id, bm, bn, per_cu; float a, b, c, bw; };
 constexpr SmallCost kSmallK[] = {{16, 32, 32, 2, 1.9f, 0.16f, 1.52f, 13.0f}, {17, 64, 32, 1, 0.5f, 2.2f, 2.24f, 17.5f},
                                  {18, 64, 64, 1, 0.5f, 3.1f, 3.03f, 12.8f},  {19, 96, 64, 1, 0.5f, 3.95f, 3.82f, 16.6f},
                                  {20, 64, 128, 1, 0.5f, 2.9f, 5.48f, 13.9f}};
-constexpr SmallCost kSmallKR[] = {{16, 32, 32, 2, 1.35f, 0.f, 2.39f, 1e9f}, {18, 64, 64, 1, 0.5f, 2.9f, 3.95f, 1e9f}};
-constexpr SmallCost kSmallRR[] = {{16, 32, 32, 2, 1.6f, 0.f, 2.81f, 1e9f}, {18, 64, 64, 1, 0.6f, 2.6f, 4.47f, 1e9f}};
-
-template <int NC>
-int cheapest(const SmallCost (&cand)[NC], int epi, int M, int N, int K, float* us) {
+int cheapest(int epi, int M, int N, int K, float* us) {
     int best = 0;
-    for (const SmallCost& t : cand) {
+    for (const SmallCost& t : kSmallK) {
         const int bn_out = epi == EPI_SWIGLU_BF16 ? t.bn / 2 : t.bn;
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + bn_out - 1) / bn_out), round = 256 * t.per_cu;
         const long units = tiles / round * t.per_cu + (tiles % round == 0 ? 0 : tiles % round <= 256 ? 1 : t.per_cu);
@@ -396,14 +392,12 @@ int cheapest(const SmallCost (&cand)[NC], int epi, int M, int N, int K, float* u
 int spk_small_gemm_tile(int epi, int a_form, int w_form, int M, int N, int K, float* us) {
     const int forms = a_form * 2 + w_form;
     if (forms == 0) {
-        if (M > 16) return cheapest(kSmallK, epi, M, N, K, us);
+        if (M > 16) return cheapest(epi, M, N, K, us);
         // at most 16 rows: 16 columns per work-group while that is one round of the chip (4096 x 4096,
         // 8 rows: 8.5 us against 10.6), 32 beyond (11008 x 4096 SwiGLU: 38.3 against 32.1)
         *us = 0.f;
         return (epi == EPI_SWIGLU_BF16 ? (N + 7) / 8 : (N + 15) / 16) <= 256 ? 14 : 15;
     }
-    if (forms == 1 && (epi == EPI_BF16 || epi == EPI_F32)) return cheapest(kSmallKR, epi, M, N, K, us);
-    if (forms == 3 && epi == EPI_F32) return cheapest(kSmallRR, epi, M, N, K, us);
     return 0;
 }
 

@@ -290,6 +290,29 @@ def test_gemm_transposed_operands_lds_dma(M, N, K, tile):
         assert np.all(np.abs(got - want) <= tol + (2.0 ** -23 * np.abs(want) if f32out else BF16_EPS * np.abs(want))), (epi, a_form)
 
 
+@pytest.mark.parametrize("M,N,K", [(1024, 4096, 64), (2560, 640, 320), (640, 640, 512), (512, 2048, 64), (2072, 1032, 256), (264, 40, 1088),
+                                   (1032, 2560, 128)])
+def test_gemm_transposed_operands_own_choice(M, N, K):
+    """The backward forms with the library's own tile: few tokens (short contractions), narrow and wide outputs, ragged
+    rows and columns.  One guard row behind C."""
+    rng = np.random.default_rng(M + N + K)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (N, K), 0.1)
+    Ad, ATd, WTd = dev_u16(Ab), dev_u16(Ab.T), dev_u16(Wb.T)
+    ref = A @ W.T
+    tol = 2e-6 * np.sqrt(K) * np.max(np.abs(ref))                          # as in test_gemm_transposed_operands
+    for epi, a_form in ((sp.EPI_BF16, 0), (sp.EPI_F32, 0), (sp.EPI_F32, 1)):
+        f32out = epi != sp.EPI_BF16
+        Cd = torch.full((M + 1, N), 7.0 if f32out else 7, dtype=torch.float32 if f32out else torch.int16, device=DEV)
+        assert sp.spk_gemm(stream_ptr(), epi, ptr(ATd if a_form else Ad), M if a_form else K, a_form, ptr(WTd), N, 1, ptr(Cd), N,
+                           None, N, None, M, N, K, 0) == sp.SP_OK
+        sync()
+        out = Cd.cpu()
+        assert bool((out[M] == 7).all())
+        got = out[:M].numpy() if f32out else bf16_vals(host_u16(out[:M].contiguous()))
+        assert np.all(np.abs(got - ref) <= tol + (0 if f32out else BF16_EPS * np.abs(ref))), (epi, a_form)
+
+
 def test_gemm_rejects_shapes_it_cannot_take():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     args = lambda M, N, K, lda=64, ldw=64, ldc=64: sp.spk_gemm(  # noqa: E731
