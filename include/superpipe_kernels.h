@@ -47,12 +47,13 @@ int spk_gemm(void* stream, int epilogue, const uint16_t* A, int lda, int a_form,
              int w_form, void* C, int ldc, const float* R, int ldr, const uint16_t* bias, int M, int N, int K,
              int tile);
 
-/* The large-tile plan behind tile = 0 for a shape (host-only query, nothing is launched; the choice depends
- * on the shape alone, never on addresses or on the streaming window): out3 (host) = {tile id of rows
- * [0, body_rows), body_rows, tile id of rows [body_rows, M) or 0 when body_rows == M}.  A launch too small
- * for it (judged with K) runs on the small-tile kernel instead.  With an operand of form 1 the answer is the
- * register-staged tile, which runs where the rows of C are no multiple of 16 bytes; other launches of these
- * forms take the LDS-DMA tiles by the same rule with their own measured costs. */
+/* What tile = 0 runs (host-only query, nothing is launched; the launch itself asks the same function, and the answer
+ * depends on the arguments alone, never on addresses or on the streaming window): out3 (host) = {tile id of rows
+ * [0, body_rows), body_rows, tile id of rows [body_rows, M) or 0 when body_rows == M}. */
+int spk_gemm_resolve(int epilogue, int a_form, int w_form, int M, int N, int K, int ldc, int* out3);
+/* The part of that choice that M and N alone decide: with both forms 0 the large-tile plan (a launch too small for it,
+ * judged with K, runs on the small-tile kernel instead), with an operand of form 1 the register-staged tile, which
+ * runs where the rows of C are no multiple of 16 bytes. */
 int spk_gemm_plan(int epilogue, int a_form, int w_form, int M, int N, int* out3);
 
 /* z bf16 [T,f] = silu(gu[:, :f]) * gu[:, f:]; gu bf16 [T,2f]; f % 8 == 0. */

@@ -909,6 +909,10 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
 
 }  // namespace
 
+GemmPlan spk_gemm_resolve_host(int epi, bool wide, int a_form, int w_form, int M, int N, int K) {
+    return resolve_gemm(epi, wide, a_form, w_form, M, N, K);
+}
+
 GemmPlan spk_gemm_plan_host(int epi, int a_form, int w_form, int M, int N) {
     if (a_form == OP_KMAJOR && w_form == OP_KMAJOR) return plan_large(epi, M, N);
     return GemmPlan{pick_tile(kRegTiles, M, N, epi, nullptr), M, 0};

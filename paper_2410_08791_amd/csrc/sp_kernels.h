@@ -62,6 +62,8 @@ int spk_small_gemm_tile(int epilogue, int a_form, int w_form, int M, int N, int 
 // kernel.  A launch whose estimate the small-tile kernel undercuts runs on that one instead.
 struct GemmPlan { int tile, body_rows, tail_tile; };
 GemmPlan spk_gemm_plan_host(int epilogue, int a_form, int w_form, int M, int N);
+// What tile = 0 runs (the launcher uses this itself); wide: the rows of C start on 16 bytes.
+GemmPlan spk_gemm_resolve_host(int epilogue, bool wide, int a_form, int w_form, int M, int N, int K);
 
 // out bf16 [T,d] = norm(h fp32 [T,d]); bias == nullptr -> RMSNorm, else LayerNorm.
 hipError_t spk_launch_norm(hipStream_t st, const float* h, const bf16_t* gain, const bf16_t* bias,

@@ -222,15 +222,15 @@ def gemm_plan(epi, a_form, w_form, M, N):
 
 
 def test_gemm_plan_is_a_function_of_the_shape_alone():
-    """What tile = 0 resolves to: valid ids, the whole of M covered, the SwiGLU epilogue never on
-    the tile that cannot pair gate and up rows, the operand forms the LDS-DMA kernel does not take
-    on the register-staged tiles, and the workloads' projections on the tiles their round counts
-    call for (256 work-groups run at a time)."""
+    """What M and N alone decide: valid ids, the whole of M covered, the SwiGLU epilogue never on the tile that
+    cannot pair gate and up rows, for a row-contiguous operand the register-staged tile of outputs whose rows are
+    not on 16 bytes, and the workloads' projections on the tiles their round counts call for (256 work-groups run
+    at a time)."""
     for epi in range(5):
         for M in (1, 8, 16, 17, 64, 65, 200, 256, 300, 2048, 4096, 8192, 16448):
             for N in (8, 128, 1280, 4096, 5120, 11008, 12288, 28672):
                 tile, body, tail_tile = gemm_plan(epi, 0, 0, M, N)
-                if M <= 64:           # a decode step: the weight-streaming kernel
+                if M <= 64:           # a decode step: the small-tile kernel
                     assert (tile, body, tail_tile) == (9, M, 0)
                     assert gemm_plan(epi, 0, 1, M, N)[0] in (1, 4)
                     continue
@@ -259,6 +259,57 @@ def test_gemm_plan_is_a_function_of_the_shape_alone():
     assert gemm_plan(sp.EPI_BF16, 0, 0, 4096, 10240) == (10, 4096, 0)
     assert sp.lib.spk_gemm_plan(7, 0, 0, 8, 8, (C.c_int * 3)()) == sp.SP_ERR_INVALID_ARG
     assert sp.lib.spk_gemm_plan(0, 0, 0, 0, 8, (C.c_int * 3)()) == sp.SP_ERR_INVALID_ARG
+
+
+def gemm_resolve(epi, a_form, w_form, M, N, K, ldc=None):
+    out = (C.c_int * 3)()
+    assert sp.lib.spk_gemm_resolve(epi, a_form, w_form, M, N, K, N if ldc is None else ldc, out) == sp.SP_OK
+    return tuple(out)
+
+
+def test_gemm_resolve_covers_every_form_and_the_small_tiles():
+    """What a launch with tile = 0 runs.  Any form: the whole of M covered, cuts at multiples of 256, tiles that the
+    epilogue and the form can take, the register-staged tiles only for outputs whose rows are not on 16 bytes."""
+    large, small = (5, 6, 7, 8, 10), (14, 15, 16, 17, 18, 19, 20)
+    for epi in range(5):
+        forms = {sp.EPI_GELU_BF16: [(0, 0)], sp.EPI_SWIGLU_BF16: [(0, 0)], sp.EPI_F32: [(0, 0), (0, 1), (1, 1)]}.get(epi, [(0, 0), (0, 1)])
+        for a_form, w_form in forms:
+            ok = large + small if (a_form, w_form) == (0, 0) else large if epi == sp.EPI_RESID_F32 else large + (16, 18)
+            for M in (8, 16, 64, 72, 200, 256, 264, 2048, 4104, 16448):
+                for N in (8, 264, 1280, 4096, 11008):
+                    for K in (64, 320, 1280, 5120, 16384):
+                        t, b, tt = got = gemm_resolve(epi, a_form, w_form, M, N, K)
+                        assert t in ok and 0 < b <= M and (tt == 0) == (b == M), got
+                        if b < M:
+                            assert b % 256 == 0 and M - b < 256 and tt in ok
+                        if epi == sp.EPI_SWIGLU_BF16:
+                            assert not {t, tt} & {8, 10}
+                        if M <= 16 and (a_form, w_form) == (0, 0):
+                            assert t in (14, 15)
+                        if M <= 64 and (a_form, w_form) == (0, 0):
+                            assert t in small
+                        assert gemm_resolve(epi, a_form, w_form, M, N, K) == got
+                        if epi in (sp.EPI_BF16, sp.EPI_GELU_BF16, sp.EPI_SWIGLU_BF16):
+                            t, b, tt = gemm_resolve(epi, a_form, w_form, M, N, K, ldc=N + 4)
+                            assert b == M and tt == 0 and t in ((1, 4) + small if (a_form, w_form) == (0, 0) else (1, 4))
+    # forward: large launches as planned from M and N, the ragged rows of ViT-H on a small tile, one image's
+    # projections and a 512-row output projection on small tiles altogether
+    assert gemm_resolve(sp.EPI_SWIGLU_BF16, 0, 0, 2048, 11008, 4096) == (5, 2048, 0)
+    assert gemm_resolve(sp.EPI_BF16, 0, 0, 2048, 12288, 4096) == (8, 2048, 0)
+    t, b, tt = gemm_resolve(sp.EPI_GELU_BF16, 0, 0, 16448, 5120, 1280)
+    assert (t, b) == (10, 16384) and tt in small
+    assert gemm_resolve(sp.EPI_GELU_BF16, 0, 0, 257, 5120, 1280)[0] in small
+    assert gemm_resolve(sp.EPI_RESID_F32, 0, 0, 512, 4096, 4096)[0] in small
+    # backward: large tiles for many tokens, 128x128 for a short contraction into a wide output (measured 8.5 us, 32x32
+    # 16.5), 32x32 or 64x64 where large tiles leave the chip idle, ragged rows cut off
+    assert gemm_resolve(sp.EPI_BF16, 0, 1, 16384, 11008, 4096)[0] in (5, 10)
+    assert gemm_resolve(sp.EPI_F32, 1, 1, 22016, 4096, 16384)[0] in (5, 10)
+    assert gemm_resolve(sp.EPI_F32, 1, 1, 1024, 4096, 64) == (7, 1024, 0)
+    assert gemm_resolve(sp.EPI_F32, 1, 1, 256, 1024, 1024)[0] in (16, 18)
+    t, b, tt = gemm_resolve(sp.EPI_BF16, 0, 1, 16448, 5120, 1280)
+    assert b == 16384 and t in large and tt in (16, 18)
+    for bad in ((7, 0, 0, 8, 8, 64, 8), (0, 2, 0, 8, 8, 64, 8), (0, 0, 0, 8, 8, 65, 8), (0, 0, 0, 8, 9, 64, 12), (0, 0, 0, 8, 8, 64, 9), (0, 0, 0, 0, 8, 64, 8)):
+        assert sp.lib.spk_gemm_resolve(*bad, (C.c_int * 3)()) == sp.SP_ERR_INVALID_ARG
 
 
 def test_unit_ranges_and_the_plan_in_units():
