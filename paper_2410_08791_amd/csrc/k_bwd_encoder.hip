@@ -164,9 +164,11 @@ __global__ __launch_bounds__(TH) void colsum_bf16_wide_kernel(const bf16_t* __re
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4_t*>(src + (size_t)(row + j * stride) * ld + c);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) { s[2 * k] += bf_lo(v[j][k]); s[2 * k + 1] += bf_hi(v[j][k]); }
+            for (int k = 0; k < 4; ++k) {
+                // the four rows among themselves first: a quarter of the additions to the running sum, and of its error
+                s[2 * k] += (bf_lo(v[0][k]) + bf_lo(v[1][k])) + (bf_lo(v[2][k]) + bf_lo(v[3][k]));
+                s[2 * k + 1] += (bf_hi(v[0][k]) + bf_hi(v[1][k])) + (bf_hi(v[2][k]) + bf_hi(v[3][k]));
+            }
         }
         for (; row < T; row += stride) {
             const u32x4_t v = *reinterpret_cast<const u32x4_t*>(src + (size_t)row * ld + c);
@@ -179,10 +181,8 @@ __global__ __launch_bounds__(TH) void colsum_bf16_wide_kernel(const bf16_t* __re
     __syncthreads();
     const int oc = blockIdx.x * CS_COLS + threadIdx.x;
     if (oc < n) {
-        float a = 0.f;
-#pragma unroll
-        for (int r = 0; r < CS_ROWS; ++r) a += lds[r][threadIdx.x];
-        part[(size_t)blockIdx.y * n + oc] = a;
+        const int t = threadIdx.x;
+        part[(size_t)blockIdx.y * n + oc] = ((lds[0][t] + lds[1][t]) + (lds[2][t] + lds[3][t])) + ((lds[4][t] + lds[5][t]) + (lds[6][t] + lds[7][t]));
     }
 }
 

@@ -546,12 +546,31 @@ def test_layernorm_backward(T, d):
     assert np.all(np.abs(bf16_vals(host_u16(dhb)) - got) <= BF16_EPS * np.abs(got) + 1e-12)
 
 
-@pytest.mark.parametrize("T,d", [(1024, 64), (1501, 2048), (1100, 2052), (1030, 4096), (2050, 4100), (1025, 8192)])
+@pytest.mark.parametrize("T,d", [(1024, 64), (1024, 512), (1027, 516), (1501, 2048), (1100, 2052), (1030, 4096), (2050, 4100), (1025, 8192)])
 def test_norm_backward_many_rows(T, d):
     """1024 rows and more: a row held by one, two or four waves (RMSNorm; LayerNorm up to 4096 elements), at
     and past each limit, row counts that leave the last work-groups short."""
     test_rmsnorm_backward(T, d)
     test_layernorm_backward(T, d)
+
+
+@pytest.mark.parametrize("T,d", [(1024, 256), (2048, 1280), (1100, 4096)])
+def test_layernorm_backward_many_rows_error(T, d):
+    """The residual gradient of the many-rows form against float64, all operands N(0, 1): 4.6e-8 relative, as the
+    row-per-work-group form has it.  One more rounding per element (the products with the gain taken from the row sums
+    instead of being fused) gives 4.9e-8, the formula multiplied out 5.05e-8."""
+    gen = torch.Generator(device=DEV).manual_seed(T + d)
+    da, h, dh = (torch.randn(T, d, device=DEV, generator=gen) for _ in range(3))
+    gain = (1 + 0.02 * torch.randn(d, device=DEV, generator=gen)).bfloat16()
+    H = h.double().requires_grad_()
+    torch.nn.functional.layer_norm(H, (d,), gain.double(), None, 1e-5).backward(da.double())
+    ref = dh.double() + H.grad
+    dhb, scratch = torch.zeros(T, d, dtype=torch.bfloat16, device=DEV), torch.zeros(256 * 2 * d + 4096, device=DEV)
+    dg, db = torch.zeros(d, device=DEV), torch.zeros(d, device=DEV)
+    assert sp.spk_layernorm_bwd(stream_ptr(), ptr(da), ptr(h), ptr(gain), ptr(dh), ptr(dhb), ptr(scratch), ptr(dg), ptr(db), T, d, 1e-5) == sp.SP_OK
+    sync()
+    err = float((dh.double() - ref).norm() / ref.norm())
+    assert err <= 4.78e-8, err
 
 
 @pytest.mark.parametrize("n", [8, 4096 * 33, 5120 * 7])
