@@ -57,6 +57,7 @@ struct sp_engine {
     std::vector<hipEvent_t> thr_ev;
     std::vector<uint64_t> thr_at;
     uint64_t thr_head = 0, thr_tail = 0, thr_packets = 0;
+    uint64_t pass_end_thr = 0;                   // thr_head at the end of the latest training pass
     hipEvent_t pass_end_c = nullptr;             // end of the latest training pass on compute ...
     std::shared_ptr<sp_pass_end> pass_end;       // ... and on d2h
     int device = 0;

@@ -615,7 +615,8 @@ static int enqueue_training_step(sp_engine* e, const float* x_dev, const float* 
         SP_HIP(e, hipEventSynchronize(e->pass_end->d2h));
         SP_HIP(e, hipEventSynchronize(e->pass_end_c));
         e->pass_pending = false;
-        e->thr_tail = e->thr_head;                   // nothing of the previous pass is unfinished
+        // nothing of the previous pass is unfinished; forward passes enqueued after it may be
+        e->thr_tail = std::max(e->thr_tail, e->pass_end_thr);
     }
     std::shared_ptr<sp_pass_end>& last = last_pass_on(e->device);
     if (last && last != e->pass_end) SP_HIP(e, hipEventSynchronize(last->d2h));
@@ -635,6 +636,7 @@ static int enqueue_training_step(sp_engine* e, const float* x_dev, const float* 
     if ((rc = e->sched.run_pass(-1, false, sink, dx_dev ? 0 : e->frozen)) != SP_OK) return rc;
     if ((rc = sp_train_end(e, dx_dev, B, S)) != SP_OK) return rc;
     SP_HIP(e, hipEventRecord(e->pass_end_c, e->compute));
+    e->pass_end_thr = e->thr_head;
     SP_HIP(e, hipEventRecord(e->pass_end->d2h, e->d2h));
     e->pass_pending = true;
     last = e->pass_end;

@@ -8,7 +8,10 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
+#include <chrono>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/superpipe.h"
@@ -232,6 +235,43 @@ static void test_training(int arch) {
     printf("ok training arch %d\n", arch);
 }
 
+// Whether `call`, run on a thread of its own, is still inside after a while; `then` lets it end.
+template <class CALL, class THEN>
+static bool blocks_until(CALL call, THEN then) {
+    std::atomic<bool> done{false};
+    std::thread th([&] {
+        call();
+        done = true;
+    });
+    for (int i = 0; i < 40 && !done; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(10));
+    const bool blocked = !done;
+    then();
+    th.join();
+    return blocked;
+}
+
+// The run-ahead bound of 1400 packets counts forward passes that a training handle enqueued after its last step: with
+// 1152 packets of them unfinished a step of 464 more has to wait.  (The step before, which stops above seven frozen
+// layers, is 156 packets.)
+static void test_run_ahead_with_forwards_between_steps() {
+    const int B = 1, S = 8;
+    Rig r(SP_DECODER_SWIGLU_RMS, 8, B, S);
+    Handle H(r, 8, 8, SP_FLAG_TRAINING, 0, 0, 0, 7);
+    std::vector<float> y((size_t)B * S * 64), dx(y.size());
+    float loss;
+    auto step = [&](float* dx_out) {
+        CHECK(sp_forward_backward(H.h, r.x.data(), r.t.data(), y.data(), &loss, dx_out, r.grads.data(), B, S) == SP_OK, "step: %s",
+              sp_last_error(H.h));
+    };
+    step(nullptr);
+    r.sync();
+    mock_stream_hold(r.compute);
+    for (int i = 0; i < 9; ++i) CHECK(sp_forward(H.h, r.x.data(), y.data(), B, S) == SP_OK, "forward");
+    CHECK(blocks_until([&] { step(dx.data()); }, [&] { mock_stream_release(r.compute); }), "a step ran ahead of the forward passes");
+    r.sync();
+    printf("ok run-ahead with forwards between steps\n");
+}
+
 static void test_decode() {
     const int B = 2, S0 = 6, steps = 4, max_len = 16;
     Rig r(SP_DECODER_SWIGLU_RMS, 4, B, S0);
@@ -351,6 +391,7 @@ int main(int argc, char** argv) {
     test_forward_windows(SP_ENCODER_GELU_LN);
     test_training(SP_DECODER_SWIGLU_RMS);
     test_training(SP_ENCODER_GELU_LN);
+    test_run_ahead_with_forwards_between_steps();
     test_decode();
     test_injected_failures(false);
     test_injected_failures(true);

@@ -42,6 +42,9 @@ const char* hipGetErrorString(hipError_t e);
 // ---- controls of the stand-in (not part of HIP) ----
 hipStream_t mock_stream_create(void);
 void mock_stream_destroy(hipStream_t st);
+// The stream executes nothing between the two calls (what it is executing it finishes first).
+void mock_stream_hold(hipStream_t st);
+void mock_stream_release(hipStream_t st);
 // memory that hipPointerGetAttributes reports as pinned host memory
 void* mock_pinned_alloc(size_t bytes);
 void mock_pinned_free(void* p);

@@ -40,7 +40,7 @@ struct mockStream {
     std::mutex mu;
     std::condition_variable cv, idle_cv;
     std::deque<std::function<void()>> q;
-    bool stop = false, busy = false;
+    bool stop = false, busy = false, held = false;
     std::thread th;
     mockStream() : th([this] { run(); }) {}
     ~mockStream() {
@@ -56,7 +56,7 @@ struct mockStream {
             std::function<void()> f;
             {
                 std::unique_lock<std::mutex> lk(mu);
-                cv.wait(lk, [&] { return stop || !q.empty(); });
+                cv.wait(lk, [&] { return stop || (!q.empty() && !held); });
                 if (q.empty()) return;
                 f = std::move(q.front());
                 q.pop_front();
@@ -114,6 +114,17 @@ mockStream* S(hipStream_t st) {
 
 hipStream_t mock_stream_create(void) { return new mockStream(); }
 void mock_stream_destroy(hipStream_t st) { delete st; }
+void mock_stream_hold(hipStream_t st) {
+    std::lock_guard<std::mutex> lk(st->mu);
+    st->held = true;
+}
+void mock_stream_release(hipStream_t st) {
+    {
+        std::lock_guard<std::mutex> lk(st->mu);
+        st->held = false;
+    }
+    st->cv.notify_all();
+}
 
 void* mock_pinned_alloc(size_t bytes) {
     char* p = static_cast<char*>(malloc(bytes ? bytes : 1));
