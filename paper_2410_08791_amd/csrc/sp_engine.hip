@@ -78,7 +78,16 @@ constexpr uint64_t kMaxQueuedTraining = 1400, kResumeTraining = 350;
 constexpr size_t kThrottleRing = 256;
 constexpr unsigned kPacketsForward = 16, kPacketsForwardTrain = 14, kPacketsBackward = 44;
 
+// A captured pass is not executing: nothing to wait for, and nothing that a later wait could be for.
+static bool being_captured(sp_engine* e) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(e->compute, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 static int throttle_before(sp_engine* e) {
+    if (being_captured(e)) return SP_OK;
     const bool training = e->flags & SP_FLAG_TRAINING;
     const uint64_t max_packets = training ? kMaxQueuedTraining : kMaxQueuedForward;
     const uint64_t resume_packets = training ? kResumeTraining : kResumeForward;
@@ -94,6 +103,7 @@ static int throttle_before(sp_engine* e) {
 }
 
 static int throttle_after(sp_engine* e, unsigned packets) {
+    if (being_captured(e)) return SP_OK;
     e->thr_packets += packets;
     const size_t i = e->thr_head % kThrottleRing;
     SP_HIP(e, hipEventRecord(e->thr_ev[i], e->compute));

@@ -272,6 +272,24 @@ static void test_run_ahead_with_forwards_between_steps() {
     printf("ok run-ahead with forwards between steps\n");
 }
 
+// A resident stack's pass under stream capture: deeper than the run-ahead bound, behind eager passes that the bound
+// still counts; and eager passes afterwards.
+static void test_forward_under_capture() {
+    const int B = 1, S = 8;
+    Rig r(SP_DECODER_SWIGLU_RMS, 40, B, S);
+    Handle H(r, 40, 1, 0);
+    std::vector<float> y0((size_t)B * S * 64), y1(y0.size()), y2(y0.size());
+    for (int i = 0; i < 2; ++i) CHECK(sp_forward(H.h, r.x.data(), y0.data(), B, S) == SP_OK, "eager: %s", sp_last_error(H.h));
+    r.sync();
+    mock_stream_capture(r.compute, 1);
+    CHECK(sp_forward(H.h, r.x.data(), y1.data(), B, S) == SP_OK, "captured: %s", sp_last_error(H.h));
+    mock_stream_capture(r.compute, 0);
+    for (int i = 0; i < 20; ++i) CHECK(sp_forward(H.h, r.x.data(), y2.data(), B, S) == SP_OK, "eager after: %s", sp_last_error(H.h));
+    r.sync();
+    CHECK(same(y0, y1) && same(y0, y2), "a captured pass differs");
+    printf("ok forward under capture\n");
+}
+
 static void test_decode() {
     const int B = 2, S0 = 6, steps = 4, max_len = 16;
     Rig r(SP_DECODER_SWIGLU_RMS, 4, B, S0);
@@ -392,6 +410,7 @@ int main(int argc, char** argv) {
     test_training(SP_DECODER_SWIGLU_RMS);
     test_training(SP_ENCODER_GELU_LN);
     test_run_ahead_with_forwards_between_steps();
+    test_forward_under_capture();
     test_decode();
     test_injected_failures(false);
     test_injected_failures(true);

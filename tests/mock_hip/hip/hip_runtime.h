@@ -35,6 +35,8 @@ hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t ev, unsigned flags);
 hipError_t hipStreamSynchronize(hipStream_t st);
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind kind, hipStream_t st);
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p);
+typedef enum { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 } hipStreamCaptureStatus;
+hipError_t hipStreamIsCapturing(hipStream_t st, hipStreamCaptureStatus* status);
 hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute a, int v);
 hipError_t hipGetLastError(void);
 const char* hipGetErrorString(hipError_t e);
@@ -45,6 +47,9 @@ void mock_stream_destroy(hipStream_t st);
 // The stream executes nothing between the two calls (what it is executing it finishes first).
 void mock_stream_hold(hipStream_t st);
 void mock_stream_release(hipStream_t st);
+// The stream reports that it is being captured (work still runs at once); waiting for an event from the host is then
+// an error, as it is under HIP.
+void mock_stream_capture(hipStream_t st, int on);
 // memory that hipPointerGetAttributes reports as pinned host memory
 void* mock_pinned_alloc(size_t bytes);
 void mock_pinned_free(void* p);

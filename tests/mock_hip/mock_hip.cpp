@@ -40,7 +40,7 @@ struct mockStream {
     std::mutex mu;
     std::condition_variable cv, idle_cv;
     std::deque<std::function<void()>> q;
-    bool stop = false, busy = false, held = false;
+    bool stop = false, busy = false, held = false, captured = false;
     std::thread th;
     mockStream() : th([this] { run(); }) {}
     ~mockStream() {
@@ -90,6 +90,7 @@ std::map<std::string, int> g_fail;       // api -> calls left until the failing 
 std::map<std::string, long> g_count;
 std::map<const char*, size_t> g_pinned;  // base -> bytes
 mockStream* g_default = nullptr;
+int g_captures = 0;
 
 bool inject(const char* api) {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -181,7 +182,21 @@ hipError_t hipEventRecord(hipEvent_t ev, hipStream_t st) {
     });
     return hipSuccess;
 }
+void mock_stream_capture(hipStream_t st, int on) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_captures += (on ? 1 : 0) - (st->captured ? 1 : 0);
+    st->captured = on != 0;
+}
+hipError_t hipStreamIsCapturing(hipStream_t st, hipStreamCaptureStatus* status) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    *status = st && st->captured ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t ev) {
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (g_captures) return hipErrorUnknown;
+    }
     std::unique_lock<std::mutex> lk(ev->mu);
     const uint64_t target = ev->recorded;
     ev->cv.wait(lk, [&] { return ev->done >= target; });

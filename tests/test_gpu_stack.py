@@ -404,3 +404,32 @@ def test_rewritten_weights_are_streamed_in_again(k, p, pinned, units):
     assert np.array_equal(y1.view(np.uint32), y2.view(np.uint32))
     if k == 8:
         assert copies == 1                                # only the rewritten layer crossed the link again
+
+
+def test_captured_resident_pass_replays_and_leaves_the_handle_usable():
+    """A resident stack deeper than the host's run-ahead bound, its pass captured into a graph behind eager passes: every
+    replay, with eager passes between them, and the eager passes afterwards give the same bits."""
+    c = Case(synth.Workload("captured", "decoder", 40, 128, 2, 1, 64, 256, True, 1, 24))
+    w = c.w
+    eng = sp.Engine(c.desc, c.blobs, w.n_layers, 1)
+    y, yg = torch.empty_like(c.xd), torch.empty_like(c.xd)
+    for _ in range(2):
+        eng.forward(c.xd, y, w.batch, w.seq)
+    eng.sync()
+    want = y.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=eng.compute):
+        eng.forward(c.xd, yg, w.batch, w.seq)
+    for _ in range(4):
+        yg.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(yg, want)
+        y.fill_(float("nan"))
+        for _ in range(6):
+            eng.forward(c.xd, y, w.batch, w.seq)
+        eng.sync()
+        assert torch.equal(y, want)
+    del g
+    assert eng.destroy() == sp.SP_OK
