@@ -83,6 +83,7 @@ struct Rig {
     }
 };
 
+static int g_arena_device = 0;       // the device that the arena of the next Handle is on
 struct Handle {
     sp_handle h = nullptr;
     void* arena_raw = nullptr;
@@ -98,6 +99,7 @@ struct Handle {
         arena_raw = malloc(budget + 4096);
         arena = reinterpret_cast<unsigned char*>(((uintptr_t)arena_raw + 4095) & ~(uintptr_t)4095);
         memset(arena, 0xEE, budget);
+        mock_device_register(arena, budget, g_arena_device);
         sp_config cfg;
         memset(&cfg, 0, sizeof(cfg));
         cfg.struct_size = sizeof(cfg);
@@ -117,6 +119,7 @@ struct Handle {
     }
     ~Handle() {
         if (h) sp_destroy(h);
+        mock_device_unregister(arena);
         free(arena_raw);
     }
 };
@@ -272,6 +275,58 @@ static void test_run_ahead_with_forwards_between_steps() {
     printf("ok run-ahead with forwards between steps\n");
 }
 
+// A training step waits for the gradients of the step that its thread enqueued before through another handle of the
+// device, and for nothing of other threads' or other devices' handles; a handle may be destroyed on another thread.
+static void test_steps_of_several_handles() {
+    const int B = 1, S = 8;
+    Rig ra(SP_DECODER_SWIGLU_RMS, 3, B, S), rb(SP_DECODER_SWIGLU_RMS, 3, B, S);
+    std::vector<float> y((size_t)B * S * 64), dx(y.size()), yb(y.size()), dxb(y.size());
+    float loss, lossb;
+    auto step = [&](Rig& r, Handle& H, std::vector<float>& yo, std::vector<float>& dxo, float& lo) {
+        CHECK(sp_forward_backward(H.h, r.x.data(), r.t.data(), yo.data(), &lo, dxo.data(), r.grads.data(), B, S) == SP_OK, "step: %s",
+              sp_last_error(H.h));
+    };
+    // the same thread: the second handle's step waits for the first one's gradients
+    {
+        Handle a(ra, 1, 1, SP_FLAG_TRAINING), b(rb, 1, 1, SP_FLAG_TRAINING);
+        ra.sync();
+        rb.sync();
+        mock_stream_hold(ra.d2h);
+        CHECK(blocks_until([&] { step(ra, a, y, dx, loss); step(rb, b, yb, dxb, lossb); }, [&] { mock_stream_release(ra.d2h); }),
+              "a step did not wait for the other handle's gradients");
+        ra.sync();
+        rb.sync();
+    }
+    // another thread, or another device: it does not
+    for (int other_device = 0; other_device < 2; ++other_device) {
+        Handle a(ra, 1, 1, SP_FLAG_TRAINING);
+        g_arena_device = other_device;
+        Handle b(rb, 1, 1, SP_FLAG_TRAINING);
+        g_arena_device = 0;
+        ra.sync();
+        rb.sync();
+        mock_stream_hold(ra.d2h);
+        step(ra, a, y, dx, loss);
+        const bool blocked = other_device ? (step(rb, b, yb, dxb, lossb), false)          // would never return
+                                          : blocks_until([&] { step(rb, b, yb, dxb, lossb); }, [&] { mock_stream_release(ra.d2h); });
+        CHECK(!blocked, "a step waited for another thread's handle");
+        mock_stream_release(ra.d2h);
+        ra.sync();
+        rb.sync();
+    }
+    // destroyed on another thread while this one remembers its last step
+    {
+        Handle a(ra, 1, 1, SP_FLAG_TRAINING), b(rb, 1, 1, SP_FLAG_TRAINING);
+        step(ra, a, y, dx, loss);
+        sp_handle h = a.h;
+        a.h = nullptr;
+        std::thread([&] { CHECK(sp_destroy(h) == SP_OK, "destroy"); }).join();
+        step(rb, b, yb, dxb, lossb);
+        rb.sync();
+    }
+    printf("ok steps of several handles\n");
+}
+
 // A resident stack's pass under stream capture: deeper than the run-ahead bound, behind eager passes that the bound
 // still counts; and eager passes afterwards.
 static void test_forward_under_capture() {
@@ -411,6 +466,7 @@ int main(int argc, char** argv) {
     test_training(SP_ENCODER_GELU_LN);
     test_run_ahead_with_forwards_between_steps();
     test_forward_under_capture();
+    test_steps_of_several_handles();
     test_decode();
     test_injected_failures(false);
     test_injected_failures(true);

@@ -22,7 +22,7 @@ typedef struct mockEvent* hipEvent_t;
 enum { hipEventDefault = 0, hipEventDisableTiming = 2 };
 typedef enum { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2 } hipMemcpyKind;
 typedef enum { hipMemoryTypeUnregistered = 0, hipMemoryTypeHost = 1, hipMemoryTypeDevice = 2 } hipMemoryType;
-typedef struct { hipMemoryType type; } hipPointerAttribute_t;
+typedef struct { hipMemoryType type; int device; } hipPointerAttribute_t;
 typedef enum { hipFuncAttributeMaxDynamicSharedMemorySize = 8 } hipFuncAttribute;
 
 hipError_t hipEventCreate(hipEvent_t* ev);
@@ -47,6 +47,9 @@ void mock_stream_destroy(hipStream_t st);
 // The stream executes nothing between the two calls (what it is executing it finishes first).
 void mock_stream_hold(hipStream_t st);
 void mock_stream_release(hipStream_t st);
+// memory that hipPointerGetAttributes reports as device memory of `device`
+void mock_device_register(void* p, size_t bytes, int device);
+void mock_device_unregister(void* p);
 // The stream reports that it is being captured (work still runs at once); waiting for an event from the host is then
 // an error, as it is under HIP.
 void mock_stream_capture(hipStream_t st, int on);

@@ -89,6 +89,7 @@ std::mutex g_mu;
 std::map<std::string, int> g_fail;       // api -> calls left until the failing one
 std::map<std::string, long> g_count;
 std::map<const char*, size_t> g_pinned;  // base -> bytes
+std::map<const char*, std::pair<size_t, int>> g_device_mem;  // base -> bytes, device
 mockStream* g_default = nullptr;
 int g_captures = 0;
 
@@ -182,6 +183,14 @@ hipError_t hipEventRecord(hipEvent_t ev, hipStream_t st) {
     });
     return hipSuccess;
 }
+void mock_device_register(void* p, size_t bytes, int device) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_device_mem[static_cast<const char*>(p)] = {bytes, device};
+}
+void mock_device_unregister(void* p) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_device_mem.erase(static_cast<const char*>(p));
+}
 void mock_stream_capture(hipStream_t st, int on) {
     std::lock_guard<std::mutex> lk(g_mu);
     g_captures += (on ? 1 : 0) - (st->captured ? 1 : 0);
@@ -243,6 +252,13 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p) {
     for (auto& kv : g_pinned)
         if (c >= kv.first && c < kv.first + kv.second) {
             at->type = hipMemoryTypeHost;
+            at->device = 0;
+            return hipSuccess;
+        }
+    for (auto& kv : g_device_mem)
+        if (c >= kv.first && c < kv.first + kv.second.first) {
+            at->type = hipMemoryTypeDevice;
+            at->device = kv.second.second;
             return hipSuccess;
         }
     at->type = hipMemoryTypeUnregistered;
