@@ -90,12 +90,12 @@ struct Handle {
     unsigned char* arena = nullptr;
     uint64_t budget = 0;
     int rc = SP_OK;
-    Handle(Rig& r, int k, int p, uint32_t flags, int budget_layers = 0, int pinned = 0, int units = 0, int frozen = 0) {
+    Handle(Rig& r, int k, int p, uint32_t flags, int budget_layers = 0, int pinned = 0, int units = 0, int frozen = 0, size_t extra = 0) {
         const int mode = (flags & SP_FLAG_TRAINING) ? ((flags & SP_FLAG_KEEP_ACTIVATIONS) ? 2 : 1) : 0;
         const uint64_t slot = (r.blob_bytes + 4095) / 4096 * 4096;
         int nl = budget_layers ? budget_layers : k + p + (pinned > 0 ? pinned : 0);
         if (nl > r.L) nl = r.L;
-        budget = sp_workspace_bytes(&r.desc, mode) + (uint64_t)nl * slot;
+        budget = sp_workspace_bytes(&r.desc, mode) + (uint64_t)nl * slot + extra;
         arena_raw = malloc(budget + 4096);
         arena = reinterpret_cast<unsigned char*>(((uintptr_t)arena_raw + 4095) & ~(uintptr_t)4095);
         memset(arena, 0xEE, budget);
@@ -349,9 +349,22 @@ static void test_decode() {
     const int B = 2, S0 = 6, steps = 4, max_len = 16;
     Rig r(SP_DECODER_SWIGLU_RMS, 4, B, S0);
     std::vector<std::vector<float>> outs;
-    for (int variant = 0; variant < 3; ++variant) {
-        Handle H(r, variant == 0 ? 8 : 1, variant == 0 ? 8 : 1, variant == 2 ? (SP_FLAG_WRAP_PREFETCH | SP_FLAG_POISON) : 0, 0,
-                 variant == 2 ? 1 : 0);
+    std::vector<std::vector<unsigned char>> caches;
+    // resident, one layer ahead, wrapped with a pinned layer, in units; with and without room for partial results
+    struct { int k, p; uint32_t flags; int pinned, units; bool scratch; } cases[] = {
+        {8, 8, 0, 0, 0, true}, {8, 8, 0, 0, 0, false}, {1, 1, 0, 0, 0, true}, {1, 1, SP_FLAG_WRAP_PREFETCH | SP_FLAG_POISON, 1, 0, true},
+        {1, 1, SP_FLAG_DELAY | SP_FLAG_POISON, 0, 3, true}, {2, 1, SP_FLAG_WRAP_PREFETCH, 0, 3, false}};
+    CHECK(sp_decode_scratch_bytes(&r.desc) > 0, "the rig's workspace holds the partial results");
+    for (auto& c : cases) {
+        Handle H(r, c.k, c.p, c.flags, 0, c.pinned, c.units, 0, c.scratch ? sp_decode_scratch_bytes(&r.desc) : 0);
+        CHECK(H.rc == SP_OK, "sp_create: %s", sp_last_error(nullptr));
+        if (H.rc != SP_OK) return;
+        sp_stats st;
+        st.struct_size = sizeof(st);
+        CHECK(sp_get_stats(H.h, &st) == SP_OK, "stats");
+        const uint64_t ring = (uint64_t)(st.plan.n_slots - st.plan.n_pinned) * st.plan.slot_bytes;
+        CHECK((st.plan.arena_bytes_used > st.plan.workspace_bytes + st.plan.pinned_bytes + ring) == c.scratch && st.plan.arena_bytes_used <= H.budget,
+              "scratch in the plan");
         const size_t cb = sp_kv_cache_bytes(&r.desc, B, max_len);
         std::vector<unsigned char> cache(cb, 0xFF);
         std::vector<float> y((size_t)B * S0 * 64), y1((size_t)B * 64), all;
@@ -365,8 +378,26 @@ static void test_decode() {
         }
         CHECK(sp_decode(H.h, r.x.data(), y1.data(), cache.data(), B, max_len, max_len) == SP_ERR_SHAPE, "pos beyond the cache");
         outs.push_back(all);
+        caches.push_back(cache);
+        CHECK(same(outs[0], all), "decode outputs differ between windows (%d,%d) units %d", c.k, c.p, c.units);
+        CHECK(caches[0] == cache, "the cache differs between windows (%d,%d) units %d", c.k, c.p, c.units);
     }
-    CHECK(same(outs[0], outs[1]) && same(outs[0], outs[2]), "decode outputs differ between windows");
+    // positions past the last one are untouched, the others written
+    const size_t layer = caches[0].size() / r.L, head = (size_t)64 * max_len * 2;
+    for (int l = 0; l < r.L; ++l)
+        for (int bh = 0; bh < B; ++bh) {
+            const unsigned char* k = caches[0].data() + l * layer + bh * head;
+            const unsigned char* v = k + layer / 2;
+            for (int e = 0; e < 64; ++e)
+                for (int t = S0 + steps; t < max_len; ++t) {
+                    CHECK(k[(e * max_len + t) * 2] == 0xFF && k[(e * max_len + t) * 2 + 1] == 0xFF, "key past the end written");
+                    CHECK(v[(t * 64 + e) * 2] == 0xFF && v[(t * 64 + e) * 2 + 1] == 0xFF, "value past the end written");
+                }
+            int blank = 0;
+            for (int t = 0; t < S0 + steps; ++t)
+                for (int e = 0; e < 64; ++e) blank += (k[(e * max_len + t) * 2] == 0xFF) + (v[(t * 64 + e) * 2] == 0xFF);
+            CHECK(blank < 64, "layer %d: %d bytes of the cached positions look unwritten", l, blank);
+        }
     printf("ok decode\n");
 }
 

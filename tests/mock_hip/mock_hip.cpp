@@ -323,8 +323,6 @@ hipError_t spk_launch_gemm(hipStream_t st, int epi, const GemmArgs& g) {
     for (int m = 0; m < g.M; ++m) out.push_back({static_cast<char*>(g.C) + (size_t)m * g.ldc * csz, (size_t)g.N * csz});
     return launch(st, 1, in, out);
 }
-hipError_t spk_launch_gemm_skinny(hipStream_t st, int epi, const GemmArgs& g) { return spk_launch_gemm(st, epi, g); }
-GemmPlan spk_gemm_plan_host(int, int, int, int M, int) { return GemmPlan{1, M, 0}; }
 
 hipError_t spk_launch_norm(hipStream_t st, const float* h, const bf16_t* gain, const bf16_t* bias, bf16_t* out, int T,
                            int d, float) {
@@ -336,7 +334,27 @@ hipError_t spk_launch_norm(hipStream_t st, const float* h, const bf16_t* gain, c
 hipError_t spk_launch_swiglu(hipStream_t st, const bf16_t* gu, bf16_t* z, int T, int f) {
     return launch(st, 3, {{gu, (size_t)T * 2 * f * 2}}, {{z, (size_t)T * f * 2}});
 }
+// A decode step: reads the query and the cached positions [0, pos), writes the output, position pos of the cache and
+// the scratch.
+static hipError_t decode_step(hipStream_t st, const bf16_t* qkv, bf16_t* o, const AttnShape& a) {
+    if (a.S != 1 || a.pos < 0 || a.pos >= a.max_len) return hipErrorInvalidValue;
+    std::vector<Span> in = {{qkv, (size_t)a.B * a.ld_qkv * 2}};
+    std::vector<MSpan> out = {{o, (size_t)a.B * a.Hq * a.hd * 2}};
+    for (size_t bh = 0; bh < (size_t)a.B * a.Hkv; ++bh) {
+        for (int e = 0; e < a.hd; ++e) {
+            bf16_t* row = a.kt + (bh * a.hd + e) * a.max_len;
+            in.push_back({row, (size_t)a.pos * 2});
+            out.push_back({row + a.pos, 2});
+        }
+        bf16_t* rows = a.v + bh * a.max_len * a.hd;
+        in.push_back({rows, (size_t)a.pos * a.hd * 2});
+        out.push_back({rows + (size_t)a.pos * a.hd, (size_t)a.hd * 2});
+    }
+    if (a.part) out.push_back({a.part, decode_scratch_floats(a.Hq, a.Hkv, a.hd) * 4});
+    return launch(st, 6, in, out);
+}
 hipError_t spk_launch_attention(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, const AttnShape& a) {
+    if (a.kt) return decode_step(st, qkv, o, a);
     const size_t T = (size_t)a.B * a.S;
     std::vector<MSpan> out = {{o, T * a.Hq * a.hd * 2}};
     if (lse) out.push_back({lse, T * a.Hq * 4});
@@ -353,16 +371,6 @@ hipError_t spk_launch_kv_append(hipStream_t st, const bf16_t* qkv, int ld_qkv, b
             out.push_back({v + (((size_t)b * Hkv + h) * max_len + pos0) * hd, (size_t)S * hd * 2});
         }
     return launch(st, 5, {{qkv, (size_t)B * S * ld_qkv * 2}}, out);
-}
-hipError_t spk_launch_decode_attention(hipStream_t st, const bf16_t* qkv, int ld_qkv, const bf16_t* kt, const bf16_t* v,
-                                       bf16_t* o, int ld_o, int B, int n, int max_len, int, int Hkv, int hd) {
-    std::vector<Span> in = {{qkv, (size_t)B * ld_qkv * 2}};
-    for (int b = 0; b < B; ++b)
-        for (int h = 0; h < Hkv; ++h) {
-            for (int e = 0; e < hd; ++e) in.push_back({kt + (((size_t)b * Hkv + h) * hd + e) * max_len, (size_t)n * 2});
-            in.push_back({v + ((size_t)b * Hkv + h) * max_len * hd, (size_t)n * hd * 2});
-        }
-    return launch(st, 6, in, {{o, (size_t)B * ld_o * 2}});
 }
 hipError_t spk_launch_copy_f32(hipStream_t st, const float* src, float* dst, size_t n) {
     if (n == 0 || src == dst) return hipSuccess;
