@@ -40,15 +40,15 @@ struct Rig {
     hipStream_t compute, h2d, d2h;
     std::vector<float> x, t;
 
-    Rig(int arch, int n_layers, int B, int S) {
+    Rig(int arch, int n_layers, int B, int S, int heads = 2, int kv_heads = 1, int ffn = 128) {
         memset(&desc, 0, sizeof(desc));
         desc.struct_size = sizeof(desc);
         desc.n_layers = L = n_layers;
-        desc.d_model = 64;
-        desc.n_q_heads = 2;
-        desc.n_kv_heads = 1;
+        desc.d_model = heads == 2 ? 64 : heads * 64;
+        desc.n_q_heads = heads;
+        desc.n_kv_heads = kv_heads;
         desc.head_dim = 64;
-        desc.d_ffn = 128;
+        desc.d_ffn = ffn;
         desc.arch = arch;
         desc.causal = arch == SP_DECODER_SWIGLU_RMS;
         desc.norm_eps = 1e-5f;
@@ -65,7 +65,7 @@ struct Rig {
         compute = mock_stream_create();
         h2d = mock_stream_create();
         d2h = mock_stream_create();
-        x.resize((size_t)B * S * 64);
+        x.resize((size_t)B * S * desc.d_model);
         t.resize(x.size());
         for (size_t i = 0; i < x.size(); ++i) { x[i] = (float)(i % 97) * 0.01f; t[i] = (float)(i % 89) * 0.02f; }
     }
@@ -192,7 +192,7 @@ static StepOut train(Rig& r, int k, int p, uint32_t flags, int B, int S, int cal
     Handle H(r, k, p, SP_FLAG_TRAINING | flags, budget_layers, pinned, 0, frozen);
     CHECK(H.rc == SP_OK, "sp_create(training): %s", sp_last_error(nullptr));
     if (H.rc != SP_OK) return o;
-    o.y.assign((size_t)B * S * 64, -1.f);
+    o.y.assign((size_t)B * S * r.desc.d_model, -1.f);
     o.dx.assign(o.y.size(), -1.f);
     for (int c = 0; c < calls; ++c) {
         for (void* g : r.grads) memset(g, 0xFF, r.grad_bytes);
@@ -236,6 +236,19 @@ static void test_training(int arch) {
         free(pageable);
     }
     printf("ok training arch %d\n", arch);
+}
+
+// Layers of more than 16 MB of gradients, sent in three parts as they are complete: the bytes do not depend on the
+// window, on kept activations or on how the streams drift, and arrive whole (the slots are reused by later layers).
+static void test_large_gradients(int arch) {
+    const int B = 1, S = 2;
+    Rig r(arch, 6, B, S, 12, 12, arch == SP_DECODER_SWIGLU_RMS ? 1024 : 1536);
+    CHECK(r.grad_bytes > (size_t)16 << 20, "gradients of %zu bytes are sent whole", r.grad_bytes);
+    mock_count_reset();
+    const StepOut base = train(r, 8, 8, 0, B, S, 1);
+    CHECK(mock_count("hipMemcpyAsync") == r.L + 3 * r.L, "%ld copies", mock_count("hipMemcpyAsync"));
+    CHECK(train(r, 1, 1, SP_FLAG_DELAY | SP_FLAG_POISON | SP_FLAG_KEEP_ACTIVATIONS, B, S, 1) == base, "streamed, kept and delayed differs");
+    printf("ok large gradients arch %d\n", arch);
 }
 
 // Whether `call`, run on a thread of its own, is still inside after a while; `then` lets it end.
@@ -495,6 +508,8 @@ int main(int argc, char** argv) {
     test_forward_windows(SP_ENCODER_GELU_LN);
     test_training(SP_DECODER_SWIGLU_RMS);
     test_training(SP_ENCODER_GELU_LN);
+    test_large_gradients(SP_DECODER_SWIGLU_RMS);
+    test_large_gradients(SP_ENCODER_GELU_LN);
     test_run_ahead_with_forwards_between_steps();
     test_forward_under_capture();
     test_steps_of_several_handles();
