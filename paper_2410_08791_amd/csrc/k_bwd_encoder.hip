@@ -145,8 +145,8 @@ __global__ __launch_bounds__(TH) void colsum_bf16_kernel(const bf16_t* __restric
     }
 }
 
-// The same with 16-byte loads: a work-group adds rows b, b+8, ... of its row range for 256 columns, eight rows
-// side by side (32 lanes of 8 columns each), four loads in flight per lane, the eight sums of a column added
+// The same with 16-byte loads: work-group (c, b) adds the rows 8 b .. 8 b + 7 of every 8 x gridDim.y rows for its 256
+// columns, eight rows side by side (32 lanes of 8 columns each), four loads in flight per lane, the eight sums of a column added
 // in a fixed order.  HBM-bound; the form above walks all columns of a row with 4-byte loads, each waited for
 // in turn: 8224 x 5120 in 600 us.
 constexpr int CS_COLS = 256, CS_ROWS = 8;

@@ -38,12 +38,10 @@ struct SmallCfg {
     static constexpr int NBLK = STAGE / 1024;          // 1 KiB load instructions per k-tile and group
     static constexpr int NI = (NBLK + GW - 1) / GW;    // per wave (the last may repeat a block)
     static constexpr int CSTR = BN + 4;                // floats per row of a partial tile
-    // partial tiles that meet in LDS at once: all groups', or (too large) the upper half's first
-    static constexpr int RG = KG * BM * CSTR * 4 <= 160 * 1024 ? KG : KG / 2;
-    static constexpr int LDS_LOOP = KG * NST * STAGE, LDS_EPI = RG * BM * CSTR * 4;
+    static constexpr int LDS_LOOP = KG * NST * STAGE, LDS_EPI = KG * BM * CSTR * 4;     // stages; all groups' partial tiles
     static constexpr int LDS = LDS_LOOP > LDS_EPI ? LDS_LOOP : LDS_EPI;
     static_assert(!ROW16 || GW == 1);
-    static_assert(NI * (NST - 1) < 63 && (RG == KG || KG % 2 == 0) && LDS <= 160 * 1024 && THREADS <= 1024, "fits the counters, the LDS and a work-group");
+    static_assert(NI * (NST - 1) < 63 && LDS <= 160 * 1024 && THREADS <= 1024, "fits the counters, the LDS and a work-group");
 };
 
 // NACC: accumulator sets, taken in turn by a k-tile's steps and added at the end.  Two with four contraction groups,
@@ -232,34 +230,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
     sp_lds_barrier();     // every load has been waited for, every fragment read is done: the LDS is free
 
     float* red = reinterpret_cast<float*>(smem);
-    if constexpr (C::RG < C::KG) {
-        // the upper half of the groups hands its accumulators to the lower half, as they lie in the lanes
-        float4* x = reinterpret_cast<float4*>(smem) + (size_t)((grp % C::RG) * C::GW + gw) * (TM * TN * (ACC / 4) * 64) + lane;
-        if (grp >= C::RG) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < ACC / 4; ++g)
-                        x[((i * TN + j) * (ACC / 4) + g) * 64] = make_float4(acc[j][i][g * 4], acc[j][i][g * 4 + 1], acc[j][i][g * 4 + 2], acc[j][i][g * 4 + 3]);
-        }
-        sp_lds_barrier();
-        if (grp < C::RG) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < ACC / 4; ++g) {
-                        const float4 o = x[((i * TN + j) * (ACC / 4) + g) * 64];
-                        acc[j][i][g * 4] += o.x; acc[j][i][g * 4 + 1] += o.y; acc[j][i][g * 4 + 2] += o.z; acc[j][i][g * 4 + 3] += o.w;
-                    }
-        }
-        sp_lds_barrier();
-    }
-    // partial tiles, one per (remaining) group: rows of BN + 4 floats
-    if (grp < C::RG)
+    // partial tiles, one per group: rows of BN + 4 floats
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -285,7 +256,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_small_kernel(GemmDev p) {
         if (!SWIGLU && p.bias) b = *reinterpret_cast<const uint2*>(p.bias + n);
         float v[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int g = 0; g < C::RG; ++g) {
+        for (int g = 0; g < C::KG; ++g) {
             const float* row = red + (g * BM + r) * C::CSTR + c;
             const float4 a = *reinterpret_cast<const float4*>(row);
             v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;

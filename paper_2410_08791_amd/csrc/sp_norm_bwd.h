@@ -1,7 +1,7 @@
 // Norm backward over many rows, RMSNorm and LayerNorm: a row is held by WPR waves (1, 2, 4: rows of at most
 // 2048, 4096, 8192 elements; a lane keeps at most eight float4 of da, h and dh), a work-group of eight waves
-// has 8 / WPR rows in flight and walks rows with the grid.  HBM-bound: 14 bytes in and out per element of da,
-// h and dh.  With one row per work-group the loads of a row were waited for before the next row's were issued
+// has 8 / WPR rows in flight and walks rows with the grid.  HBM-bound: 18 bytes per element (da, h and dh in,
+// dh and its bf16 copy out).  With one row per work-group the loads of a row were waited for before the next row's were issued
 // and four to six barriers separated the rows: LayerNorm 8224 x 1280 123 us, RMSNorm 16384 x 4096 409 us.
 //
 // RMSNorm   a = h r g, r = rsqrt(mean(h^2) + eps):

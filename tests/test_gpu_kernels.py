@@ -85,7 +85,7 @@ def test_gemm_kmajor(epi, M, N, K, tile):
 @pytest.mark.parametrize("epi", [sp.EPI_BF16, sp.EPI_RESID_F32, sp.EPI_GELU_BF16, sp.EPI_SWIGLU_BF16, sp.EPI_F32])
 def test_gemm_few_rows_streams_the_weights(epi, M, N, K, tile):
     """At most 64 activation rows (a decode step, the ragged last rows of a long launch): the
-    weight-streaming kernel, forced (tile 9; 11-13 with 16, 32, 64 rows per work-group, the rest of
+    small-tile kernel with its few-row tiles, forced (tile 9; 11-13 with 16, 32, 64 rows per work-group, the rest of
     the rows in further work-groups) and as the heuristic's choice; N not a multiple of the
     16 columns of a work-group nor of the 8 column blocks of a dispatch group, K / 32 not a multiple of the eight waves that share the
     contraction, M at and next to the limits of its one, two and four 16-row tiles."""
