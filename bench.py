@@ -73,20 +73,20 @@ def op_work(w, training):
     f1 = 2 * f if dec else f
     attn = 4.0 * w.batch * w.n_q_heads * w.seq * w.seq * w.head_dim * (0.5 if w.causal else 1.0)
     mats = d * nqkv + nq * d + d * f1 + f * d                 # matrix elements of a layer
-    fwd_passes = 2 if training else 1                         # the backward recomputes the layer
+    n_fwd = 2 * L - 1 if training else L                      # the backward recomputes every layer but the last
     out = {
-        "norm": ("hbm", fwd_passes * L * 2 * T * 6.0 * d),
-        "gemm_qkv": ("mfma", fwd_passes * L * 2.0 * T * nqkv * d),
-        "attention": ("mfma", fwd_passes * L * attn),
-        "gemm_o": ("mfma", fwd_passes * L * 2.0 * T * d * nq),
-        "gemm_ffn1": ("mfma", fwd_passes * L * 2.0 * T * d * f1),
+        "norm": ("hbm", n_fwd * 2 * T * 6.0 * d),
+        "gemm_qkv": ("mfma", n_fwd * 2.0 * T * nqkv * d),
+        "attention": ("mfma", n_fwd * attn),
+        "gemm_o": ("mfma", n_fwd * 2.0 * T * d * nq),
+        "gemm_ffn1": ("mfma", n_fwd * 2.0 * T * d * f1),
         # forward pass only: the recompute stops before the last projection
         "gemm_ffn2": ("mfma", L * 2.0 * T * f * d),
         "copy": ("hbm", 8.0 * T * d * (2 if training else 1)),
     }
     if training:
         out.update({
-            "act": ("hbm", fwd_passes * L * T * f * (6.0 if dec else 4.0)),
+            "act": ("hbm", n_fwd * T * f * (6.0 if dec else 4.0)),
             "loss": ("hbm", 14.0 * T * d),
             "gemm_dw": ("mfma", L * 2.0 * T * mats),
             "gemm_dx": ("mfma", L * 2.0 * T * mats),

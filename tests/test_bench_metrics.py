@@ -3,6 +3,7 @@ synthetic two-stream schedules (no GPU)."""
 import numpy as np
 
 import bench
+from paper_2410_08791_amd import synth
 
 
 def simulate(copy_ms, comp_ms, n_slots, rng=None):
@@ -52,3 +53,12 @@ def test_bounds_hold_on_random_schedules():
 def test_empty_trace_gives_no_figures():
     m = bench.overlap_metrics(0.0, 0.0, 0.0, 0.0)
     assert all(v is None for v in m.values())
+
+
+def test_op_work_counts_the_layers_that_run():
+    # a training step recomputes every layer but the last, and no layer's second FFN projection
+    w = synth.WORKLOADS["train1p3b"]
+    fwd, step = bench.op_work(w, False), bench.op_work(w, True)
+    for name in ("norm", "gemm_qkv", "attention", "gemm_o", "gemm_ffn1"):
+        assert step[name][1] * w.n_layers == fwd[name][1] * (2 * w.n_layers - 1)
+    assert step["gemm_ffn2"] == fwd["gemm_ffn2"]
