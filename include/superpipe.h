@@ -27,7 +27,8 @@
  *    compute stream, the next layer's enqueue waits until about 200 (350) are
  *    left (every call kind; a deep stack reaches the bound inside one call;
  *    beyond about 1500 this HIP runtime was measured to run whole passes 30-60 %
- *    slower); (2) sp_forward_backward waits at entry for the last gradient of the
+ *    slower; a pass under stream capture is neither counted nor waited for);
+ *    (2) sp_forward_backward waits at entry for the last gradient of the
  *    previous step, its own and that of any other handle of the device that the
  *    same host thread called (gradient copies submitted while others execute run
  *    at a fraction of the link rate); (3) sp_wait_gradient, sp_get_stats with a
