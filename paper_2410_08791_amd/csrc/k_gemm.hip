@@ -2,16 +2,15 @@
 // accumulate, used for every dense projection of a layer (QKV, O, gate/up,
 // down) and for the backward contractions.
 //
-// Work-group = 4 or 8 waves in a 2 x (waves/2) grid; block tile BM x BN x 64,
-// each wave owns its share as 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16).
-// Both operand tiles are staged in LDS with the contraction index contiguous
+// Block tile BM x BN x 64.  Both operand tiles are staged in LDS with the contraction index contiguous
 // (128-byte rows, 16-byte chunks XOR-swizzled so that both the 16-byte stores
-// and the per-lane 16-byte fragment loads spread over all banks), double
-// buffered.  Two kernels build that LDS image: gemm_dma_kernel (global loads
-// that write LDS directly; every projection, forward and backward) and gemm_kernel
+// and the per-lane 16-byte fragment loads spread over all banks), more than one k-tile
+// deep.  Two kernels build that LDS image: gemm_dma_kernel (global loads
+// that write LDS directly; every projection, forward and backward; v_mfma_f32_16x16x32_bf16) and gemm_kernel
 // (register staging: global loads for tile t+1 are issued before the MFMAs of tile t
 // and stored to the other buffer afterwards, one barrier per tile; takes the outputs
-// whose rows do not start on 16 bytes, which the other kernel's epilogue cannot write).
+// whose rows do not start on 16 bytes, which the other kernel's epilogue cannot write; 4 or 8 waves in a 2 x (waves/2)
+// grid, each with its share as 32x32 tiles of v_mfma_f32_32x32x16_bf16).
 //
 // The MFMA is issued "transposed" (weights as the A operand, activations as B)
 // so that a lane's four consecutive accumulator registers are four consecutive
@@ -123,7 +122,7 @@ struct LoaderSel { typedef LoaderK<ROWS, NT> type; };
 template <int ROWS, int NT>
 struct LoaderSel<ROWS, NT, OP_RMAJOR> { typedef LoaderR<ROWS, NT> type; };
 
-// Epilogue shared by the GEMM kernels.  acc[j][i] is the 32x32 tile (n tile j, m tile i) of
+// Epilogue of the register-staged kernel.  acc[j][i] is the 32x32 tile (n tile j, m tile i) of
 // a wave whose first row is m_base and first output column n_base; a lane holds row l32 of
 // the m tile and, in register e, column j*32 + (e/4)*8 + half*4 + e%4.
 template <int EPI, int TM, int TN>
@@ -344,11 +343,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_kernel(GemmDev p) {
 // are first laid out in LDS as the output tile, RP rows at a time (row stride + 16 bytes: a
 // wave's 32 rows spread over the banks), and then written with 16 bytes per lane, consecutive
 // lanes on consecutive bytes of a row: whole 128-byte lines.  The residual is read the same way.
-// acc[j][i]: tile (n tile j, m tile i) of a wave whose first tile row is wrow0 and first output
-// column inside the tile wcol0; lane layout as in gemm_epilogue.
+// acc[j][i]: 16x16 tile (n tile j, m tile i) of a wave whose first tile row is wrow0 and first output
+// column inside the tile wcol0; a lane holds row lane & 15 and the four columns 4 (lane >> 4) ..
 template <int EPI, int TM, int TN, int BM, int BN_OUT, int NT, int LDS_BYTES>
-__device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t (&acc)[TN][TM], unsigned char* smem,
-                                                     int m0, int n0, int wrow0, int wcol0, int l32, int half) {
+__device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x4_t (&acc)[TN][TM], unsigned char* smem,
+                                                     int m0, int n0, int wrow0, int wcol0, int lane) {
     constexpr bool SWIGLU = (EPI == EPI_SWIGLU_BF16);
     constexpr bool F32OUT = (EPI == EPI_RESID_F32 || EPI == EPI_F32);
     constexpr int ESZ = F32OUT ? 4 : 2;
@@ -361,15 +360,16 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
     constexpr int TNO = SWIGLU ? TN / 2 : TN;
     constexpr int CPR = ROWB / 16, CHUNKS = RP * CPR;     // 16-byte chunks per row / per pass
     // the values of 4 consecutive columns (register group g of tile (j, i))
-    auto values = [&](int i, int j, int g, float (&v)[4]) {
-        const int nl = wcol0 + j * 32 + g * 8 + half * 4;
+    const int l16 = lane & 15, quarter = lane >> 4;
+    auto values = [&](int i, int j, float (&v)[4]) {
+        const int nl = wcol0 + j * 16 + quarter * 4;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if (SWIGLU) {
-                const float gv = acc[j][i][g * 4 + e], uv = acc[j + TN / 2][i][g * 4 + e];
+                const float gv = acc[j][i][e], uv = acc[j + TN / 2][i][e];
                 v[e] = gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv)) * uv;
             } else {
-                v[e] = acc[j][i][g * 4 + e];
+                v[e] = acc[j][i][e];
             }
         }
         if (!SWIGLU && p.bias) {
@@ -404,18 +404,16 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
     }
     // bf16 outputs: every wave computes and packs all of its values first (the activation
     // functions are the expensive part and must not be serialised by the passes below)
-    uint2 pk[F32OUT ? 1 : TM][F32OUT ? 1 : TNO][4];
+    uint2 pk[F32OUT ? 1 : TM][F32OUT ? 1 : TNO];
     if (!F32OUT) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TNO; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float v[4];
-                    values(i, j, g, v);
-                    pk[F32OUT ? 0 : i][F32OUT ? 0 : j][g] = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
-                }
+            for (int j = 0; j < TNO; ++j) {
+                float v[4];
+                values(i, j, v);
+                pk[F32OUT ? 0 : i][F32OUT ? 0 : j] = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+            }
     }
     // A thread's residual loads of a pass are all issued before the first is used (one after the
     // other, each waited for, they cost a memory round trip per 16 bytes), the first batch before
@@ -445,22 +443,20 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
         if (pass) lds_barrier();     // the previous pass has been read out
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int r = wrow0 + i * 32;                 // wave-uniform
+            const int r = wrow0 + i * 16;                 // wave-uniform
             if (r / RP != pass) continue;
-            unsigned char* rowp = smem + (r - pass * RP + l32) * STRIDE;
+            unsigned char* rowp = smem + (r - pass * RP + l16) * STRIDE;
 #pragma unroll
-            for (int j = 0; j < TNO; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int nl = wcol0 + j * 32 + g * 8 + half * 4;
-                    if (F32OUT) {
-                        float v[4];
-                        values(i, j, g, v);
-                        *reinterpret_cast<float4*>(rowp + nl * 4) = make_float4(v[0], v[1], v[2], v[3]);
-                    } else {
-                        *reinterpret_cast<uint2*>(rowp + nl * 2) = pk[F32OUT ? 0 : i][F32OUT ? 0 : j][g];
-                    }
+            for (int j = 0; j < TNO; ++j) {
+                const int nl = wcol0 + j * 16 + quarter * 4;
+                if (F32OUT) {
+                    float v[4];
+                    values(i, j, v);
+                    *reinterpret_cast<float4*>(rowp + nl * 4) = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+                    *reinterpret_cast<uint2*>(rowp + nl * 2) = pk[F32OUT ? 0 : i][F32OUT ? 0 : j];
                 }
+            }
         }
         lds_barrier();
 #pragma unroll
@@ -493,49 +489,61 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmDev& p, f32x16_t 
 // operand gets the LDS image the register-staged kernel builds, a row-contiguous one lies as in memory
 // (LDS row = contraction index) and is read with the transposing LDS read.
 //
-// Backward forms on this kernel against the register-staged one (256x256 tiles, random operands, us):
-//   dX 16384 x 11008 x 4096, 16384 x 4096 x 22016, 8192 x 2048 x 6144   1462 / 2702 / 187 -> 1237 / 2408 / 175
-//   dW 22016 x 4096 x 16384, 4096 x 4096 x 16384, 6144 x 2048 x 8192    2802 / 481 / 213 -> 2563 / 436 / 195
-// bit for bit the same sums.  What bounds both is the matrix pipe at the clock that random operands
-// allow (1.15-1.25 PFLOP/s); the stores to LDS were the rest.
+// What bounds it is the power of the matrix pipes on operands that toggle (the clock falls to 1.8-2.0 GHz) and what
+// keeps them from issuing.  Three things about the loop follow from that, us on random operands (before -> after all
+// three; 8192^3 780 with two stages and the compiler's order on zeros, 998 on random operands):
+//   8192 x 8192 x 8192 998 -> 755      2048 x 22016 x 4096 336 -> 289     4096 x 10240 x 8192 514 -> 462
+//   2048 x 12288 x 4096 196 -> 162     16384 x 1280 x 5120 175 -> 164     16384 x 3840 x 1280 158 -> 141
+//   dW 22016 x 4096 x 16384 2640 -> 2400   dX 16384 x 4096 x 22016 2419 -> 2149   dX 16384 x 11008 x 4096 1234 -> 1073
+// * v_mfma_f32_16x16x32 instead of 32x32x16.  Both take 1024 flop per cycle and SIMD, but an instruction of the former
+//   goes 32 deep, so each accumulator is read and written half as often: MFMAs alone on N(0,1) x N(0,0.02)
+//   operands run at 2.05 PFLOP/s against 1.64-1.8 (on zeros both at 2.45).
+// * Loads that miss the L2 take more than a k-tile's 1.0-1.4 us under load, and two stages leave a load one k-tile at
+//   most.  RING5: five slots of one operand's tile, i.e. two k-tiles and ONE operand of the k-tile after; which one
+//   alternates over the output's tiles like the colours of a chess board.  Every row of A (of W) is used by
+//   neighbouring work-groups of both colours at the same time, so half of its users fetch it two k-tiles ahead and the
+//   others, one k-tile ahead, find it in the L2.  (8192^3 with the compiler's order 986 -> 868; the 256x320
+//   tile has no room for a fifth slot.)  The 128x256 tile has three whole stages: 2048 x 4096 x 11008 229 -> 183.
+// * The order of MFMAs, fragment reads and loads is fixed by hand (sched_barrier after every MFMA).  With scheduling
+//   hints the compiler read fragments just before their use, and it waits for ALL reads in flight
+//   (s_waitcnt lgkmcnt(0)) once LDS-DMA loads are about: five such waits per k-tile, each right behind a read.
 //
-// NST 64-deep stages: two, where more do not fit, three for the 128x256 tile, whose 1024 MFMA cycles per k-tile
-// are too few for a load that misses the L2 to come back under one tile (cold operands, two -> three stages, us:
-// 2048 x 4096 x 11008 229 -> 183, dW 1280 x 5120 x 8256 160 -> 125, dW 2048 x 2048 x 8192 144 -> 104).  The only barrier of a tile sits before its LAST k-step: by then a wave
-// has read all its fragments of the tile (the last step's are in registers) and its loads of the
-// next tile, issued NST - 1 tiles earlier, have landed, so after the barrier the next stage is
-// readable and this stage is free.  The last step then runs with the first fragments of the
+// The only barrier of a tile sits before its LAST part: by then a wave
+// has read all its fragments of the tile (the last part's are in registers) and its loads of the
+// next tile have landed, so after the barrier the next tile is
+// readable and this one's slots are free.  The last part then runs with the first fragments of the
 // next tile being read under its MFMAs: nothing that follows the barrier waits on memory.
-// The loads of a tile are spread over three k-steps (after a barrier, then steps 0 and 1 of
-// the tile after it): issued in one burst they fill the address unit's queue and stall the
-// wave's MFMAs behind them (253 -> 231 us on the gate/up shape with zero operands).
+// The loads of a tile are spread over three parts: issued in one burst they fill the address unit's queue and stall
+// the wave's MFMAs behind them (253 -> 231 us on the gate/up shape with zero operands).
 // The compiler does not order these loads against later LDS reads; the kernel waits with
 // explicit vmcnt/lgkmcnt counts and uses a bare s_barrier (the fence of __syncthreads() is
 // what the counts replace).
+// (Four waves of 128x128 instead of eight of 128x64, a third less LDS traffic: 5-10 % slower, one wave per SIMD
+// hides nothing.)
 
 template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM, int NST>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kernel(GemmDev p) {
-    typedef OpTile<BM, AFORM> TA;
-    typedef OpTile<BN, WFORM> TW;
+    typedef OpTile16<BM, AFORM> TA;
+    typedef OpTile16<BN, WFORM> TW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int WNC = WAVES / WM;              // wave grid: WM (m) x WNC (n)
     constexpr int WMR = BM / WM, WN = BN / WNC;  // tile rows of A / of W per wave
-    constexpr int TM = WMR / 32, TN = WN / 32;   // 32x32 tiles per wave
-    static_assert(WMR % 32 == 0 && WN % 32 == 0, "whole MFMA tiles per wave");
+    constexpr int TM = WMR / 16, TN = WN / 16;   // 16x16 tiles per wave
+    static_assert(WMR % 32 == 0 && WN % 32 == 0, "whole halves of MFMA tiles per wave");
     constexpr int A_BYTES = BM * ROW_BYTES, STAGE = (BM + BN) * ROW_BYTES;
     constexpr bool SWIGLU = (EPI == EPI_SWIGLU_BF16);
     constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
-    constexpr int NBLK_A = BM / 8, NBLK = (BM + BN) / 8;   // 1 KiB load blocks (8 tile rows each)
-    constexpr int NI = NBLK / WAVES;           // load instructions per wave and stage
-    constexpr int N_AFTER = (3 * NI + 7) / 8;  // of those: issued right after the barrier,
-    constexpr int N_STEP0 = N_AFTER < NI - N_AFTER ? N_AFTER : NI - N_AFTER;   // in step 0 (rest: step 1)
-    static_assert(NBLK % WAVES == 0, "whole load blocks per wave");
+    // 1 KiB load blocks (8 tile rows each) per wave and tile, A's and W's
+    constexpr int NA = BM / 8 / WAVES, NW = BN / 8 / WAVES, NI = NA + NW;
+    static_assert(BM / 8 % WAVES == 0 && BN / 8 % WAVES == 0, "whole load blocks per wave");
     static_assert(!SWIGLU || (TN % 2 == 0), "gate and up tiles pair up inside a wave");
+    constexpr bool RING5 = NST == 5;
+    constexpr int SLOT = RING5 ? (BM > BN ? BM : BN) * ROW_BYTES : STAGE;
+    constexpr int LDS_BYTES = NST * SLOT;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    const int l32 = lane & 31, half = lane >> 5;
 
     int pid = xcd_remap(blockIdx.x, gridDim.x);
     constexpr int GM = 8;
@@ -546,163 +554,213 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void gemm_dma_kerne
     const int tn = (pid % group) / gm;
     const int m0 = tm * BM, n0 = tn * BN_OUT;
 
-    // load assignment: block b of 1 KiB, b < BM/8 -> the A tile, else the W tile.  Lane l lands at
-    // its 16 bytes l of the block and fetches the piece that the swizzle puts there.
-    const bf16_t* src[NI];
-    int dst[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int blk = wave * NI + i;
-        const bool is_w = blk >= NBLK_A;
-        const int off = (is_w ? blk - NBLK_A : blk) * 1024 + lane * 16;
+    // Loads: lane l of a 1 KiB block lands at its 16 bytes l and fetches the piece that the swizzle puts there; its
+    // address is a base that is uniform in the wave plus a 32-bit lane offset inside the tile's rows.  The operands of
+    // a tile are fetched in the order first, second: RING5 alternates it between neighbouring tiles of the output.
+    const bool w_first = RING5 && ((tm ^ tn) & 1);
+    constexpr int NMAX = NA > NW ? NA : NW;
+    [[maybe_unused]] constexpr int NMIN = NA < NW ? NA : NW;
+    const int n_first = w_first ? NW : NA, n_second = NI - n_first;
+    const bf16_t* const a_src = p.A + (AFORM == OP_KMAJOR ? (size_t)m0 * p.lda : (size_t)m0);
+    // SwiGLU: the first half of a wave's W rows are gate rows, the second half the matching up rows, N further on; a
+    // wave loads one half of such a group
+    static_assert(!SWIGLU || NW * 8 == WN / 2, "gate or up rows per wave");
+    const bool up = SWIGLU && (wave & 1);
+    const bf16_t* const w_src = p.W + (WFORM == OP_KMAJOR ? (size_t)(n0 + (up ? p.N : 0)) * p.ldw : (size_t)n0);
+    const size_t a_step = AFORM == OP_KMAJOR ? BK : (size_t)BK * p.lda, w_step = WFORM == OP_KMAJOR ? BK : (size_t)BK * p.ldw;
+    // byte offset of the lane's piece of the wave's block i
+    auto lane_offset = [&](bool is_w, int i) -> uint32_t {
         int row, k;
         if (is_w) {
-            TW::piece(off, &row, &k);
-            if (SWIGLU) {
-                const int wr = row / WN, j = (row % WN) >> 5, rr = row & 31;
-                const int isup = j >= TN / 2;
-                const int col = n0 + wr * (WN / 2) + (isup ? j - TN / 2 : j) * 32 + rr;
-                row = min(col, p.N - 1) + (isup ? p.N : 0);
-            } else {
-                row = min(n0 + row, p.N - (WFORM == OP_KMAJOR ? 1 : 8));
-            }
-            src[i] = WFORM == OP_KMAJOR ? p.W + (size_t)row * p.ldw + k : p.W + (size_t)k * p.ldw + row;
-        } else {
-            TA::piece(off, &row, &k);
-            row = min(m0 + row, p.M - (AFORM == OP_KMAJOR ? 1 : 8));
-            src[i] = AFORM == OP_KMAJOR ? p.A + (size_t)row * p.lda + k : p.A + (size_t)k * p.lda + row;
+            TW::piece((wave * NW + i) * 1024 + lane * 16, &row, &k);
+            if (SWIGLU) row = row / WN * (WN / 2) + row % (WN / 2);
+            row = min(row, p.N - n0 - (WFORM == OP_KMAJOR ? 1 : 8));
+            return 2 * (WFORM == OP_KMAJOR ? (uint32_t)row * p.ldw + k : (uint32_t)k * p.ldw + row);
         }
-        dst[i] = blk * 1024;
+        TA::piece((wave * NA + i) * 1024 + lane * 16, &row, &k);
+        row = min(row, p.M - m0 - (AFORM == OP_KMAJOR ? 1 : 8));
+        return 2 * (AFORM == OP_KMAJOR ? (uint32_t)row * p.lda + k : (uint32_t)k * p.lda + row);
+    };
+    uint32_t off1[NMAX], off2[NMAX];     // of the first and the second operand
+#pragma unroll
+    for (int i = 0; i < NMAX; ++i) {
+        off1[i] = w_first ? lane_offset(true, min(i, NW - 1)) : lane_offset(false, min(i, NA - 1));
+        off2[i] = w_first ? lane_offset(false, min(i, NA - 1)) : lane_offset(true, min(i, NW - 1));
     }
+    const bf16_t *const src1 = w_first ? w_src : a_src, *const src2 = w_first ? a_src : w_src;
+    const size_t step1 = w_first ? w_step : a_step, step2 = w_first ? a_step : w_step;
     const int KT = p.K / BK;
     // (The builtin's address-space-qualified parameters do not type-check in the host pass
     // of a template, which would silently drop the kernel's host stub: device pass only.)
 #if defined(__HIP_DEVICE_COMPILE__)
-#define SP_DMA_ISSUE(tile, stage) SP_DMA_ISSUE_R(tile, stage, 0, NI)
-#define SP_DMA_ISSUE_R(tile, stage, i0, i1)                                                                   \
-    do {                                                                                                       \
-        const int k0_ = min((tile), KT - 1) * BK;                                                              \
-        const size_t ka_ = AFORM == OP_KMAJOR ? k0_ : (size_t)k0_ * p.lda;                                     \
-        const size_t kw_ = WFORM == OP_KMAJOR ? k0_ : (size_t)k0_ * p.ldw;                                     \
-        _Pragma("unroll") for (int i_ = (i0); i_ < (i1); ++i_)                                                 \
-            __builtin_amdgcn_global_load_lds(src[i_] + (wave * NI + i_ >= NBLK_A ? kw_ : ka_),                 \
-                                             (lds_void_ptr)(smem + (stage) * STAGE + dst[i_]), 16, 0, 0);      \
-    } while (0)
+#define SP_DMA(src, step, off, n, tile, lds, i)                                                                \
+    if ((i) < NMIN || (i) < (n))                                                                               \
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const unsigned char*>((src) + min((tile), KT - 1) * (step)) + (off)[i], \
+                                         (lds_void_ptr)((lds) + (wave * (n) + (i)) * 1024), 16, 0, 0);
 #else
-#define SP_DMA_ISSUE(tile, stage) ((void)src, (void)dst)
-#define SP_DMA_ISSUE_R(tile, stage, i0, i1) ((void)src, (void)dst)
+#define SP_DMA(src, step, off, n, tile, lds, i) ((void)(src), (void)(step), (void)(off), (void)(n), (void)(lds), (void)(tile));
 #endif
+    // load l of a tile's first / second operand
+#define SP_LOAD1(tile, lds, l) SP_DMA(src1, step1, off1, n_first, tile, lds, l)
+#define SP_LOAD2(tile, lds, l) SP_DMA(src2, step2, off2, n_second, tile, lds, l)
 
-    f32x16_t acc[TN][TM];
+    f32x4_t acc[TN][TM];
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
+        for (int i = 0; i < TM; ++i) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    // fragment addresses: a contraction-contiguous tile is base + block * 4096 + foff[ks], a row-contiguous
-    // one has its block in the swizzle (one base per block)
-    const int sw = (l32 >> 1) & 7;
-    int foff[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) foff[ks] = l32 * ROW_BYTES + (((2 * ks + half) ^ sw) << 4);
     int abase[TM], wbase[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-        abase[i] = AFORM == OP_KMAJOR ? (wm * TM + i) * 32 * ROW_BYTES : TA::frag_base(wm * TM + i, lane);
+    for (int i = 0; i < TM; ++i) abase[i] = TA::frag_base(wm * TM + i, lane);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-        wbase[j] = A_BYTES + (WFORM == OP_KMAJOR ? (wn * TN + j) * 32 * ROW_BYTES : TW::frag_base(wn * TN + j, lane));
+    for (int j = 0; j < TN; ++j) wbase[j] = TW::frag_base(wn * TN + j, lane);
 
-    constexpr int NFRAG = TM + TN, NMFMA = TM * TN;
-    constexpr int AR = AFORM == OP_KMAJOR ? 1 : 2, WR = WFORM == OP_KMAJOR ? 1 : 2;   // LDS reads per fragment
-    constexpr int M_MFMA = 0x008, M_VMEM_RD = 0x020, M_DS_RD = 0x100;
-    // loads of later tiles that may still be in flight when a tile is needed
-    constexpr int LATER = (NST - 2) * NI;
-    static_assert(LATER + N_AFTER < 64, "fits the load counter");
-
-    bf16x8_t af[2][TM], wf[2][TN];
-    auto load_frags = [&](const unsigned char* tile, int ks, int buf) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-            af[buf][i] = AFORM == OP_KMAJOR ? *reinterpret_cast<const bf16x8_t*>(tile + abase[i] + foff[ks]) : TA::frag(tile, abase[i], ks, lane);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-            wf[buf][j] = WFORM == OP_KMAJOR ? *reinterpret_cast<const bf16x8_t*>(tile + wbase[j] + foff[ks]) : TW::frag(tile, wbase[j], ks, lane);
+    // A 32-deep k-step is worked in NP parts: all fragments of one operand (X, the one with fewer) against a part of
+    // the other's (Y), so that besides a part's NX + NY fragments only the next part's are in registers.
+    constexpr bool X_IS_W = TN <= TM;
+    constexpr int NP = TM * TN > 32 ? 5 : 2, NPT = 2 * NP;           // parts per k-step, per tile
+    constexpr int NX = X_IS_W ? TN : TM, NY = (X_IS_W ? TM : TN) / NP, NMFMA = NX * NY;
+    static_assert((X_IS_W ? TM : TN) % NP == 0 && NX + NY < NMFMA, "equal parts, a read behind each MFMA but the first");
+    bf16x8_t fx[2][NX], fy[2][NY];
+    auto load_x = [&](const unsigned char* ta, const unsigned char* tw, int ks, int x) {
+        if constexpr (X_IS_W) fx[ks][x] = TW::frag(tw, wbase[x], ks, lane); else fx[ks][x] = TA::frag(ta, abase[x], ks, lane);
     };
-    auto mfmas = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][j], af[buf][i], acc[j][i], 0, 0, 0);
+    auto load_y = [&](const unsigned char* ta, const unsigned char* tw, int part, int y) {
+        const int ks = part / NP, i = part % NP * NY + y;
+        if constexpr (X_IS_W) fy[part & 1][y] = TA::frag(ta, abase[i], ks, lane); else fy[part & 1][y] = TW::frag(tw, wbase[i], ks, lane);
     };
-
-#pragma unroll
-    for (int t = 0; t < NST - 1; ++t) SP_DMA_ISSUE(t, t);
-    SP_DMA_ISSUE_R(NST - 1, NST - 1, 0, N_AFTER);
-    __builtin_amdgcn_s_waitcnt(sp_waitcnt(LATER + N_AFTER, 15));      // this thread's loads of tile 0 have landed
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    load_frags(smem, 0, 0);
-    int st = 0;                                        // stage of tile kt
-    for (int kt = 0; kt < KT; ++kt) {
-        const int st1 = st + 1 == NST ? 0 : st + 1;
-        [[maybe_unused]] const int st_last = st == 0 ? NST - 1 : st - 1;
-        unsigned char* cur = smem + st * STAGE;
-        unsigned char* nxt = smem + st1 * STAGE;
-        // the rest of tile kt+NST-1's loads (its first N_AFTER went out after the last barrier)
-        SP_DMA_ISSUE_R(kt + NST - 1, st_last, N_AFTER, N_AFTER + N_STEP0);
-        load_frags(cur, 1, 1);
-        mfmas(0);
-        SP_DMA_ISSUE_R(kt + NST - 1, st_last, N_AFTER + N_STEP0, NI);
-        load_frags(cur, 2, 0);
-        mfmas(1);
-        load_frags(cur, 3, 1);
-        mfmas(0);
-#define SP_SCHED_STEP(NV)                                                                  \
-        _Pragma("unroll") for (int i = 0; i < NFRAG; ++i) {                                    \
-            if (i < TM) __builtin_amdgcn_sched_group_barrier(M_DS_RD, AR, 0);                  \
-            else __builtin_amdgcn_sched_group_barrier(M_DS_RD, WR, 0);                         \
-            __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA / NFRAG, 0);                    \
-            if (i < (NV)) __builtin_amdgcn_sched_group_barrier(M_VMEM_RD, 1, 0);                  \
-        }                                                                                      \
-        if (NMFMA % NFRAG) __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA % NFRAG, 0);
-        SP_SCHED_STEP(N_STEP0)
-        SP_SCHED_STEP(NI - N_AFTER - N_STEP0)
-        SP_SCHED_STEP(0)
-#undef SP_SCHED_STEP
-        // This wave's reads of tile kt are complete and its loads of tile kt+1 (issued NST-1 tiles
-        // ago) have landed; after the barrier that holds for every wave, so the next stage is
-        // readable and this stage may be refilled.
-        __builtin_amdgcn_s_waitcnt(sp_waitcnt(LATER, 0));
+    // read r of those that bring the operands of part `part` (with a new k-step its X too)
+    auto load_part = [&](const unsigned char* ta, const unsigned char* tw, int part, int r) {
+        const int nx = part % NP == 0 ? NX : 0;
+        if (r < nx) load_x(ta, tw, part / NP, r);
+        else if (r < nx + NY) load_y(ta, tw, part, r - nx);
+    };
+    auto mfma = [&](int part, int q) {
+        const int ks = part / NP, x = q % NX, y = q / NX, i = part % NP * NY + y;
+        if constexpr (X_IS_W) acc[x][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[ks][x], fy[part & 1][y], acc[x][i], 0, 0, 0);
+        else acc[i][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fy[part & 1][y], fx[ks][x], acc[i][x], 0, 0, 0);
+    };
+    auto wg_barrier = [&]() {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        SP_DMA_ISSUE_R(kt + NST, st, 0, N_AFTER);
-        load_frags(nxt, 0, 0);
-        mfmas(1);
-#pragma unroll
-        for (int i = 0; i < NFRAG; ++i) {
-            __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA / NFRAG, 0);
-            if (i < TM) __builtin_amdgcn_sched_group_barrier(M_DS_RD, AR, 0);
-            else __builtin_amdgcn_sched_group_barrier(M_DS_RD, WR, 0);
-        }
-        if (NMFMA % NFRAG) __builtin_amdgcn_sched_group_barrier(M_MFMA, NMFMA % NFRAG, 0);
-        st = st1;
+    };
+    // One part: its MFMAs one by one, behind them the reads of the next part's operands and loads of later tiles; the
+    // order is fixed here.  The first MFMA stands before the reads because the compiler waits for all reads in flight
+    // in front of it.  SP_RIDE: load l of n goes out with MFMA (2 l + 1) NMFMA / 2 n.
+#define SP_PART(part, ta, tw, ISSUE)                                                                           \
+    _Pragma("unroll") for (int q_ = 0; q_ < NMFMA; ++q_) {                                                     \
+        if (q_) load_part(ta, tw, ((part) + 1) % NPT, q_ - 1);                                                 \
+        ISSUE(q_)                                                                                              \
+        mfma(part, q_);                                                                                        \
+        __builtin_amdgcn_sched_barrier(0);                                                                     \
     }
+#define SP_RIDE(q, l0, n, LOAD)                                                                                \
+    _Pragma("unroll") for (int l_ = 0; l_ < (n); ++l_)                                                         \
+        if ((2 * l_ + 1) * NMFMA / (2 * (n) + ((n) == 0)) == (q)) { [[maybe_unused]] const int i_ = (l0) + l_; LOAD(i_) }
+    if constexpr (RING5) {
+        auto wrap = [](int s) { return s >= 5 ? s - 5 : s; };
+        auto slot = [&](int s) { return smem + s * SLOT; };
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i) { SP_LOAD1(0, slot(0), i) }
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i) { SP_LOAD2(0, slot(1), i) }
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i) { SP_LOAD1(1, slot(2), i) }
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i) { SP_LOAD2(1, slot(3), i) }
+        __builtin_amdgcn_s_waitcnt(sp_waitcnt(NI, 15));                   // tile 0
+        wg_barrier();
+        int s0 = 0;                                                       // slot of tile kt's first operand
+#pragma unroll
+        for (int r = 0; r < NX + NY; ++r) load_part(slot(w_first), slot(!w_first), 0, r);
+        for (int kt = 0; kt < KT; ++kt) {
+            const int s1 = wrap(s0 + 1), s2 = wrap(s0 + 2), s3 = wrap(s0 + 3);
+            [[maybe_unused]] const int s4 = wrap(s0 + 4);
+            const unsigned char *ca = slot(w_first ? s1 : s0), *cw = slot(w_first ? s0 : s1);
+            const unsigned char *na = slot(w_first ? s3 : s2), *nw = slot(w_first ? s2 : s3);
+            __builtin_amdgcn_sched_barrier(0);
+            // the first operand of tile kt + 2, to the slot that tile kt - 1 left with its second
+            constexpr int H = (NMAX + 1) / 2;
+#define SP_L1(i) SP_LOAD1(kt + 2, slot(s4), i)
+#define SP_L2(i) SP_LOAD2(kt + 2, slot(s0), i)
+#define SP_ISSUE(q) if (part == 0) { SP_RIDE(q, 0, H, SP_L1) } else if (part == 1) { SP_RIDE(q, H, NMAX - H, SP_L1) }
+#define SP_ISSUE_LAST(q) SP_RIDE(q, 0, NMAX, SP_L2)
+#pragma unroll
+            for (int part = 0; part < NPT - 1; ++part) { SP_PART(part, ca, cw, SP_ISSUE) }
+            // This wave's reads of tile kt are complete and its loads of tile kt + 1 have landed (only the first
+            // operand of tile kt + 2 may be in flight); after the barrier that holds for every wave: the next tile is
+            // readable, this one's slots may be refilled.
+            if (NA == NW || !w_first) __builtin_amdgcn_s_waitcnt(sp_waitcnt(NA, 0));
+            else __builtin_amdgcn_s_waitcnt(sp_waitcnt(NW, 0));
+            wg_barrier();
+            SP_PART(NPT - 1, na, nw, SP_ISSUE_LAST)
+            s0 = s2;
+#undef SP_L1
+#undef SP_L2
+#undef SP_ISSUE
+#undef SP_ISSUE_LAST
+        }
+    } else {
+        constexpr int LATER = (NST - 2) * NI;      // loads of later tiles that may be in flight when a tile is needed
+        // of a tile's loads, those with the last part of the tile NST before it, and with each of the next LP parts
+        constexpr int N_AFTER = (3 * NI + 7) / 8, LP = NP == 2 ? 2 : 3, PER = (NI - N_AFTER + LP - 1) / LP;
+        static_assert(LATER + N_AFTER < 64, "fits the load counter");
+#define SP_LOAD(tile, stage, i)                                                                                \
+        if ((i) < NA) { SP_LOAD1(tile, smem + (stage) * STAGE, i) } else { SP_LOAD2(tile, smem + (stage) * STAGE + A_BYTES, (i) - NA) }
+#pragma unroll
+        for (int t = 0; t < NST - 1; ++t)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) { SP_LOAD(t, t, i) }
+#pragma unroll
+        for (int i = 0; i < N_AFTER; ++i) { SP_LOAD(NST - 1, NST - 1, i) }
+        __builtin_amdgcn_s_waitcnt(sp_waitcnt(LATER + N_AFTER, 15));      // this thread's loads of tile 0 have landed
+        wg_barrier();
+#pragma unroll
+        for (int r = 0; r < NX + NY; ++r) load_part(smem, smem + A_BYTES, 0, r);
+        int st = 0;                                        // stage of tile kt
+        for (int kt = 0; kt < KT; ++kt) {
+            const int st1 = st + 1 == NST ? 0 : st + 1;
+            [[maybe_unused]] const int st_last = st == 0 ? NST - 1 : st - 1;
+            const unsigned char *cur = smem + st * STAGE, *nxt = smem + st1 * STAGE;
+            __builtin_amdgcn_sched_barrier(0);
+            // the rest of tile kt + NST - 1's loads (its first N_AFTER went out after the last barrier)
+#define SP_L(i) SP_LOAD(kt + NST - 1, st_last, i)
+#define SP_LN(i) SP_LOAD(kt + NST, st, i)
+#define SP_ISSUE(q)                                                                                            \
+            if (part < LP) {                                                                                   \
+                const int l0_ = N_AFTER + part * PER, n_ = NI - l0_ < PER ? (NI - l0_ > 0 ? NI - l0_ : 0) : PER; \
+                SP_RIDE(q, l0_, n_, SP_L)                                                                      \
+            }
+#define SP_ISSUE_LAST(q) SP_RIDE(q, 0, N_AFTER, SP_LN)
+#pragma unroll
+            for (int part = 0; part < NPT - 1; ++part) { SP_PART(part, cur, cur + A_BYTES, SP_ISSUE) }
+            // as above: the loads of tile kt + 1 were issued NST - 1 tiles ago
+            __builtin_amdgcn_s_waitcnt(sp_waitcnt(LATER, 0));
+            wg_barrier();
+            SP_PART(NPT - 1, nxt, nxt + A_BYTES, SP_ISSUE_LAST)
+            st = st1;
+#undef SP_L
+#undef SP_LN
+#undef SP_LOAD
+#undef SP_ISSUE
+#undef SP_ISSUE_LAST
+        }
+    }
+#undef SP_PART
+#undef SP_RIDE
     __builtin_amdgcn_s_waitcnt(sp_waitcnt(0, 0));   // drain the tail's idle loads
-    gemm_epilogue_staged<EPI, TM, TN, BM, BN_OUT, WAVES * 64, NST * STAGE>(p, acc, smem, m0, n0, wm * WMR,
-                                                                         SWIGLU ? wn * (WN / 2) : wn * WN, l32, half);
-#undef SP_DMA_ISSUE
-#undef SP_DMA_ISSUE_R
+    gemm_epilogue_staged<EPI, TM, TN, BM, BN_OUT, WAVES * 64, LDS_BYTES>(p, acc, smem, m0, n0, wm * WMR,
+                                                                         SWIGLU ? wn * (WN / 2) : wn * WN, lane);
+#undef SP_DMA
+#undef SP_LOAD1
+#undef SP_LOAD2
 }
 
 template <int BM, int BN, int EPI, int AFORM, int WFORM, int WAVES, int WM, int NST = 2>
 hipError_t launch_dma(hipStream_t st, const GemmArgs& g) {
-    constexpr int LDS = NST * (BM + BN) * ROW_BYTES;
+    constexpr int LDS = NST == 5 ? 5 * std::max(BM, BN) * ROW_BYTES : NST * (BM + BN) * ROW_BYTES;
     static_assert(LDS <= 160 * 1024, "the stages fit a CU's LDS");
     constexpr int BN_OUT = (EPI == EPI_SWIGLU_BF16) ? BN / 2 : BN;
     static LdsLimitOnce lds_limit;
@@ -898,10 +956,10 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
         case 2: return launch_one<128, 256, EPI, AFORM, WFORM, 4>(st, g);
         case 3: return launch_one<256, 256, EPI, AFORM, WFORM, 4>(st, g);
         case 4: return launch_one<256, 256, EPI, AFORM, WFORM, 8>(st, g);
-        case 5: return launch_dma<256, 256, EPI, AFORM, WFORM, 8, 2>(st, g);
+        case 5: return launch_dma<256, 256, EPI, AFORM, WFORM, 8, 2, 5>(st, g);
         case 6: return launch_dma<128, 256, EPI, AFORM, WFORM, 8, 2, 3>(st, g);
-        case 7: return launch_dma<128, 128, EPI, AFORM, WFORM, 4, 2>(st, g);
-        case 8: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 192, NOSWIGLU, AFORM, WFORM, 8, 4>(st, g); break;
+        case 7: return launch_dma<128, 128, EPI, AFORM, WFORM, 4, 2, 5>(st, g);
+        case 8: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 192, NOSWIGLU, AFORM, WFORM, 8, 4, 5>(st, g); break;
         case 10: if (EPI != EPI_SWIGLU_BF16) return launch_dma<256, 320, NOSWIGLU, AFORM, WFORM, 8, 4>(st, g); break;
     }
     return hipErrorInvalidValue;

@@ -66,6 +66,36 @@ struct OpTile {
     }
 };
 
+// The same tile for v_mfma_f32_16x16x32: 32-deep k-steps, fragments of 16 rows, lane l -> operand row l & 15 of the
+// block, eight contraction indexes 32 ks + 8 (l >> 4) ..  A row-contiguous tile has its 32-byte pieces XOR-ed with
+// (k >> 3) & 1 on top: a transposing read takes 32 bytes of the k rows 8 g .. 8 g + 3 for each group g of 16 lanes, and
+// two groups eight rows apart would otherwise share their banks.
+template <int ROWS, int FORM>
+struct OpTile16 {
+    typedef OpTile<ROWS, FORM> T;
+    __device__ static void piece(int off, int* r, int* k) {
+        T::piece(off, r, k);
+        if (FORM == OP_RMAJOR) *r ^= ((*k >> 3) & 1) << 4;
+    }
+    // lane part of the address of the fragment of the 16-row block `blk`; a contraction-contiguous tile: without the chunk
+    __device__ static int frag_base(int blk, int lane) {
+        if (FORM == OP_KMAJOR) return blk * 16 * 128 + (lane & 15) * 128;
+        const int s16 = lane & 15, g = lane >> 4;
+        const int s = T::SWZ == 2 ? s16 >> 2 : T::SWZ == 1 ? (s16 >> 3) & 1 : 0;
+        return (8 * g + (s16 >> 2)) * T::RB + ((blk ^ (s << 1) ^ (g & 1)) << 5) + 8 * (s16 & 3);
+    }
+    __device__ static bf16x8_t frag(const unsigned char* tile, int base, int ks, int lane) {
+        if (FORM == OP_KMAJOR) {
+            const int sw = ((lane & 15) >> 1) & 7;
+            return *reinterpret_cast<const bf16x8_t*>(tile + base + (((4 * ks + (lane >> 4)) ^ sw) << 4));
+        }
+        const unsigned char* p = tile + base + ks * 32 * T::RB;
+        const s16x4_t lo = sp_tr_read((lds_s16x4_ptr)(p));
+        const s16x4_t hi = sp_tr_read((lds_s16x4_ptr)(p + 4 * T::RB));
+        return __builtin_bit_cast(bf16x8_t, s16x8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    }
+};
+
 // s_waitcnt immediate (gfx9 encoding: vmcnt[3:0] | expcnt << 4 | lgkmcnt << 8 | vmcnt[5:4] << 14)
 constexpr int sp_waitcnt(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | ((vm >> 4) << 14); }
 // Barrier over LDS traffic only: unlike __syncthreads() it does not wait for global stores.

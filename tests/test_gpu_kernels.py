@@ -290,6 +290,31 @@ def test_gemm_transposed_operands_lds_dma(M, N, K, tile):
         assert np.all(np.abs(got - want) <= tol + (2.0 ** -23 * np.abs(want) if f32out else BF16_EPS * np.abs(want))), (epi, a_form)
 
 
+@pytest.mark.parametrize("tile", [5, 6, 7, 8, 10])
+@pytest.mark.parametrize("K", [64, 128, 192, 320, 384, 704])
+def test_gemm_lds_dma_k_tiles(K, tile):
+    """One to eleven k-tiles through the rings of three to five stages and slots (fewer than the ring holds, its
+    length, once and twice round), several tiles of every width in both directions so that both orders of fetching
+    the operands occur, ragged rows and columns; every operand form against the same float64 product."""
+    M, N = 536, 712
+    rng = np.random.default_rng(K + tile)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (N, K), 0.1)
+    d = [dev_u16(x) for x in (Ab, Wb, Ab.T, Wb.T)]
+    ref = A @ W.T
+    for epi, a_form, w_form in ((sp.EPI_F32, 0, 0), (sp.EPI_F32, 0, 1), (sp.EPI_F32, 1, 1), (sp.EPI_BF16, 0, 0)):
+        f32out = epi == sp.EPI_F32
+        Cd = torch.full((M + 1, N), 7.0 if f32out else 7, dtype=torch.float32 if f32out else torch.int16, device=DEV)
+        assert sp.spk_gemm(stream_ptr(), epi, ptr(d[2 * a_form]), M if a_form else K, a_form, ptr(d[1 + 2 * w_form]), N if w_form else K, w_form,
+                           ptr(Cd), N, None, 0, None, M, N, K, tile) == sp.SP_OK
+        sync()
+        out = Cd.cpu()
+        assert bool((out[M] == 7).all())
+        got = out[:M].numpy() if f32out else bf16_vals(host_u16(out[:M].contiguous()))
+        tol = 2e-6 * np.sqrt(K) * np.max(np.abs(ref))                      # as in test_gemm_transposed_operands
+        assert np.all(np.abs(got - ref) <= tol + (0 if f32out else BF16_EPS * np.abs(ref))), (epi, a_form, w_form)
+
+
 @pytest.mark.parametrize("M,N,K", [(1024, 4096, 64), (2560, 640, 320), (640, 640, 512), (512, 2048, 64), (2072, 1032, 256), (264, 40, 1088),
                                    (1032, 2560, 128)])
 def test_gemm_transposed_operands_own_choice(M, N, K):
