@@ -52,7 +52,11 @@ struct sp_engine {
     int ci = 0, mi = 0;                                  // ops issued by the current call
     std::vector<int> tr_copy_layer, tr_copy_dep, tr_comp_layer, tr_comp_dep;
     hipEvent_t ev_sync_c = nullptr, ev_sync_h = nullptr;
-    // Host run-ahead bound: ring of events, one per enqueued layer op, with the running count
+    // A slot that never changes its layer needs no fence behind a compute, until weights are updated.
+    bool slot_refilled(int slot) const { return plan.n_slots < n_units && slot >= plan.n_pinned; }
+    bool weights_change = false;                         // sp_weights_updated was called
+    hipEvent_t ev_updated = nullptr;                     // everything enqueued before its first call
+    // Host run-ahead bound: ring of events behind enqueued layer ops, with the running count
     // of compute-stream packets at each; see throttle() in sp_engine.hip.
     std::vector<hipEvent_t> thr_ev;
     std::vector<uint64_t> thr_at;

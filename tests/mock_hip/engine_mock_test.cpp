@@ -177,6 +177,33 @@ static void test_forward_windows(int arch) {
     printf("ok forward windows arch %d\n", arch);
 }
 
+// Slots that keep their layers record no event behind a compute until weights are updated: the copy of a rewritten layer
+// still waits for the passes enqueued before, in the first such pass and in later ones.
+static void test_updates_of_kept_layers() {
+    const int B = 2, S = 8;
+    for (int pinned = 0; pinned < 2; ++pinned) {
+        Rig r(SP_DECODER_SWIGLU_RMS, 4, B, S);
+        const int k = pinned ? 1 : 8;
+        Handle H(r, k, 1, 0, 0, pinned ? 2 : 0);
+        CHECK(H.rc == SP_OK, "sp_create: %s", sp_last_error(nullptr));
+        if (H.rc != SP_OK) return;
+        std::vector<float> y[4];
+        for (auto& v : y) v.assign((size_t)B * S * 64, -1.f);
+        CHECK(sp_forward(H.h, r.x.data(), y[0].data(), B, S) == SP_OK, "forward");
+        for (int i = 1; i < 4; ++i) {
+            // the pass before has read the host blobs; its computes may still be running
+            r.sync();
+            CHECK(sp_forward(H.h, r.x.data(), y[0].data(), B, S) == SP_OK, "forward");
+            CHECK(sp_weights_updated(H.h, 1) == SP_OK, "weights_updated");
+            CHECK(sp_forward(H.h, r.x.data(), y[i].data(), B, S) == SP_OK, "forward after an update");
+        }
+        r.sync();
+        const std::vector<float> base = forward(r, 8, 8, 0, B, S);
+        for (auto& v : y) CHECK(same(v, base), "pinned %d: a pass around an update differs", pinned);
+    }
+    printf("ok updates of kept layers\n");
+}
+
 struct StepOut {
     std::vector<float> y, dx;
     float loss = 0;
@@ -512,6 +539,7 @@ int main(int argc, char** argv) {
     test_large_gradients(SP_ENCODER_GELU_LN);
     test_run_ahead_with_forwards_between_steps();
     test_forward_under_capture();
+    test_updates_of_kept_layers();
     test_steps_of_several_handles();
     test_decode();
     test_injected_failures(false);
