@@ -835,22 +835,23 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
     return best;
 }
 
-// Operands with the row index contiguous: the estimated time in us of a tile, as fitted to 764 launches (T 64..8192,
-// widths 256..4096, operands not in the caches; rms 4-12 %): launch and prologue a, per unit (one work-group on every
-// CU) b and c per 1000 of K, w per MB of output.  A last round of the two-per-CU tiles that fills one half of the slots
-// counts `half` units.  The LDS-DMA tiles and the small ones (16, 18; not with the residual epilogue) stand in one
-// table, so that every pair is compared by measured time: the choice is 0.5 % off the best tile on average.  Estimates
-// from tile area and a rate, without the output's share, were 2.7 % off and up to 1.9 times with few tokens (dW
-// 1024 x 4096 over 64 tokens 16.5 us on 32x32 tiles, 8.5 on 128x128).
+// Operands with the row index contiguous: the estimated time in us of a tile, as fitted to 79 shapes on every tile (rows
+// 64..22016, contraction 256..23808, weights not in the caches; rms 4-13 %): launch and prologue a, per unit (one
+// work-group on every CU) b and c per 1000 of K, w per MB of output.  A last round of the two-per-CU tiles that fills one
+// half of the slots counts `half` units.  The LDS-DMA tiles and the small ones (16, 18; not with the residual epilogue)
+// stand in one table, so that every pair is compared by measured time: the choice is 0.2 % (weights transposed) and
+// 0.3 % (both) off the best tile on average.  The table fitted to the two-stage form of the LDS-DMA kernel, whose lone
+// 128x128 tile on a CU waited for its loads (`half` 1.76), was 5.2 and 2.6 % off: dX 2304 x 1152 x 2944 35.8 us on
+// 128x256 tiles, 26.1 on 128x128; 1152 x 3072 x 15616 193 and 147; dW 1472 x 1472 x 7488 86 and 67.
 struct TileTime { int id, bm, bn, concurrent; float a, b, c, w, half; };
-constexpr TileTime kTimesKR[] = {{5, 256, 256, 256, 4.245f, 1.305f, 20.73f, 0.417f, 1.f}, {10, 256, 320, 256, 0.335f, 6.826f, 23.81f, 0.326f, 1.f},
-                                 {8, 256, 192, 256, 3.847f, 0.f, 18.25f, 0.448f, 1.f},    {6, 128, 256, 256, 1.256f, 2.700f, 11.91f, 0.443f, 1.f},
-                                 {7, 128, 128, 512, 2.006f, 0.f, 7.214f, 0.495f, 1.764f}, {16, 32, 32, 512, 2.321f, 0.f, 2.340f, 0.422f, 1.f},
-                                 {18, 64, 64, 256, 1.670f, 1.554f, 3.881f, 0.718f, 1.f}};
-constexpr TileTime kTimesRR[] = {{5, 256, 256, 256, 2.697f, 5.682f, 20.57f, 0.173f, 1.f}, {10, 256, 320, 256, 2.748f, 8.311f, 23.87f, 0.154f, 1.f},
-                                 {8, 256, 192, 256, 4.663f, 1.246f, 17.92f, 0.218f, 1.f}, {6, 128, 256, 256, 3.889f, 0.785f, 11.85f, 0.261f, 1.f},
-                                 {7, 128, 128, 512, 3.809f, 0.f, 7.698f, 0.230f, 1.625f}, {16, 32, 32, 512, 2.238f, 0.f, 2.507f, 0.462f, 1.184f},
-                                 {18, 64, 64, 256, 2.078f, 1.246f, 4.123f, 0.380f, 1.f}};
+constexpr TileTime kTimesKR[] = {{5, 256, 256, 256, 0.f, 3.117f, 19.05f, 0.319f, 1.f}, {10, 256, 320, 256, 1.575f, 0.f, 24.95f, 0.324f, 1.f},
+                                 {8, 256, 192, 256, 0.f, 3.118f, 15.77f, 0.255f, 1.f}, {6, 128, 256, 256, 0.f, 3.639f, 11.58f, 0.177f, 1.f},
+                                 {7, 128, 128, 512, 3.569f, 0.f, 7.213f, 0.107f, 1.08f}, {16, 32, 32, 512, 2.258f, 0.166f, 1.830f, 0.369f, 1.04f},
+                                 {18, 64, 64, 256, 1.240f, 1.711f, 3.608f, 0.461f, 1.f}};
+constexpr TileTime kTimesRR[] = {{5, 256, 256, 256, 6.181f, 0.f, 19.86f, 0.186f, 1.f}, {10, 256, 320, 256, 0.f, 5.736f, 25.28f, 0.125f, 1.f},
+                                 {8, 256, 192, 256, 4.116f, 1.893f, 16.28f, 0.139f, 1.f}, {6, 128, 256, 256, 3.699f, 0.f, 11.93f, 0.198f, 1.f},
+                                 {7, 128, 128, 512, 3.495f, 0.f, 7.371f, 0.145f, 1.04f}, {16, 32, 32, 512, 2.570f, 0.484f, 2.046f, 0.f, 1.12f},
+                                 {18, 64, 64, 256, 2.167f, 1.739f, 3.163f, 0.311f, 1.f}};
 
 int quickest_tile(int epi, int a_form, int M, int N, int K, float* us) {
     const bool small_ok = epi != EPI_RESID_F32;
