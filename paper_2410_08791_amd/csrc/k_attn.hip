@@ -30,6 +30,7 @@
 namespace {
 
 constexpr int KB = 64;    // keys per LDS tile
+constexpr int ATTN_SPLIT_WAVES = 4;
 constexpr int PF = 3;     // fragment reads in flight ahead of the MFMA that uses them
 
 // NW = waves per work-group: a work-group handles NW * 32 queries of one head.
@@ -354,6 +355,148 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_kernel(const bf16_t* __re
 #undef SP_ATTN_ISSUE
 }
 
+// The same attention where 128-query work-groups are too few for the chip: a work-group handles 32 queries of one head
+// and its four waves share out the KEY tiles, wave w the tiles w, w + 4, ...  A wave loads its tiles into an LDS stage of
+// its own and waits for nobody; at the end the waves' outputs, sums and maxima meet in LDS and are added in wave order.
+// What bounds a launch like this is the chain of one wave -- load a tile, scores, softmax, output -- with a few
+// work-groups on the chip, so four chains of a quarter of the tiles take the place of one.
+template <int HD>
+__global__ __launch_bounds__(256, 1) void attn_fwd_split_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
+                                                              float* __restrict__ lse, int S, int Hq, int Hkv, int ld_qkv,
+                                                              int causal, float scale_log2e) {
+    typedef AttnCfg<HD, 1> C;
+    constexpr int NW = ATTN_SPLIT_WAVES;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_split[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int nqb = gridDim.x;
+    const int lin = blockIdx.x + (int)gridDim.x * (blockIdx.y + (int)gridDim.y * blockIdx.z);
+    const int job = xcd_remap(lin, (int)(gridDim.x * gridDim.y * gridDim.z));
+    const int bx = job % nqb, h = (job / nqb) % (int)gridDim.y, b = job / (nqb * (int)gridDim.y);
+    const int q0 = (causal ? nqb - 1 - bx : bx) * 32, qi = q0 + l32;
+    const size_t tok0 = (size_t)b * S;
+    const bf16_t* kbase = qkv + tok0 * ld_qkv + (size_t)(Hq + h / (Hq / Hkv)) * HD;
+    unsigned char* sK = smem_split + wave * C::STAGE;
+    unsigned char* sV = sK + C::TILE_BYTES;
+
+    int ld_col[C::NINST], ld_row[C::NINST];
+    bool ld_on[C::NINST];
+#pragma unroll
+    for (int i = 0; i < C::NINST; ++i) {
+        const int off = i * 1024 + lane * 16;
+        const bool isv = i * 1024 >= C::TILE_BYTES;
+        const int rel = off - (isv ? C::TILE_BYTES : 0);
+        const int row = rel / C::ROWB, pos = (rel % C::ROWB) >> 4;
+        const int c = isv ? pos ^ (C::v_swz(row) << 2) : pos ^ C::k_swz(row);
+        ld_on[i] = c < C::CPR;
+        ld_row[i] = row;
+        ld_col[i] = (isv ? Hkv * HD : 0) + (c < C::CPR ? c : 0) * 8;
+    }
+    auto issue = [&](int kt) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+        for (int i = 0; i < C::NINST; ++i)
+            if (ld_on[i])
+                __builtin_amdgcn_global_load_lds(kbase + ((size_t)min(kt * KB + ld_row[i], S - 1) * ld_qkv + ld_col[i]),
+                                                 (lds_void_ptr)(sK + i * 1024), 16, 0, 0);
+#endif
+    };
+    const int k_end = causal ? min(S, q0 + 32) : S;
+    const int ntiles = (k_end + KB - 1) / KB;
+    if (wave < ntiles) issue(wave);
+    if (C::ONES_ROW) {
+        // the padding of the wave's V rows, which no load writes: bf16 1.0 (see AttnCfg)
+        constexpr int PER_ROW = (C::ROWB - HD * 2) / 16;
+        for (int i = lane; i < KB * PER_ROW; i += 64)
+            *reinterpret_cast<u32x4_t*>(sV + i / PER_ROW * C::ROWB + HD * 2 + i % PER_ROW * 16) =
+                u32x4_t{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    }
+    bf16x8_t qf[C::NKS];
+    {
+        const bf16_t* qp = qkv + (tok0 + min(qi, S - 1)) * ld_qkv + h * HD + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < C::NKS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_t*>(qp + ks * 16);
+    }
+    int kpos[C::NKS], vpos[C::NMT];
+#pragma unroll
+    for (int ks = 0; ks < C::NKS; ++ks) kpos[ks] = l32 * C::ROWB + (((2 * ks + half) ^ C::k_swz(l32)) << 4);
+    const int rowv = half * 4 + ((lane & 15) >> 2);
+#pragma unroll
+    for (int mt = 0; mt < C::NMT; ++mt) vpos[mt] = rowv * C::ROWB + ((mt ^ C::v_swz(rowv)) << 6) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+
+    f32x16_t oacc[C::NMT];
+#pragma unroll
+    for (int t = 0; t < C::NMT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
+    // Finite, unlike the other kernel's start: a wave may hold no key that a query sees, and the difference of two
+    // -infinities would make its probabilities NaN instead of 0.
+    SoftmaxState sm{-3.402823466e38f, 0.f};
+    for (int kt = wave; kt < ntiles; kt += NW) {
+        // this wave's loads have landed, its writes of the padding are complete
+        __builtin_amdgcn_s_waitcnt(sp_waitcnt(0, 0));
+        asm volatile("" ::: "memory");
+        if (HD != 128 && k_end - kt * KB <= 32)
+            attn_tile<HD, 1, 1>(sK, sV, kpos, vpos, qf, oacc, sm, kt * KB, S, causal, qi, q0, half, scale_log2e, kt == wave);
+        else
+            attn_tile<HD, 1, 2>(sK, sV, kpos, vpos, qf, oacc, sm, kt * KB, S, causal, qi, q0, half, scale_log2e, kt == wave);
+        // every read of the tile is done before the next tile's loads write over it
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (kt + NW < ntiles) issue(kt + NW);
+    }
+    const float l = C::ONES_ROW ? oacc[C::NMT - 1][(HD % 32) / 8 * 4] : sm.l_run + __shfl_xor(sm.l_run, 32, 64);
+    __syncthreads();                          // the stages are free
+    float4* rows = reinterpret_cast<float4*>(smem_split);                   // [wave][group of four rows][lane]
+    float* ml = reinterpret_cast<float*>(smem_split) + NW * C::NMT * 16 * 64;      // [wave][maximum, sum][lane]
+#pragma unroll
+    for (int mt = 0; mt < C::NMT; ++mt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            rows[((wave * C::NMT + mt) * 4 + g) * 64 + lane] =
+                make_float4(oacc[mt][g * 4], oacc[mt][g * 4 + 1], oacc[mt][g * 4 + 2], oacc[mt][g * 4 + 3]);
+    ml[(wave * 2) * 64 + lane] = sm.m_run;
+    ml[(wave * 2 + 1) * 64 + lane] = l;
+    __syncthreads();
+    float M = ml[lane], f[NW], L = 0.f;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[w * 2 * 64 + lane]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        f[w] = __builtin_amdgcn_exp2f((ml[w * 2 * 64 + lane] - M) * scale_log2e);
+        L = fmaf(f[w], ml[(w * 2 + 1) * 64 + lane], L);
+    }
+    if (qi >= S) return;
+    const float inv = 1.0f / L;
+    bf16_t* op = o + (tok0 + qi) * (size_t)(Hq * HD) + h * HD;
+#pragma unroll
+    for (int i = 0; i < C::NMT; ++i) {
+        const int grp = wave + NW * i, e0 = grp * 8 + half * 4;            // group of eight head-dimension rows, four a lane
+        if (e0 >= HD) continue;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float4 r = rows[(w * C::NMT * 4 + grp) * 64 + lane];
+            v[0] = fmaf(f[w], r.x, v[0]); v[1] = fmaf(f[w], r.y, v[1]); v[2] = fmaf(f[w], r.z, v[2]); v[3] = fmaf(f[w], r.w, v[3]);
+        }
+        *reinterpret_cast<uint2*>(op + e0) = make_uint2(pack_bf2(v[0] * inv, v[1] * inv), pack_bf2(v[2] * inv, v[3] * inv));
+    }
+    if (lse && wave == 0 && half == 0) lse[((size_t)b * Hq + h) * S + qi] = M * scale_log2e * 0.69314718055994530942f + logf(L);
+}
+
+template <int HD>
+hipError_t launch_split(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, const AttnShape& a, float sl2) {
+    typedef AttnCfg<HD, 1> C;
+    constexpr int LDS_EPI = ATTN_SPLIT_WAVES * (C::NMT * 16 + 2) * 64 * 4, LDS_LOOP = ATTN_SPLIT_WAVES * C::STAGE;
+    constexpr int LDS = LDS_EPI > LDS_LOOP ? LDS_EPI : LDS_LOOP;
+    static_assert(LDS <= 160 * 1024 && C::NINST < 63, "fits the LDS and the load counter");
+    static LdsLimitOnce lds_limit;
+    hipError_t e = lds_limit.set(reinterpret_cast<const void*>(attn_fwd_split_kernel<HD>), LDS);
+    if (e != hipSuccess) return e;
+    attn_fwd_split_kernel<HD><<<dim3((a.S + 31) / 32, a.Hq, a.B), 64 * ATTN_SPLIT_WAVES, LDS, st>>>(qkv, o, lse, a.S, a.Hq, a.Hkv, a.ld_qkv,
+                                                                                               a.causal, sl2);
+    return hipGetLastError();
+}
+
 template <int HD, int NW>
 hipError_t launch_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, const AttnShape& a, float sl2) {
     typedef AttnCfg<HD, NW> C;
@@ -373,6 +516,16 @@ hipError_t launch_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, 
 // holds nine waves instead of twelve, and hiding the loads' latency matters more than the idle waves.)
 template <int HD>
 hipError_t launch_hd(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, const AttnShape& a, float sl2) {
+    // The split form while its work-groups all run at once (one per CU, two at head_dim 64 with its 64 KB of LDS), and a
+    // wave has more than one key tile to give away.  us, 128-query form and split form:
+    //   one image, 257 tokens, 16 heads of 80  9.3 and 7.2, two images (288 work-groups) 9.5 and 13.2
+    //   2 x 128 tokens, 4 heads of 64, causal 6.5 and 4.8;  1024 tokens, 16 heads of 64 19.3 and 12.5, twice as many 20.4 and 19.5
+    //   512 tokens, 16 heads of 128, causal 16.2 and 8.6, 32 heads 16.9 and 16.1;  64 tokens, 16 heads of 80 4.6 and 5.2
+    // Long causal heads of 128 gain up to two rounds: their first blocks have few tiles (1024 tokens, 16 heads 27.0 and
+    // 18.5; with 128 tokens x 64 heads 9.2 and 11.8).
+    const long groups = (long)((a.S + 31) / 32) * a.Hq * a.B;
+    const bool two = HD == 64 || (HD == 128 && a.causal && a.S >= 512);
+    if (a.S > KB && groups <= (two ? 512 : 256)) return launch_split<HD>(st, qkv, o, lse, a, sl2);
     return launch_fwd<HD, 4>(st, qkv, o, lse, a, sl2);
 }
 

@@ -435,6 +435,29 @@ def test_attention_causal_writes_every_query_block(B, S, Hq, Hkv, hd):
     assert np.max(np.abs(got - ref)) <= 3 * BF16_EPS * np.max(np.abs(ref))   # as in test_attention
 
 
+@pytest.mark.parametrize("hd,Hq,Hkv,causal", [(64, 4, 2, 1), (64, 2, 2, 0), (80, 2, 2, 0), (80, 4, 2, 1), (128, 4, 1, 1), (128, 2, 2, 0)])
+@pytest.mark.parametrize("S", [65, 95, 97, 193, 257, 319, 512, 513])
+def test_attention_key_tiles_shared_by_waves(S, hd, Hq, Hkv, causal):
+    """Few work-groups: waves with no key tile, one or several, ragged last tiles of 1, 32, 33 and 63 keys, queries that
+    see none of a wave's keys; scores spread over tens of units, so that the waves' maxima differ widely, with the
+    largest keys first or last."""
+    rng = np.random.default_rng(S + hd + causal)
+    nq, nk = Hq * hd, Hkv * hd
+    _, qkv = rand_bf16(rng, (2 * S, nq + 2 * nk))
+    grow = np.tile(np.linspace(0.1, 6.0, S), 2) if S % 2 else np.tile(np.linspace(6.0, 0.1, S), 2)
+    qkv[:, nq:nq + nk] *= grow[:, None]
+    t = torch.from_numpy(qkv).to(torch.bfloat16)
+    qkv = t.to(torch.float64).numpy()
+    sh = O.StackShape(O.DECODER, 1, nq, Hq, Hkv, hd, 64, bool(causal))
+    ref = O.attention(qkv[:, :nq], qkv[:, nq:nq + nk], qkv[:, nq + nk:], 2, S, sh)
+    o = torch.full((2 * S, nq), 0x7FC1, dtype=torch.int16, device=DEV)      # bf16 NaN where nothing is written
+    qd = t.to(DEV)
+    assert sp.spk_attention(stream_ptr(), ptr(qd), ptr(o), None, 2, S, Hq, Hkv, hd, causal) == sp.SP_OK
+    sync()
+    got = bf16_vals(host_u16(o))
+    assert np.max(np.abs(got - ref)) <= 3 * BF16_EPS * np.max(np.abs(ref))   # as in test_attention
+
+
 def test_attention_rejects_unsupported_head_dim():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     assert sp.spk_attention(stream_ptr(), ptr(z), ptr(z), None, 1, 8, 2, 2, 48, 1) == sp.SP_ERR_INVALID_ARG
