@@ -378,30 +378,38 @@ hipError_t launch_one(hipStream_t st, const DecodeCall& c, int splits, int per) 
 
 // Splits, query heads per work-group and waves.  Splits and waves, which the order of the sums depends on, follow
 // from the shapes alone; without a scratch for the splits' rows G is 1.
-//   splits: enough work-groups for the chip, at least 512 positions each (a split saves less than the second
-//     launch costs below that), and no more rows of partial results than decode_scratch_floats counts.
-//   G: the fewest heads whose work-groups still fit one round of the chip (256, or 1024 of two waves); a group's
-//     cache is then read again through the L2, which costs less than idle CUs.  Always sharing it cost, us:
-//     1 x 64/8 heads of 128 over 500 positions 34.3 against 9.1, 4 x 64/8 over 800 38.6 against 19.5; never sharing
-//     it 32 x 32/8 over 500 39.5 against 21.  More than four heads per work-group spilled registers and was slower
-//     than two blocks of four (8 x 64/8 over 4096 positions 91 against 43).
+//   splits: none below 1024 positions (they would save less than the second launch costs).  Above, as many as fill the
+//     chip twice over, with at least 256 positions each, and beyond 16 of them with 512 -- more rows of partial
+//     results cost the second launch more than shorter splits save -- and no more rows than decode_scratch_floats counts.
+//   G: the fewest heads whose work-groups still fit one round of the chip (splits: two rounds of small ones; else 256, or
+//     1024 of two waves); a group's cache is then read again through the L2, which costs less than idle CUs.  Always
+//     sharing it cost, us: 1 x 64/8 heads of 128 over 500 positions 34.3 against 9.1, 4 x 64/8 over 800 38.6 against
+//     19.5; never sharing it 32 x 32/8 over 500 39.5 against 21.  More than four heads per work-group spilled registers
+//     and was slower than two blocks of four (8 x 64/8 over 4096 positions 91 against 43).
 //   NW: a wave with less than a step of 128 positions idles in its loads, and every wave has its part in the
 //     merge: 64 x 32 heads over 16 positions 42.6 us with eight waves, 15.8 with two.  Several rounds of work-groups
-//     of a split launch overlap better in small ones (8 x 64/8 over 4096, G = 4: eight waves 64, two 43).
-// Against 258 shapes (1..64 sequences, groups of 1 to 8, 20..16000 positions) the choice is 3.6 % off the best
-// of all combinations on average.
+//     of a split launch overlap better in small ones (8 x 64/8 over 4096, G = 4: four waves 45, two 39).
+// One split: against 258 shapes (1..64 sequences, groups of 1 to 8, 20..16000 positions) 3.6 % off the best of all
+// combinations on average.  Several: against 57 shapes (1..29 sequences, 2..64 heads, 1024..14652 positions) 3.5 % off
+// the best; splits of 512 positions in work-groups of up to eight waves that filled the chip once, which left a wave 72
+// positions of a step of 128, were 9.5 % off.  us, before and after: 2 x 32/8 heads of 128 over 8191 positions
+// 23.0 and 20.5, 16 x 32/8 over 2000 37.2 and 30.9, 4 x 36/9 of 64 over 5580 24.0 and 19.7; slowest 4 x 28/7 over 3355
+// 19.6 and 20.8.
 struct DecodePlan { int splits, per, G, NW; };
 DecodePlan plan_decode(const DecodeCall& c) {
     const int heads = c.B * c.Hkv, grp = c.Hq / c.Hkv;
     DecodePlan p;
-    p.splits = c.one_split ? 1 : std::max(std::min(std::max(kDecodeSplitGroups / heads, 1), c.n / 512), 1);
+    p.splits = 1;
+    if (!c.one_split && c.n >= 1024)
+        p.splits = std::max(std::min(std::min(kDecodeSplitGroups / heads, (c.n + 255) / 256), std::max(16, (c.n + 511) / 512)), 1);
     p.per = std::max(((c.n + p.splits - 1) / p.splits + 63) / 64 * 64, 64);
     p.splits = std::max((c.n + p.per - 1) / p.per, 1);           // none is empty
-    p.NW = p.per <= 128 ? 2 : p.per <= 400 ? 4 : 8;
     auto groups = [&](int G) { return (long)heads * ((grp + G - 1) / G) * p.splits; };
+    const bool split = p.splits > 1;
+    p.NW = split ? (p.per <= 256 ? 2 : 4) : p.per <= 128 ? 2 : p.per <= 400 ? 4 : 8;
     p.G = 1;
-    while (p.G < 4 && p.G < grp && groups(p.G) > (p.NW == 2 ? 1024 : 256)) p.G *= 2;
-    if (p.splits > 1 && groups(p.G) > 256) p.NW = p.G == 4 && groups(4) > 512 ? 2 : 4;
+    while (p.G < 4 && p.G < grp && groups(p.G) > (split ? 512 : p.NW == 2 ? 1024 : 256)) p.G *= 2;
+    if (split && p.G == 4 && groups(4) > 512) p.NW = 2;
     return p;
 }
 
@@ -409,8 +417,7 @@ template <int HD>
 hipError_t launch_decode(hipStream_t st, const DecodeCall& c) {
     const DecodePlan p = plan_decode(c);
     if (p.splits > 1 && !c.part)
-        return p.NW == 2 ? launch_one<HD, 1, 2, 8>(st, c, p.splits, p.per) : p.NW == 4 ? launch_one<HD, 1, 4, 4>(st, c, p.splits, p.per)
-                                                                                       : launch_one<HD, 1, 8, 2>(st, c, p.splits, p.per);
+        return p.NW == 2 ? launch_one<HD, 1, 2, 8>(st, c, p.splits, p.per) : launch_one<HD, 1, 4, 4>(st, c, p.splits, p.per);
 #define SP_DECODE(g, w) if (p.G == g && p.NW == w) return launch_one<HD, g, w, 1>(st, c, p.splits, p.per);
     SP_DECODE(1, 2) SP_DECODE(1, 4) SP_DECODE(1, 8) SP_DECODE(2, 2) SP_DECODE(2, 4) SP_DECODE(2, 8) SP_DECODE(4, 2) SP_DECODE(4, 4) SP_DECODE(4, 8)
 #undef SP_DECODE
