@@ -8,7 +8,8 @@
 //                     user; one hipMemcpyAsync of the whole layer blob; record
 //                     a "loaded" event
 //   compute(l):       compute stream waits for l's "loaded" event; the layer's
-//                     kernels; record a "done" event
+//                     kernels; record a "done" event where a copy into the slot
+//                     may follow
 // Those two event kinds are the only cross-stream edges (training adds the pair
 // that fences the two gradient slots against the device-to-host stream).  An event is always
 // recorded (in host order) before anything waits on it.  The host blocks only at
