@@ -399,7 +399,8 @@ int sp_forward_backward(sp_handle h, const float* x_dev, const float* target_dev
  * sp_weights_updated tells the handle that the caller has rewritten
  * layer_host_blobs[layer] (layer -1: every layer): a copy of it still in device
  * memory is forgotten and the next pass streams the layer in again.  Host order
- * only, no device work.  A layer's host blob may be rewritten (a) while none of the
+ * only, no device work.  That next pass may not be under stream capture where the
+ * handle has run a pass outside the capture (SP_ERR_STATE, the handle stays usable).  A layer's host blob may be rewritten (a) while none of the
  * handle's passes is in flight, or (b) during a training step once
  * sp_wait_gradient(layer) has returned: the step reads the layer for the last time
  * before it sends that gradient.  Skipping the call leaves stale weights in use for

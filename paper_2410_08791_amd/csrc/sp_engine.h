@@ -54,8 +54,11 @@ struct sp_engine {
     hipEvent_t ev_sync_c = nullptr, ev_sync_h = nullptr;
     // A slot that never changes its layer needs no fence behind a compute, until weights are updated.
     bool slot_refilled(int slot) const { return plan.n_slots < n_units && slot >= plan.n_pinned; }
-    bool weights_change = false;                         // sp_weights_updated was called
-    hipEvent_t ev_updated = nullptr;                     // everything enqueued before its first call
+    bool update_pending = false;                         // sp_weights_updated was called since the latest pass
+    bool weights_change = false;                         // a pass has followed such a call
+    bool unfenced = false, unfenced_eager = false;       // computes without a done event: any, any outside a capture
+    hipEvent_t ev_updated = nullptr;                     // everything enqueued before the first pass behind an update
+    bool captured = false;                               // the current call is under stream capture
     // Host run-ahead bound: ring of events behind enqueued layer ops, with the running count
     // of compute-stream packets at each; see throttle() in sp_engine.hip.
     std::vector<hipEvent_t> thr_ev;

@@ -248,6 +248,9 @@ struct HipSink : SchedSink {
             hipEvent_t ev = e->comp_event(e->mi);
             SP_HIP(e, hipEventRecord(ev, st));
             e->layer_done[layer] = ev;
+        } else {
+            e->unfenced = true;
+            e->unfenced_eager |= !e->captured;
         }
         e->layer_done_idx[layer] = e->mi;
         e->tr_comp_layer[e->mi] = layer;
@@ -512,6 +515,9 @@ static int check_call(sp_engine* e, int B, int S) {
     if (e->failed) return SP_ERR_STATE;          // e->error keeps the first failure's text
     if (B < 1 || S < 1 || B > e->desc.max_batch || S > e->desc.max_seq)
         return fail(e, SP_ERR_SHAPE, "B=%d S=%d outside 1..%d x 1..%d", B, S, e->desc.max_batch, e->desc.max_seq);
+    // a captured copy cannot wait for passes outside the capture
+    if (e->update_pending && e->unfenced_eager && being_captured(e))
+        return fail(e, SP_ERR_STATE, "the first pass after sp_weights_updated cannot be captured");
     return SP_OK;
 }
 
@@ -522,6 +528,19 @@ static int begin_call(sp_engine* e) {
     e->ci = e->mi = 0;
     std::fill(e->layer_loaded_idx.begin(), e->layer_loaded_idx.end(), -1);
     std::fill(e->layer_done_idx.begin(), e->layer_done_idx.end(), -1);
+    e->captured = being_captured(e);
+    if (e->update_pending && !e->weights_change) {
+        // Slots that keep their layer have recorded nothing so far: one event behind all that is enqueued stands in for
+        // their passes, this and later passes record their own.
+        if (e->unfenced) {
+            SP_HIP(e, hipEventRecord(e->ev_updated, e->compute));
+            for (int u = 0; u < e->n_units; ++u)
+                if (!e->layer_done[u]) e->layer_done[u] = e->ev_updated;
+            e->unfenced = e->unfenced_eager = false;
+        }
+        e->weights_change = true;
+    }
+    e->update_pending = false;
     if (e->flags & SP_FLAG_TIMING) SP_HIP(e, hipEventRecord(e->t0, e->compute));
     return SP_OK;
 }
@@ -687,14 +706,7 @@ extern "C" int sp_weights_updated(sp_handle e, int layer) {
     if (e->failed) return SP_ERR_STATE;
     const int L = e->desc.n_layers;
     if (layer < -1 || layer >= L) return fail(e, SP_ERR_INVALID_ARG, "layer %d out of range", layer);
-    if (!e->weights_change) {
-        // Slots that keep their layer have recorded nothing so far: one event behind all that is enqueued stands in for
-        // their passes, later passes record their own.
-        SP_HIP(e, hipEventRecord(e->ev_updated, e->compute));
-        for (int u = 0; u < e->n_units; ++u)
-            if (!e->layer_done[u]) e->layer_done[u] = e->ev_updated;
-        e->weights_change = true;
-    }
+    e->update_pending = true;
     const int lo = layer < 0 ? 0 : layer, hi = layer < 0 ? L : layer + 1;
     for (int u = lo * e->units; u < hi * e->units; ++u) e->sched.invalidate(u);
     return SP_OK;

@@ -204,6 +204,55 @@ static void test_updates_of_kept_layers() {
     printf("ok updates of kept layers\n");
 }
 
+// sp_weights_updated works in host order only: it enqueues nothing and queries no stream, so it cannot fail for the
+// device's reasons and does not join a capture that is running.
+static void test_update_is_host_work() {
+    const int B = 1, S = 8;
+    const char* apis[] = {"hipEventRecord", "hipStreamWaitEvent", "hipMemcpyAsync", "launch"};
+    Rig r(SP_DECODER_SWIGLU_RMS, 4, B, S);
+    const std::vector<float> base = forward(r, 8, 8, 0, B, S);
+    Handle H(r, 8, 1, 0);
+    std::vector<float> y(base.size());
+    CHECK(sp_forward(H.h, r.x.data(), y.data(), B, S) == SP_OK, "forward: %s", sp_last_error(H.h));
+    r.sync();
+    mock_count_reset();
+    for (const char* api : apis) mock_fail_nth(api, 1);
+    CHECK(sp_weights_updated(H.h, 2) == SP_OK, "weights_updated: %s", sp_last_error(H.h));
+    for (const char* api : apis) {
+        CHECK(mock_count(api) == 0, "weights_updated called %s", api);
+        mock_fail_nth(api, 0);
+    }
+    // Under capture the copies of updated layers cannot be fenced against eager passes: refused before anything is
+    // enqueued, and the handle works on.
+    mock_stream_capture(r.compute, 1);
+    CHECK(sp_weights_updated(H.h, 3) == SP_OK, "weights_updated under capture: %s", sp_last_error(H.h));
+    mock_count_reset();
+    CHECK(sp_forward(H.h, r.x.data(), y.data(), B, S) == SP_ERR_STATE, "a captured pass behind an update");
+    for (const char* api : apis) CHECK(mock_count(api) == 0, "the refused pass called %s", api);
+    mock_stream_capture(r.compute, 0);
+    for (int i = 0; i < 2; ++i) {
+        y.assign(y.size(), -1.f);
+        CHECK(sp_forward(H.h, r.x.data(), y.data(), B, S) == SP_OK, "eager after: %s", sp_last_error(H.h));
+        r.sync();
+        CHECK(same(y, base), "the pass after an update differs");
+    }
+    sp_stats st;
+    st.struct_size = sizeof(st);
+    CHECK(sp_get_stats(H.h, &st) == SP_OK && st.h2d_copies == 4 + 2, "copies of the updated layers: %llu", (unsigned long long)st.h2d_copies);
+    // a handle's first pass needs no fence: an update in front of it changes nothing for a capture
+    Handle F(r, 8, 1, 0);
+    CHECK(sp_weights_updated(F.h, -1) == SP_OK, "fresh handle");
+    mock_stream_capture(r.compute, 1);
+    CHECK(sp_forward(F.h, r.x.data(), y.data(), B, S) == SP_OK, "first pass under capture: %s", sp_last_error(F.h));
+    // nor does a pass whose predecessors are part of the same capture
+    CHECK(sp_weights_updated(F.h, 1) == SP_OK, "weights_updated under capture");
+    CHECK(sp_forward(F.h, r.x.data(), y.data(), B, S) == SP_OK, "second pass under capture: %s", sp_last_error(F.h));
+    mock_stream_capture(r.compute, 0);
+    r.sync();
+    CHECK(same(y, base), "the captured first pass differs");
+    printf("ok updates are host work\n");
+}
+
 struct StepOut {
     std::vector<float> y, dx;
     float loss = 0;
@@ -540,6 +589,7 @@ int main(int argc, char** argv) {
     test_run_ahead_with_forwards_between_steps();
     test_forward_under_capture();
     test_updates_of_kept_layers();
+    test_update_is_host_work();
     test_steps_of_several_handles();
     test_decode();
     test_injected_failures(false);

@@ -50,7 +50,7 @@ def test_engine_under_address_and_undefined_sanitizers(tmp_path):
     assert "ERROR: AddressSanitizer" not in out and "LeakSanitizer" not in out and "runtime error" not in out, out[-4000:]
     for line in ("ok forward windows arch 0", "ok forward windows arch 1", "ok training arch 0", "ok training arch 1",
                  "ok large gradients arch 0", "ok large gradients arch 1", "ok run-ahead with forwards between steps",
-                 "ok forward under capture", "ok updates of kept layers", "ok steps of several handles",
+                 "ok forward under capture", "ok updates of kept layers", "ok updates are host work", "ok steps of several handles",
                  "ok decode", "ok injected hipMemcpyAsync failures (forward)", "ok injected launch failures (training step)",
                  "ok injected event-creation failures"):
         assert line in r.stdout, line
