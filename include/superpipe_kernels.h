@@ -79,6 +79,12 @@ int spk_kv_append(void* stream, const uint16_t* qkv, uint16_t* kt, uint16_t* v, 
 int spk_decode_attention(void* stream, const uint16_t* qkv, const uint16_t* kt, const uint16_t* v, uint16_t* o,
                          int B, int n, int max_len, int Hq, int Hkv, int hd);
 
+/* How the attention of a decode step (sp_decode) over n cached positions is cut up (host-only query, nothing is
+ * launched; the launch itself asks the same function): out4 (host) = {splits of the positions, positions per split,
+ * query heads per work-group, waves per split}.  Where the handle's budget leaves no room for the splits' partial
+ * results, splits and waves are the same and a work-group serves one query head. */
+int spk_decode_plan(int B, int n, int Hq, int Hkv, int* out4);
+
 /* ---- backward steps (training, Sec. 3.3) ---- */
 
 /* loss[0] = mean((y-t)^2) over n fp32 elements; dy fp32 [n] = 2 (y-t)/n; dy_bf16 the same rounded.

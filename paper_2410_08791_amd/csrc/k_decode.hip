@@ -378,10 +378,12 @@ hipError_t launch_one(hipStream_t st, const DecodeCall& c, int splits, int per) 
 
 // Splits, query heads per work-group and waves.  Splits and waves, which the order of the sums depends on, follow
 // from the shapes alone; without a scratch for the splits' rows G is 1.
-//   splits: none below 1024 positions (they would save less than the second launch costs).  Above, as many as fill the
-//     chip twice over, with at least 256 positions each, and beyond 16 of them with 512 -- more rows of partial
-//     results cost the second launch more than shorter splits save -- and no more rows than decode_scratch_floats counts.
-//   G: the fewest heads whose work-groups still fit one round of the chip (splits: two rounds of small ones; else 256, or
+//   splits: none below 1024 positions (they would save less than the second launch costs).  Above, there are two plans.
+//     Coarse: enough splits to fill the chip once, of at least 512 positions, in work-groups of eight waves.
+//     Fine: as many as fill it twice, with at least 256 positions each, and beyond 16 of them with 512 -- more rows of
+//     partial results cost the second launch more than shorter splits save -- in work-groups of two or four waves.
+//     Neither has more rows than decode_scratch_floats counts.
+//   G: the fewest heads whose work-groups still fit one round of the chip (fine: two rounds of small ones; else 256, or
 //     1024 of two waves); a group's cache is then read again through the L2, which costs less than idle CUs.  Always
 //     sharing it cost, us: 1 x 64/8 heads of 128 over 500 positions 34.3 against 9.1, 4 x 64/8 over 800 38.6 against
 //     19.5; never sharing it 32 x 32/8 over 500 39.5 against 21.  More than four heads per work-group spilled registers
@@ -389,35 +391,63 @@ hipError_t launch_one(hipStream_t st, const DecodeCall& c, int splits, int per) 
 //   NW: a wave with less than a step of 128 positions idles in its loads, and every wave has its part in the
 //     merge: 64 x 32 heads over 16 positions 42.6 us with eight waves, 15.8 with two.  Several rounds of work-groups
 //     of a split launch overlap better in small ones (8 x 64/8 over 4096, G = 4: four waves 45, two 39).
+// Which of the two, by the coarse plan's work-groups (us, coarse and fine):
+//   up to 120, not half the chip, or more than 256, a second round: fine (2 x 16/4 heads of 128 over 1955 positions 11.6
+//     and 9.4, 8 x 48/12 over 1779 33.5 and 25.0) -- but not where the coarse one all but fills two rounds and the fine
+//     one, with its larger head blocks, would begin a third (38 x 24/3 of 64 over 1053 23.4 and 24.3).
+//   between: coarse.  The fine plan's work-groups, not many more than 256 of them or with the heads that read one cache
+//     on different XCDs, took up to 1.39 times as long (2 x 8/2 heads of 128 over 8649 positions 13.3 and 18.5, 4 x 32/4
+//     of 64 over 2139 11.0 and 14.3) as often as they were quicker.  Not so where they all but fill two rounds and share
+//     a cache in multiples of eight splits: ids go round the eight XCDs, so the heads of a split then meet in
+//     one L2 (2 x 32/8 of 128 over 8191 22.9 and 20.5, over 1813 15.1 and 11.3).  For the same reason a coarse plan of more
+//     than a round in such splits stays where the fine one has none (2 x 64/8 of 128 over 13506 42.4 and 46.4).
+// On 200 shapes drawn after the rule stood: 5.9 % quicker than coarse plans alone on average, none more than 2 % slower;
+// without a scratch 4.3 %, slowest 9 x 12/6 of 64 over 3765 28.2 and 30.7 (three turns for two).  Fine plans alone, on 179
+// others: 7 %, but 42 slower by more than 2 %.
+// Without a scratch one work-group runs 16 / NW splits of a head at a time: where the coarse plan needs one turn, a fine
+// one for a second round needs no more (2 x 44/44 heads of 64 over 1540 positions, no scratch: 14.5 us in three splits,
+// 18.6 in five of four waves).
 // One split: against 258 shapes (1..64 sequences, groups of 1 to 8, 20..16000 positions) 3.6 % off the best of all
-// combinations on average.  Several: against 57 shapes (1..29 sequences, 2..64 heads, 1024..14652 positions) 3.5 % off
-// the best; splits of 512 positions in work-groups of up to eight waves that filled the chip once, which left a wave 72
-// positions of a step of 128, were 9.5 % off.  us, before and after: 2 x 32/8 heads of 128 over 8191 positions
-// 23.0 and 20.5, 16 x 32/8 over 2000 37.2 and 30.9, 4 x 36/9 of 64 over 5580 24.0 and 19.7; slowest 4 x 28/7 over 3355
-// 19.6 and 20.8.
+// combinations on average.
 struct DecodePlan { int splits, per, G, NW; };
-DecodePlan plan_decode(const DecodeCall& c) {
-    const int heads = c.B * c.Hkv, grp = c.Hq / c.Hkv;
+long decode_groups(const DecodeCall& c, int G, int splits) { return (long)c.B * c.Hkv * ((c.Hq / c.Hkv + G - 1) / G) * splits; }
+
+DecodePlan plan_splits(const DecodeCall& c, int splits, bool fine) {
+    const int grp = c.Hq / c.Hkv;
     DecodePlan p;
-    p.splits = 1;
-    if (!c.one_split && c.n >= 1024)
-        p.splits = std::max(std::min(std::min(kDecodeSplitGroups / heads, (c.n + 255) / 256), std::max(16, (c.n + 511) / 512)), 1);
-    p.per = std::max(((c.n + p.splits - 1) / p.splits + 63) / 64 * 64, 64);
+    p.per = std::max(((c.n + splits - 1) / splits + 63) / 64 * 64, 64);
     p.splits = std::max((c.n + p.per - 1) / p.per, 1);           // none is empty
-    auto groups = [&](int G) { return (long)heads * ((grp + G - 1) / G) * p.splits; };
-    const bool split = p.splits > 1;
-    p.NW = split ? (p.per <= 256 ? 2 : 4) : p.per <= 128 ? 2 : p.per <= 400 ? 4 : 8;
+    p.NW = fine ? (p.per <= 256 ? 2 : 4) : p.per <= 128 ? 2 : p.per <= 400 ? 4 : 8;
     p.G = 1;
-    while (p.G < 4 && p.G < grp && groups(p.G) > (split ? 512 : p.NW == 2 ? 1024 : 256)) p.G *= 2;
-    if (split && p.G == 4 && groups(4) > 512) p.NW = 2;
+    while (p.G < 4 && p.G < grp && decode_groups(c, p.G, p.splits) > (fine ? 512 : p.NW == 2 ? 1024 : 256)) p.G *= 2;
+    const long groups = decode_groups(c, p.G, p.splits);
+    if (p.splits > 1 && groups > (fine ? 512 : 256)) p.NW = p.G == 4 && groups > 512 ? 2 : fine ? p.NW : 4;
     return p;
+}
+
+DecodePlan plan_decode(const DecodeCall& c) {
+    if (c.one_split || c.n < 1024) return plan_splits(c, 1, false);
+    const int room = std::max(kDecodeSplitGroups / (c.B * c.Hkv), 1);
+    const DecodePlan coarse = plan_splits(c, std::min(room, c.n / 512), false);
+    const int splits = std::min(std::min(room, (c.n + 255) / 256), std::max(16, (c.n + 511) / 512));
+    if (splits == 1) return coarse;
+    DecodePlan fine = plan_splits(c, splits, true);
+    const long in_coarse = decode_groups(c, coarse.G, coarse.splits), in_fine = decode_groups(c, fine.G, fine.splits);
+    const int grp = c.Hq / c.Hkv;
+    if (in_coarse > 120 && in_coarse <= 256) return fine.splits % 8 == 0 && fine.G < grp && in_fine >= 448 ? fine : coarse;
+    if (in_coarse > 256 && coarse.splits % 8 == 0 && coarse.G < grp && fine.splits % 8) return coarse;
+    if (in_coarse > 448 && in_coarse <= 512 && in_fine > 512) return coarse;
+    const int turn = 16 / fine.NW;
+    if (in_coarse > 256 && coarse.splits <= 16 / coarse.NW && fine.splits > turn) fine = plan_splits(c, turn, true);
+    return fine;
 }
 
 template <int HD>
 hipError_t launch_decode(hipStream_t st, const DecodeCall& c) {
     const DecodePlan p = plan_decode(c);
     if (p.splits > 1 && !c.part)
-        return p.NW == 2 ? launch_one<HD, 1, 2, 8>(st, c, p.splits, p.per) : launch_one<HD, 1, 4, 4>(st, c, p.splits, p.per);
+        return p.NW == 2 ? launch_one<HD, 1, 2, 8>(st, c, p.splits, p.per) : p.NW == 4 ? launch_one<HD, 1, 4, 4>(st, c, p.splits, p.per)
+                                                                                       : launch_one<HD, 1, 8, 2>(st, c, p.splits, p.per);
 #define SP_DECODE(g, w) if (p.G == g && p.NW == w) return launch_one<HD, g, w, 1>(st, c, p.splits, p.per);
     SP_DECODE(1, 2) SP_DECODE(1, 4) SP_DECODE(1, 8) SP_DECODE(2, 2) SP_DECODE(2, 4) SP_DECODE(2, 8) SP_DECODE(4, 2) SP_DECODE(4, 4) SP_DECODE(4, 8)
 #undef SP_DECODE
@@ -436,6 +466,13 @@ hipError_t spk_launch_kv_append(hipStream_t st, const bf16_t* qkv, int ld_qkv, b
     else
         kv_append_kernel<false><<<grid, 256, 0, st>>>(qkv, ld_qkv, kt, v, S, pos0, Hq, Hkv, hd, max_len);
     return hipGetLastError();
+}
+
+void spk_decode_plan_host(int B, int n, int Hq, int Hkv, int* out4) {
+    DecodeCall c{};
+    c.B = B; c.n = n; c.Hq = Hq; c.Hkv = Hkv;
+    const DecodePlan p = plan_decode(c);
+    out4[0] = p.splits; out4[1] = p.per; out4[2] = p.G; out4[3] = p.NW;
 }
 
 static hipError_t decode_step(hipStream_t st, const DecodeCall& c, int hd) {

@@ -101,6 +101,10 @@ hipError_t spk_launch_decode_attention(hipStream_t st, const bf16_t* qkv, int ld
                                        const bf16_t* v, bf16_t* o, int ld_o, int B, int n, int max_len, int Hq,
                                        int Hkv, int hd);
 
+// What a decode step over n cached positions runs (host code, no launch): splits, positions per split, query heads per
+// work-group, waves per split.
+void spk_decode_plan_host(int B, int n, int Hq, int Hkv, int* out4);
+
 hipError_t spk_launch_copy_f32(hipStream_t st, const float* src, float* dst, size_t n);
 hipError_t spk_launch_fill_u32(hipStream_t st, uint32_t* dst, uint32_t v, size_t n);
 // A one-wave kernel that idles for about `micros` microseconds (at most SPK_SPIN_MAX_US) and exits.

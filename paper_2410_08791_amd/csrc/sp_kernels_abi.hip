@@ -67,6 +67,12 @@ extern "C" int spk_decode_attention(void* stream, const uint16_t* qkv, const uin
                                           max_len, Hq, Hkv, hd));
 }
 
+extern "C" int spk_decode_plan(int B, int n, int Hq, int Hkv, int* out4) {
+    if (!out4 || B < 1 || n < 0 || n > kDecodeMaxLen || Hkv < 1 || Hq < Hkv || Hq % Hkv) return SP_ERR_INVALID_ARG;
+    spk_decode_plan_host(B, n, Hq, Hkv, out4);
+    return SP_OK;
+}
+
 extern "C" int spk_mse(void* stream, const float* y, const float* t, float* dy, uint16_t* dyb, float* scratch,
                        float* loss, size_t n) {
     if (!y || !t || !dy || !dyb || !scratch || !loss || n == 0) return SP_ERR_INVALID_ARG;

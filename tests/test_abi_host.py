@@ -215,6 +215,53 @@ def test_create_argument_errors_without_a_device():
     assert sp.sp_get_stats(fake, C.byref(sp.sp_stats())) == sp.SP_ERR_STATE
 
 
+def decode_plan(B, n, Hq, Hkv):
+    out = (C.c_int * 4)()
+    assert sp.lib.spk_decode_plan(B, n, Hq, Hkv, out) == sp.SP_OK
+    return tuple(out)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,plan", [
+    # (sequences, query and key/value heads, cached positions) -> splits, positions per split, heads per work-group, waves.
+    # The shapes of the GPU tests of the decode step, each named there for what this list pins.
+    (2, 8, 8, 1023, (1, 1024, 1, 8)), (3, 6, 2, 1024, (4, 256, 1, 2)), (1, 4, 1, 1021, (1, 1024, 1, 8)),
+    (1, 4, 1, 1024, (4, 256, 1, 2)), (1, 4, 1, 1025, (5, 256, 1, 2)), (2, 6, 2, 1534, (6, 256, 1, 2)),
+    (2, 6, 2, 1537, (7, 256, 1, 2)), (1, 16, 1, 1087, (5, 256, 1, 2)), (1, 8, 1, 509, (1, 512, 1, 8)),
+    (1, 4, 1, 4096, (16, 256, 1, 2)), (1, 4, 1, 4097, (13, 320, 1, 4)), (1, 1, 1, 4608, (15, 320, 1, 4)),
+    (1, 4, 1, 8191, (16, 512, 1, 4)), (1, 2, 1, 8193, (17, 512, 1, 4)), (1, 2, 1, 32767, (64, 512, 1, 4)),
+    (16, 16, 8, 4100, (4, 1088, 2, 4)), (2, 64, 8, 8300, (15, 576, 4, 4)), (8, 64, 8, 4100, (8, 576, 4, 2)),
+    (1, 32, 32, 8300, (15, 576, 1, 4)), (2, 32, 16, 8300, (15, 576, 2, 4)), (3, 8, 2, 1281, (6, 256, 1, 2)),
+    # between 121 and 256 work-groups of eight waves: those, unless the finer plan's share a cache inside an XCD and fill
+    # two rounds
+    (6, 12, 6, 1100, (2, 576, 1, 8)), (2, 32, 8, 8300, (15, 576, 4, 8)), (11, 12, 3, 1024, (2, 512, 2, 8)),
+    (11, 24, 3, 1024, (2, 512, 4, 8)), (1, 64, 8, 1024, (2, 512, 1, 8)), (2, 32, 8, 8191, (16, 512, 2, 4)),
+    (2, 56, 7, 1918, (8, 256, 2, 2)), (12, 24, 3, 5058, (14, 384, 4, 2)),
+    (2, 64, 8, 13506, (24, 576, 4, 2)), (2, 8, 2, 8649, (16, 576, 1, 8)), (4, 32, 4, 2139, (4, 576, 2, 8)),
+    # just below and above those limits: 5 x 12 x 2 = 120 work-groups, 11 x 11 x 1 x 1, 256 and 257
+    (5, 12, 12, 1100, (5, 256, 1, 2)), (11, 11, 11, 1100, (2, 576, 1, 8)), (8, 16, 16, 1100, (2, 576, 1, 8)),
+    (13, 10, 10, 1100, (3, 384, 1, 4)),
+    (13, 40, 10, 1024, (3, 384, 4, 4)), (2, 44, 44, 1574, (4, 448, 1, 4)), (64, 64, 64, 32767, (1, 32768, 1, 8)),
+])
+def test_decode_plan(B, Hq, Hkv, n, plan):
+    assert decode_plan(B, n, Hq, Hkv) == plan
+
+
+def test_decode_plan_bounds():
+    """What the kernels and the scratch take: no empty split, every position in one, at most 64 rows per head (one lane of
+    the combination each), no more rows than the scratch counts, an instantiated work-group."""
+    for B in (1, 2, 3, 5, 8, 13, 31, 64):
+        for Hkv in (1, 2, 3, 5, 8, 12, 30, 64):
+            for g in (1, 2, 3, 4, 8, 16):
+                for n in (0, 1, 64, 127, 500, 1023, 1024, 1025, 1281, 2047, 4096, 4097, 8191, 8192, 8193, 16000, 32767):
+                    splits, per, G, NW = decode_plan(B, n, Hkv * g, Hkv)
+                    assert 1 <= splits <= 64 and per % 64 == 0 and splits * per >= n and (splits - 1) * per < max(n, 1)
+                    assert splits == 1 or B * Hkv * splits <= 512
+                    assert G in (1, 2, 4) and NW in (2, 4, 8) and (G == 1 or G // 2 < g)
+    for bad in ((0, 1, 1, 1), (1, -1, 1, 1), (1, 32769, 1, 1), (1, 1, 3, 2), (1, 1, 1, 0), (1, 1, 1, 2)):
+        assert sp.lib.spk_decode_plan(*bad, (C.c_int * 4)()) == sp.SP_ERR_INVALID_ARG
+    assert sp.lib.spk_decode_plan(1, 1, 1, 1, None) == sp.SP_ERR_INVALID_ARG
+
+
 def gemm_plan(epi, a_form, w_form, M, N):
     out = (C.c_int * 3)()
     assert sp.lib.spk_gemm_plan(epi, a_form, w_form, M, N, out) == sp.SP_OK

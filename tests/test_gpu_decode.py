@@ -173,11 +173,11 @@ def attention_only_layer(Hq, Hkv, hd, B):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,hd,pos,max_len", [
-    (1, 1, 1, 64, 4608, 4616),       # sixteen splits: two batches of rows in the combination
+    (1, 1, 1, 64, 4608, 4616),       # fifteen splits: two batches of rows in the combination
     (1, 4, 1, 128, 8191, 8192),      # sixteen, one group of four
     (1, 2, 1, 64, 32767, 32768),     # sixty-four, the longest cache
     (16, 16, 8, 64, 4100, 4104),     # four: the number of work-groups sets the limit
-    (2, 64, 8, 64, 8300, 8304),      # groups of eight as two blocks of four, two waves
+    (2, 64, 8, 64, 8300, 8304),      # groups of eight as two blocks of four, four waves
     (8, 64, 8, 64, 4100, 4104),      # the same, two waves
     (1, 32, 32, 64, 8300, 8304),     # one head per work-group, four waves
     (2, 32, 16, 64, 8300, 8304),     # two heads, four waves
@@ -225,9 +225,16 @@ def test_decode_step_over_a_long_cache(B, Hq, Hkv, hd, pos, max_len):
     (1, 4, 1, 64, 4096, 4104),       # sixteen splits of 256 positions, two waves
     (1, 4, 1, 128, 4097, 4104),      # the first that take four waves, the last split short
     (1, 2, 1, 64, 8193, 8200),       # seventeen: the seventeenth row of partial results is a batch of its own
-    (2, 32, 8, 64, 8300, 8304),      # groups of four in one block, four waves
-    (6, 12, 6, 128, 1100, 1104),     # five splits, two waves
-    (3, 8, 2, 128, 1281, 1288),      # six, the last of one position
+    (2, 32, 8, 64, 8300, 8304),      # groups of four in one block, eight waves
+    (6, 12, 6, 128, 1100, 1104),     # the fewest work-groups but 121 that keep eight waves, one head each
+    (3, 8, 2, 128, 1281, 1288),      # six splits, the last of one position
+    (11, 12, 3, 128, 1024, 1032),    # two heads, eight waves
+    (11, 24, 3, 64, 1024, 1032),     # four heads, eight waves
+    (2, 32, 8, 64, 8191, 8192),      # two heads of four, four waves: sixteen splits, a cache's readers on one XCD
+    (2, 56, 7, 64, 1918, 1920),      # two heads of eight, two waves
+    (13, 40, 10, 64, 1024, 1032),    # four heads, four waves
+    (12, 24, 3, 64, 5058, 5064),     # four heads, more than two rounds
+    (2, 44, 44, 64, 1574, 1576),     # no fifth split of four waves
 ])
 def test_decode_step_edges_of_the_splits(B, Hq, Hkv, hd, pos, max_len):
     test_decode_step_over_a_long_cache(B, Hq, Hkv, hd, pos, max_len)
@@ -357,8 +364,8 @@ def test_decode_argument_errors(gen):
 
 
 @pytest.mark.parametrize("B,S,s0,Hq,Hkv,hd", [
-    (1, 1030, 1021, 4, 1, 128),     # from 1024 cached positions on in four splits; one group of four
-    (2, 1540, 1534, 6, 2, 64),      # six splits, a group of three (padded to four)
+    (1, 1030, 1021, 4, 1, 128),     # one split, four at 1024 cached positions, five from 1025 on; one group of four
+    (2, 1540, 1534, 6, 2, 64),      # six splits, seven from 1537 cached positions on; a group of three
     (1, 1090, 1087, 16, 1, 64),     # a group of sixteen: two head blocks read the cache, one stores
     (1, 515, 509, 8, 1, 128),       # one split, a group of eight
     (2, 10, 0, 2, 2, 128),          # the first positions: waves without any
