@@ -37,8 +37,8 @@ int spk_norm(void* stream, const float* h, const uint16_t* gain, const uint16_t*
  *                  1 = row index contiguous        (A[k*lda+m], W[k*ldw+n]).
  * tile: 0 = library heuristic; 1..4 force a block tile of the register-staged kernel (128x128, 128x256,
  *       256x256 with 4 waves, 256x256 with 8 waves), 5..8 of the LDS-DMA kernel (256x256, 128x256, 128x128,
- *       256x192 -- the last not with epilogue 3; when the rows of C are no multiple of 16 bytes a
- *       register-staged kernel runs instead), 10 the 256x320 tile of the LDS-DMA kernel (not with epilogue 3), 9 the small-tile kernel
+ *       256x192 -- the last not with epilogue 3; when the rows of C are no multiple of 16 bytes, or an operand's
+ *       leading dimension is negative or in the millions, a register-staged kernel runs instead), 10 the 256x320 tile of the LDS-DMA kernel (not with epilogue 3), 9 the small-tile kernel
  *       for M <= 64 rows (both forms 0; the heuristic's choice for such M) with its own choice of tile,
  *       11 / 12 / 13 the same with 16 / 32 / 64 rows per work-group, 14..20 its tiles for any M: 16x16,
  *       16x32, 32x32, 64x32, 64x64, 96x64, 64x128 (an operand of form 1: 16 and 18 only).
@@ -48,7 +48,8 @@ int spk_gemm(void* stream, int epilogue, const uint16_t* A, int lda, int a_form,
              int tile);
 
 /* What tile = 0 runs (host-only query, nothing is launched; the launch itself asks the same function, and the answer
- * depends on the arguments alone, never on addresses or on the streaming window): out3 (host) = {tile id of rows
+ * depends on the arguments alone, never on addresses or on the streaming window; operands with leading dimensions
+ * between 0 and the millions): out3 (host) = {tile id of rows
  * [0, body_rows), body_rows, tile id of rows [body_rows, M) or 0 when body_rows == M}. */
 int spk_gemm_resolve(int epilogue, int a_form, int w_form, int M, int N, int K, int ldc, int* out3);
 /* The part of that choice that M and N alone decide: with both forms 0 the large-tile plan (a launch too small for it,

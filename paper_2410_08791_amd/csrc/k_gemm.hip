@@ -9,7 +9,8 @@
 // that write LDS directly; every projection, forward and backward; v_mfma_f32_16x16x32_bf16) and gemm_kernel
 // (register staging: global loads for tile t+1 are issued before the MFMAs of tile t
 // and stored to the other buffer afterwards, one barrier per tile; takes the outputs
-// whose rows do not start on 16 bytes, which the other kernel's epilogue cannot write; 4 or 8 waves in a 2 x (waves/2)
+// whose rows do not start on 16 bytes, which the other kernel's epilogue cannot write, and operands beyond the reach of
+// its 32-bit lane offsets; 4 or 8 waves in a 2 x (waves/2)
 // grid, each with its share as 32x32 tiles of v_mfma_f32_32x32x16_bf16).
 //
 // The MFMA is issued "transposed" (weights as the A operand, activations as B)
@@ -921,13 +922,21 @@ GemmPlan resolve_gemm(int epi, bool wide, int a_form, int w_form, int M, int N, 
     return pl;
 }
 
+// Whether the lane offsets of the LDS-DMA kernel, 32-bit byte offsets from a tile's first row (contraction-contiguous) or
+// first contraction index, reach every element of the largest tile.  Views whose rows lie further apart (8.4 M elements
+// at 256 rows) or run backwards take the register-staged kernel, which forms 64-bit addresses.
+bool lanes_reach(const GemmArgs& g) {
+    auto reach = [](int form, int rows, long ld) { return ld >= 0 && (form == OP_KMAJOR ? (rows - 1) * ld + BK : (BK - 1) * ld + rows) <= 1L << 31; };
+    return reach(g.a_form, std::min(g.M, 256), g.lda) && reach(g.w_form, std::min(g.N, 320), g.ldw);
+}
+
 template <int EPI, int AFORM, int WFORM>
 hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
     constexpr bool KMAJOR = (AFORM == OP_KMAJOR && WFORM == OP_KMAJOR);
     constexpr int NOSWIGLU = EPI == EPI_SWIGLU_BF16 ? EPI_BF16 : EPI;   // tile 8 has an odd tile count per wave
     constexpr size_t CSZ = (EPI == EPI_RESID_F32 || EPI == EPI_F32) ? 4 : 2;
     // the LDS-DMA kernel writes C (and reads R) in 16-byte pieces of a row
-    const bool dma = (g.ldc * CSZ) % 16 == 0;
+    const bool dma = (g.ldc * CSZ) % 16 == 0 && lanes_reach(g);
     int tile = g.tile;
     auto small = [&](int id) { GemmArgs t = g; t.tile = id; return spk_launch_gemm_small(st, EPI, t); };
     if (tile == 9 || (tile >= 11 && tile <= 13)) {

@@ -315,6 +315,39 @@ def test_gemm_lds_dma_k_tiles(K, tile):
         assert np.all(np.abs(got - ref) <= tol + (0 if f32out else BF16_EPS * np.abs(ref))), (epi, a_form, w_form)
 
 
+@pytest.mark.parametrize("a_form,w_form,far,ld", [
+    (0, 0, "a", 8_421_512), (0, 0, "w", 8_421_512), (0, 1, "w", 34_087_048), (1, 1, "a", 34_087_048),   # 255 or 63 rows just past 4 GiB
+    (0, 0, "a", 8_421_448), (1, 1, "w", 34_086_968),                                                    # ... and just below
+    (0, 0, "a", -128), (0, 0, "w", -136), (0, 1, "w", -328), (1, 1, "a", -264),                         # rows in reverse order
+])
+@pytest.mark.parametrize("tile", [0, 5, 6, 8, 10])
+def test_gemm_rows_far_apart_or_in_reverse(tile, a_form, w_form, far, ld):
+    """Operands whose rows lie so far apart that an offset inside a tile passes 32 bits, and views with a negative stride:
+    every element of the product, whichever tile is asked for."""
+    M, N, K = 256, 320, 128
+    rng = np.random.default_rng(abs(ld) + tile)
+    Ab, A = rand_bf16(rng, (M, K))
+    Wb, W = rand_bf16(rng, (N, K), 0.1)
+    def place(bits, form, lead):                       # -> (buffer, address of element (0, 0), leading dimension)
+        rows = np.ascontiguousarray(bits.T if form else bits)
+        n, width = rows.shape
+        if not lead:
+            t = dev_u16(rows)
+            return t, t.data_ptr(), width
+        buf = torch.zeros((n - 1) * abs(lead) + width, dtype=torch.int16, device=DEV)
+        view = buf.as_strided((n, width), (abs(lead), 1))
+        view.copy_(dev_u16(rows if lead > 0 else rows[::-1].copy()))
+        return buf, buf.data_ptr() + (0 if lead > 0 else 2 * (n - 1) * -lead), lead
+    abuf, ap, lda = place(Ab, a_form, ld if far == "a" else 0)
+    wbuf, wp, ldw = place(Wb, w_form, ld if far == "w" else 0)
+    Cd = torch.full((M + 1, N), 7.0, dtype=torch.float32, device=DEV)
+    assert sp.spk_gemm(stream_ptr(), sp.EPI_F32, ap, lda, a_form, wp, ldw, w_form, ptr(Cd), N, None, 0, None, M, N, K, tile) == sp.SP_OK
+    sync()
+    ref = A @ W.T
+    assert bool((Cd[M] == 7).all())
+    assert np.max(np.abs(Cd[:M].cpu().numpy() - ref)) <= 2e-6 * np.sqrt(K) * np.max(np.abs(ref))      # as in test_gemm_transposed_operands
+
+
 @pytest.mark.parametrize("M,N,K", [(1024, 4096, 64), (2560, 640, 320), (640, 640, 512), (512, 2048, 64), (2072, 1032, 256), (264, 40, 1088),
                                    (1032, 2560, 128)])
 def test_gemm_transposed_operands_own_choice(M, N, K):
