@@ -377,7 +377,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_split_kernel(const bf16_t* __
     const int bx = job % nqb, h = (job / nqb) % (int)gridDim.y, b = job / (nqb * (int)gridDim.y);
     const int q0 = (causal ? nqb - 1 - bx : bx) * 32, qi = q0 + l32;
     const size_t tok0 = (size_t)b * S;
-    const bf16_t* kbase = qkv + tok0 * ld_qkv + (size_t)(Hq + h / (Hq / Hkv)) * HD;
+    [[maybe_unused]] const bf16_t* kbase = qkv + tok0 * ld_qkv + (size_t)(Hq + h / (Hq / Hkv)) * HD;
     unsigned char* sK = smem_split + wave * C::STAGE;
     unsigned char* sV = sK + C::TILE_BYTES;
 
@@ -522,12 +522,16 @@ hipError_t launch_hd(hipStream_t st, const bf16_t* qkv, bf16_t* o, float* lse, c
     // wave has more than one key tile to give away.  us, 128-query form and split form:
     //   one image, 257 tokens, 16 heads of 80  9.3 and 7.2, two images (288 work-groups) 9.5 and 13.2
     //   2 x 128 tokens, 4 heads of 64, causal 6.5 and 4.8;  1024 tokens, 16 heads of 64 19.3 and 12.5, twice as many 20.4 and 19.5
-    //   512 tokens, 16 heads of 128, causal 16.2 and 8.6, 32 heads 16.9 and 16.1;  64 tokens, 16 heads of 80 4.6 and 5.2
-    // Long causal heads of 128 gain up to two rounds: their first blocks have few tiles (1024 tokens, 16 heads 27.0 and
-    // 18.5; with 128 tokens x 64 heads 9.2 and 11.8).
+    //   512 tokens, 16 heads of 128, causal 16.2 and 8.6;  64 tokens, 16 heads of 80 4.6 and 5.2
+    // At head_dim 80, where either form writes its rows of ones first, a second tile of more than 40 keys: 65 tokens, 2
+    // heads 5.1 and 5.5; 97 tokens, 5 heads 5.9 and 6.2; 110 tokens, 5 heads 6.0 and 5.9.
+    // Long causal heads of 128 gain beyond one round, their first blocks have few tiles: up to one and a half from 512
+    // tokens on, two from 1024 (512 tokens, 24 heads 16.6 and 14.1; 777 tokens, 15 heads 21.4 and 19.2, 20 heads 21.6 and
+    // 22.3; 1024 tokens, 16 heads 26.7 and 18.7; with 128 tokens x 64 heads 9.2 and 11.8).
     const long groups = (long)((a.S + 31) / 32) * a.Hq * a.B;
-    const bool two = HD == 64 || (HD == 128 && a.causal && a.S >= 512);
-    if (a.S > KB && groups <= (two ? 512 : 256)) return launch_split<HD>(st, qkv, o, lse, a, sl2);
+    const bool long_causal = HD == 128 && a.causal && a.S >= 512;
+    const long most = HD == 64 || (long_causal && a.S >= 1024) ? 512 : long_causal ? 384 : 256;
+    if (a.S > (HD == 80 ? KB + 40 : KB) && groups <= most) return launch_split<HD>(st, qkv, o, lse, a, sl2);
     return launch_fwd<HD, 4>(st, qkv, o, lse, a, sl2);
 }
 

@@ -491,6 +491,57 @@ def test_attention_key_tiles_shared_by_waves(S, hd, Hq, Hkv, causal):
     assert np.max(np.abs(got - ref)) <= 3 * BF16_EPS * np.max(np.abs(ref))   # as in test_attention
 
 
+def attention_both(qkv, B, S, Hq, Hkv, hd, causal):
+    """Kernel output and log-sum-exp over qkv (float64 of bf16 values, [B * S, ...]), and the same in float64."""
+    nq, nk = Hq * hd, Hkv * hd
+    o = torch.full((B * S, nq), 0x7FC1, dtype=torch.int16, device=DEV)      # bf16 NaN where nothing is written
+    lse = torch.full((B, Hq, S), np.nan, dtype=torch.float32, device=DEV)
+    qd = torch.from_numpy(qkv).to(torch.bfloat16).to(DEV)
+    assert sp.spk_attention(stream_ptr(), ptr(qd), ptr(o), ptr(lse), B, S, Hq, Hkv, hd, causal) == sp.SP_OK
+    sync()
+    heads = lambda x, n: x.reshape(B, S, n, hd).transpose(0, 2, 1, 3)  # noqa: E731
+    q, k, v = heads(qkv[:, :nq], Hq), heads(qkv[:, nq:nq + nk], Hkv), heads(qkv[:, nq + nk:], Hkv)
+    k, v = np.repeat(k, Hq // Hkv, axis=1), np.repeat(v, Hq // Hkv, axis=1)
+    s = q @ k.transpose(0, 1, 3, 2) / np.sqrt(hd)
+    if causal:
+        s = np.where(np.arange(S)[None, :] <= np.arange(S)[:, None], s, -np.inf)
+    m = s.max(-1, keepdims=True)
+    e = np.exp(s - m)
+    ref = (e / e.sum(-1, keepdims=True)) @ v
+    return (bf16_vals(host_u16(o)), lse.cpu().numpy().astype(np.float64), ref.transpose(0, 2, 1, 3).reshape(B * S, nq),
+            (m + np.log(e.sum(-1, keepdims=True)))[..., 0])
+
+
+def check_attention(qkv, B, S, Hq, Hkv, hd, causal):
+    got, lse, ref, want = attention_both(qkv, B, S, Hq, Hkv, hd, causal)
+    assert np.max(np.abs(got - ref)) <= 3 * BF16_EPS * np.max(np.abs(ref))                    # as in test_attention
+    atol = 2e-4 + (2.0 ** -9 if hd == 80 else 0.0)
+    np.testing.assert_allclose(lse, want, rtol=0, atol=atol * max(1.0, np.abs(want).max()))
+
+
+def bf16_qkv(rng, B, S, Hq, Hkv, hd, grow=False):
+    """Random activations; grow: keys that grow over the sequence (shrink for even S), scores spread over tens of units."""
+    _, qkv = rand_bf16(rng, (B * S, (Hq + 2 * Hkv) * hd))
+    if grow:
+        f = np.linspace(0.1, 6.0, S)
+        qkv[:, Hq * hd:(Hq + Hkv) * hd] *= np.tile(f if S % 2 else f[::-1], B)[:, None]
+        qkv = torch.from_numpy(qkv).to(torch.bfloat16).to(torch.float64).numpy()
+    return qkv
+
+
+@pytest.mark.parametrize("B,S,Hq,hd,causal", [
+    (2, 256, 16, 80, 0), (1, 256, 33, 80, 0), (1, 256, 32, 80, 1), (3, 256, 11, 80, 1),      # 256 and 264 work-groups of 32 queries
+    (1, 104, 3, 80, 0), (1, 105, 3, 80, 0), (1, 104, 2, 80, 1), (1, 105, 2, 80, 1),          # the second tile's length
+    (1, 64, 3, 64, 0), (1, 65, 3, 64, 0), (1, 64, 3, 128, 1), (1, 65, 3, 128, 1),            # one tile, two
+    (2, 128, 64, 64, 0), (1, 128, 129, 64, 0), (4, 128, 32, 64, 1), (3, 128, 43, 64, 1),     # 512 and 516
+    (1, 256, 32, 128, 0), (1, 256, 33, 128, 0), (1, 511, 16, 128, 1), (1, 511, 17, 128, 1),  # 256, 264 and 272
+    (2, 512, 12, 128, 1), (1, 512, 25, 128, 1), (1, 1023, 12, 128, 1), (1, 1023, 13, 128, 1),  # 384, 400 and 416
+    (1, 1024, 16, 128, 1), (1, 1024, 17, 128, 1),                                             # 512 and 544
+])
+def test_attention_both_sides_of_the_limits(B, S, Hq, hd, causal):
+    check_attention(bf16_qkv(np.random.default_rng(S + Hq), B, S, Hq, Hq, hd), B, S, Hq, Hq, hd, causal)
+
+
 def test_attention_rejects_unsupported_head_dim():
     z = torch.zeros(1 << 16, dtype=torch.int16, device=DEV)
     assert sp.spk_attention(stream_ptr(), ptr(z), ptr(z), None, 1, 8, 2, 2, 48, 1) == sp.SP_ERR_INVALID_ARG
