@@ -405,12 +405,12 @@ def test_swiglu(T, f):
     (2, 33, 2, 2, 80, 1),       # head_dim 80 (padded 192-byte LDS rows), causal, less than one key tile
     (1, 1, 2, 1, 128, 0),
     (11, 520, 16, 4, 128, 1),   # enough work-groups for the paired causal blocks; ragged last key tile
-    # head_dim 80 around the query-block (96 / 128) and key-tile (64) boundaries: three-wave and
-    # four-wave work-groups, a last key tile of 1, 32, 33, 63 and 64 keys
+    # head_dim 80 around the query-block (32 / 128) and key-tile (64) boundaries, a last key tile of 1, 32, 33, 63 and
+    # 64 keys (few work-groups: from 105 tokens on 32 queries each)
     (2, 127, 2, 2, 80, 0), (1, 128, 2, 2, 80, 0), (2, 129, 2, 2, 80, 0), (1, 160, 2, 2, 80, 0), (1, 161, 2, 2, 80, 0),
     (2, 256, 2, 2, 80, 0), (2, 257, 16, 16, 80, 0), (1, 258, 2, 2, 80, 0), (1, 289, 4, 2, 80, 1), (1, 257, 2, 1, 80, 1),
     (1, 96, 2, 2, 80, 1), (1, 97, 2, 2, 80, 0),
-    # three-wave work-groups at the other head dims (S = 77: 3 blocks of 32; S = 520: 6 x 96 < 5 x 128)
+    # ragged blocks at the other head dims
     (2, 77, 2, 2, 128, 1), (1, 520, 4, 2, 64, 1), (2, 33, 2, 2, 64, 0), (1, 289, 2, 2, 64, 0),
 ])
 def test_attention(B, S, Hq, Hkv, hd, causal):
@@ -529,6 +529,19 @@ def bf16_qkv(rng, B, S, Hq, Hkv, hd, grow=False):
     return qkv
 
 
+@pytest.mark.parametrize("hd,group,causal", [(64, 1, 0), (64, 2, 1), (80, 1, 0), (80, 2, 1), (128, 1, 0), (128, 4, 1)])
+@pytest.mark.parametrize("S", [65, 95, 96, 97, 127, 129, 160, 161, 257, 289, 319])
+def test_attention_many_work_groups(S, hd, group, causal):
+    """Too many work-groups of 32 queries for the chip: 128 queries each, all waves over the same key tiles.  Last tiles of
+    1, 31, 32, 33 and 63 keys (half a tile is worked where no more is left), query blocks with idle waves, the reference
+    maximum moving late or never."""
+    blocks = (S + 31) // 32
+    heads = (512 // blocks // 2 + 1) * group // group + group
+    Hq = (heads + group - 1) // group * group
+    assert blocks * Hq * 2 > 512
+    check_attention(bf16_qkv(np.random.default_rng(S + hd), 2, S, Hq, Hq // group, hd, grow=True), 2, S, Hq, Hq // group, hd, causal)
+
+
 @pytest.mark.parametrize("B,S,Hq,hd,causal", [
     (2, 256, 16, 80, 0), (1, 256, 33, 80, 0), (1, 256, 32, 80, 1), (3, 256, 11, 80, 1),      # 256 and 264 work-groups of 32 queries
     (1, 104, 3, 80, 0), (1, 105, 3, 80, 0), (1, 104, 2, 80, 1), (1, 105, 2, 80, 1),          # the second tile's length
@@ -540,6 +553,33 @@ def bf16_qkv(rng, B, S, Hq, Hkv, hd, grow=False):
 ])
 def test_attention_both_sides_of_the_limits(B, S, Hq, hd, causal):
     check_attention(bf16_qkv(np.random.default_rng(S + Hq), B, S, Hq, Hq, hd), B, S, Hq, Hq, hd, causal)
+
+
+@pytest.mark.parametrize("hd", [64, 80, 128])
+@pytest.mark.parametrize("causal", [0, 1])
+def test_attention_infinite_and_nan_scores(hd, causal):
+    """Key tiles shared by waves: a key with a score of -inf takes no part, also where a wave sees no other; a NaN key reaches
+    the queries that see it and no other."""
+    B, S, H = 1, 321, 2
+    qkv = bf16_qkv(np.random.default_rng(hd), B, S, H, H, hd)
+    nq = H * hd
+    qkv[:, 0] = np.abs(qkv[:, 0]) + 0.5                      # first head's queries: a positive element for the infinite keys
+    off = np.r_[1:64, 128:192, 300]                          # (key 0 stays: a query that sees no finite score has no result)
+    qkv[off, nq] = -np.inf
+    qkv = torch.from_numpy(qkv).to(torch.bfloat16).to(torch.float64).numpy()     # + 0.5 left bf16
+    with np.errstate(invalid="ignore"):
+        got, lse, ref, want = attention_both(qkv, B, S, H, H, hd, causal)
+    assert np.all(np.isfinite(got)) and np.all(np.isfinite(lse))
+    assert np.max(np.abs(got - ref)) <= 3 * BF16_EPS * np.max(np.abs(ref))                    # as in test_attention
+    atol = 2e-4 + (2.0 ** -9 if hd == 80 else 0.0)
+    np.testing.assert_allclose(lse, want, rtol=0, atol=atol * max(1.0, np.abs(want).max()))
+    clean = got
+    qkv[200, nq + 1] = np.nan
+    with np.errstate(invalid="ignore"):
+        got, lse, ref, want = attention_both(qkv, B, S, H, H, hd, causal)
+    hit = np.isnan(ref)
+    assert hit.any() and np.array_equal(np.isnan(got), hit) and np.array_equal(np.isnan(lse), np.isnan(want))
+    assert np.array_equal(got[~hit], clean[~hit])
 
 
 def test_attention_rejects_unsupported_head_dim():
