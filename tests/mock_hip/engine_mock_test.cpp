@@ -178,28 +178,57 @@ static void test_forward_windows(int arch) {
 }
 
 // Slots that keep their layers record no event behind a compute until weights are updated: the copy of a rewritten layer
-// still waits for the passes enqueued before, in the first such pass and in later ones.
+// still waits for the passes enqueued before, in the first such pass and in later ones.  A resident stack, and one with two
+// pinned layers in front of its ring.  Forward passes of the latter are fenced by the ring's own copies as well (the copy
+// stream has waited for a later layer's compute); a backward pass ends on the pinned layers, so that the copy that follows
+// it has no such predecessor.
 static void test_updates_of_kept_layers() {
     const int B = 2, S = 8;
     for (int pinned = 0; pinned < 2; ++pinned) {
-        Rig r(SP_DECODER_SWIGLU_RMS, 4, B, S);
+        Rig r(SP_DECODER_SWIGLU_RMS, 6, B, S);
         const int k = pinned ? 1 : 8;
-        Handle H(r, k, 1, 0, 0, pinned ? 2 : 0);
-        CHECK(H.rc == SP_OK, "sp_create: %s", sp_last_error(nullptr));
-        if (H.rc != SP_OK) return;
-        std::vector<float> y[4];
-        for (auto& v : y) v.assign((size_t)B * S * 64, -1.f);
-        CHECK(sp_forward(H.h, r.x.data(), y[0].data(), B, S) == SP_OK, "forward");
-        for (int i = 1; i < 4; ++i) {
-            // the pass before has read the host blobs; its computes may still be running
-            r.sync();
+        auto kept = [&](Handle& H) {
+            CHECK(H.rc == SP_OK, "sp_create: %s", sp_last_error(nullptr));
+            if (H.rc != SP_OK) return false;
+            sp_stats st;
+            st.struct_size = sizeof(st);
+            CHECK(sp_get_stats(H.h, &st) == SP_OK && st.plan.n_pinned == (pinned ? 2 : 0) && st.plan.n_slots == (pinned ? 4 : 6), "plan: %d pinned of %d slots",
+                  st.plan.n_pinned, st.plan.n_slots);
+            return true;
+        };
+        {
+            Handle H(r, k, 1, 0, 0, pinned ? 2 : 0);
+            if (!kept(H)) return;
+            std::vector<float> y[4];
+            for (auto& v : y) v.assign((size_t)B * S * 64, -1.f);
             CHECK(sp_forward(H.h, r.x.data(), y[0].data(), B, S) == SP_OK, "forward");
-            CHECK(sp_weights_updated(H.h, 1) == SP_OK, "weights_updated");
-            CHECK(sp_forward(H.h, r.x.data(), y[i].data(), B, S) == SP_OK, "forward after an update");
+            for (int i = 1; i < 4; ++i) {
+                // the pass before has read the host blobs; its computes may still be running
+                r.sync();
+                CHECK(sp_forward(H.h, r.x.data(), y[0].data(), B, S) == SP_OK, "forward");
+                CHECK(sp_weights_updated(H.h, 1) == SP_OK, "weights_updated");
+                CHECK(sp_forward(H.h, r.x.data(), y[i].data(), B, S) == SP_OK, "forward after an update");
+            }
+            r.sync();
+            const std::vector<float> base = forward(r, 8, 8, 0, B, S);
+            for (auto& v : y) CHECK(same(v, base), "pinned %d: a pass around an update differs", pinned);
         }
-        r.sync();
-        const std::vector<float> base = forward(r, 8, 8, 0, B, S);
-        for (auto& v : y) CHECK(same(v, base), "pinned %d: a pass around an update differs", pinned);
+        {
+            Handle H(r, k, 1, SP_FLAG_TRAINING, 0, pinned ? 2 : 0);
+            if (!kept(H)) return;
+            std::vector<float> y0(r.x.size()), dx(r.x.size()), y((size_t)B * S * 64), base, base0;
+            float loss;
+            for (int i = 0; i < 4; ++i) {
+                CHECK(sp_forward_backward(H.h, r.x.data(), r.t.data(), y0.data(), &loss, dx.data(), r.grads.data(), B, S) == SP_OK, "step: %s",
+                      sp_last_error(H.h));
+                // layer 0's last use is the end of the step's backward, which may still be running
+                CHECK(sp_weights_updated(H.h, i % 2 ? -1 : 0) == SP_OK, "weights_updated");
+                CHECK(sp_forward(H.h, r.x.data(), y.data(), B, S) == SP_OK, "forward after an update");
+                r.sync();
+                if (base.empty()) { base = forward(r, 8, 8, 0, B, S); base0 = y0; }
+                CHECK(same(y, base) && same(y0, base0), "pinned %d: a forward behind a step and an update differs", pinned);
+            }
+        }
     }
     printf("ok updates of kept layers\n");
 }
