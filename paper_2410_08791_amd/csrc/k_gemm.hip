@@ -836,23 +836,23 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
     return best;
 }
 
-// Operands with the row index contiguous: the estimated time in us of a tile, as fitted to 79 shapes on every tile (rows
-// 64..22016, contraction 256..23808, weights not in the caches; rms 4-13 %): launch and prologue a, per unit (one
+// Operands with the row index contiguous: the estimated time in us of a tile, as fitted to some 300 shapes with the weights
+// transposed and 260 with both operands (rows 64..33536, contraction 64..23808, weights not in the caches; rms of the
+// LDS-DMA tiles 4-9 %, of the small ones 8-17 %): launch and prologue a, per unit (one
 // work-group on every CU) b and c per 1000 of K, w per MB of output.  A last round of the two-per-CU tiles that fills one
 // half of the slots counts `half` units.  The LDS-DMA tiles and the small ones (16, 18; not with the residual epilogue)
-// stand in one table, so that every pair is compared by measured time: the choice is 0.2 % (weights transposed) and
-// 0.3 % (both) off the best tile on average.  The table fitted to the two-stage form of the LDS-DMA kernel, whose lone
-// 128x128 tile on a CU waited for its loads (`half` 1.76), was 5.2 and 2.6 % off: dX 2304 x 1152 x 2944 35.8 us on
-// 128x256 tiles, 26.1 on 128x128; 1152 x 3072 x 15616 193 and 147; dW 1472 x 1472 x 7488 86 and 67.
+// stand in one table, so that every pair is compared by measured time.  On 171 and 131 other shapes the choice is 0.4 %
+// off the best tile on average, at most 14 and 7 %.  (A fit to 79 shapes was 2.0 and 0.9 % off on these, its small tiles up
+// to 30 %: 704 x 640 x 4864 23.6 us on 32x32 tiles, 18.3 on 64x64.)
 struct TileTime { int id, bm, bn, concurrent; float a, b, c, w, half; };
-constexpr TileTime kTimesKR[] = {{5, 256, 256, 256, 0.f, 3.117f, 19.05f, 0.319f, 1.f}, {10, 256, 320, 256, 1.575f, 0.f, 24.95f, 0.324f, 1.f},
-                                 {8, 256, 192, 256, 0.f, 3.118f, 15.77f, 0.255f, 1.f}, {6, 128, 256, 256, 0.f, 3.639f, 11.58f, 0.177f, 1.f},
-                                 {7, 128, 128, 512, 3.569f, 0.f, 7.213f, 0.107f, 1.08f}, {16, 32, 32, 512, 2.258f, 0.166f, 1.830f, 0.369f, 1.04f},
-                                 {18, 64, 64, 256, 1.240f, 1.711f, 3.608f, 0.461f, 1.f}};
-constexpr TileTime kTimesRR[] = {{5, 256, 256, 256, 6.181f, 0.f, 19.86f, 0.186f, 1.f}, {10, 256, 320, 256, 0.f, 5.736f, 25.28f, 0.125f, 1.f},
-                                 {8, 256, 192, 256, 4.116f, 1.893f, 16.28f, 0.139f, 1.f}, {6, 128, 256, 256, 3.699f, 0.f, 11.93f, 0.198f, 1.f},
-                                 {7, 128, 128, 512, 3.495f, 0.f, 7.371f, 0.145f, 1.04f}, {16, 32, 32, 512, 2.570f, 0.484f, 2.046f, 0.f, 1.12f},
-                                 {18, 64, 64, 256, 2.167f, 1.739f, 3.163f, 0.311f, 1.f}};
+constexpr TileTime kTimesKR[] = {{5, 256, 256, 256, 0.f, 3.884f, 18.928f, 0.279f, 1.f}, {10, 256, 320, 256, 1.291f, 2.627f, 25.057f, 0.22f, 1.f},
+                                 {8, 256, 192, 256, 0.f, 4.292f, 15.534f, 0.218f, 1.f}, {6, 128, 256, 256, 0.097f, 3.491f, 11.553f, 0.194f, 1.f},
+                                 {7, 128, 128, 512, 2.548f, 0.666f, 6.842f, 0.137f, 1.22f}, {16, 32, 32, 512, 2.599f, 0.033f, 2.102f, 0.22f, 0.9f},
+                                 {18, 64, 64, 256, 1.283f, 1.954f, 3.516f, 0.407f, 1.f}};
+constexpr TileTime kTimesRR[] = {{5, 256, 256, 256, 3.437f, 3.673f, 20.84f, 0.124f, 1.f}, {10, 256, 320, 256, 2.236f, 6.602f, 25.206f, 0.095f, 1.f},
+                                 {8, 256, 192, 256, 2.682f, 3.774f, 16.575f, 0.108f, 1.f}, {6, 128, 256, 256, 2.93f, 1.453f, 12.001f, 0.151f, 1.f},
+                                 {7, 128, 128, 512, 3.845f, 0.f, 7.384f, 0.129f, 1.02f}, {16, 32, 32, 512, 2.292f, 0.f, 2.31f, 0.443f, 1.02f},
+                                 {18, 64, 64, 256, 2.08f, 1.096f, 3.451f, 0.388f, 1.f}};
 
 int quickest_tile(int epi, int a_form, int M, int N, int K, float* us) {
     const bool small_ok = epi != EPI_RESID_F32;
