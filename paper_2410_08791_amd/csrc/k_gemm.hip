@@ -811,6 +811,10 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& g) {
 // ceil(tiles / concurrent) rounds of one tile's time; a tile's time is its area over a measured
 // relative efficiency (larger tiles move fewer operand bytes per MFMA).  Take the cheapest.
 // (Activation rows are contiguous in A, C and R, so a launch can be cut along M.)
+// The efficiencies, like the rate that turns a cost into us in resolve_gemm and the one in plan_large's tail, were measured
+// on this kernel with two stages everywhere; the tiles with a ring have gained more since than the 256x320 one.  No launch is
+// slower for it, but on 37 shapes the choice is 3.2 % off the best tile now (3260 x 896 x 2944 50.8 us on 96x64 tiles, 34.5
+// on 128x128; 4218 x 320 x 1152 14.5 and 11.7).
 struct TileCost { int id, bm, bn, concurrent; float eff; };
 constexpr TileCost kDmaTiles[] = {{5, 256, 256, 256, 1.00f}, {10, 256, 320, 256, 1.02f}, {8, 256, 192, 256, 0.85f},
                                   {6, 128, 256, 256, 0.84f}, {7, 128, 128, 512, 0.70f}};
@@ -915,8 +919,8 @@ GemmPlan resolve_gemm(int epi, bool wide, int a_form, int w_form, int M, int N, 
     else pl.tile = pick_tile(kRegTiles, M, N, epi, &cost);
     if (pl.tile == 9) return GemmPlan{small_id, M, 0};
     // Both estimates are fits with 10-18 % error, so the small tiles have to be cheaper by a tenth:
-    // over 180 shapes of up to 2560 rows the choice is within 1 % of the better kernel on average
-    // (2.1 times as fast as the large tiles alone) and in one of them slower than the large tiles.
+    // over 180 shapes of up to 2560 rows the choice was within 1 % of the better kernel on average
+    // (2.1 times as fast as the large tiles alone) and in one of them slower than the large tiles, when those had two stages.
     if (small_id && small_us < 0.9f * (4.5f + cost * (float)K * 4.55e-7f)) return GemmPlan{small_id, M, 0};
     if (pl.tail_tile == 9) pl.tail_tile = spk_small_gemm_tile(epi, a_form, w_form, M - pl.body_rows, N, K, &small_us);
     return pl;
@@ -933,7 +937,7 @@ bool lanes_reach(const GemmArgs& g) {
 template <int EPI, int AFORM, int WFORM>
 hipError_t launch_tile(hipStream_t st, const GemmArgs& g) {
     constexpr bool KMAJOR = (AFORM == OP_KMAJOR && WFORM == OP_KMAJOR);
-    constexpr int NOSWIGLU = EPI == EPI_SWIGLU_BF16 ? EPI_BF16 : EPI;   // tile 8 has an odd tile count per wave
+    constexpr int NOSWIGLU = EPI == EPI_SWIGLU_BF16 ? EPI_BF16 : EPI;   // tiles 8, 10: a wave's load blocks are no half of gate or up rows
     constexpr size_t CSZ = (EPI == EPI_RESID_F32 || EPI == EPI_F32) ? 4 : 2;
     // the LDS-DMA kernel writes C (and reads R) in 16-byte pieces of a row
     const bool dma = (g.ldc * CSZ) % 16 == 0 && lanes_reach(g);

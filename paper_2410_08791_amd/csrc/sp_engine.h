@@ -30,11 +30,12 @@ struct sp_engine {
     float* decode_part = nullptr;     // partial results of decode attention; nullptr: the budget leaves no room
     hipStream_t compute = nullptr, h2d = nullptr, d2h = nullptr;
     std::vector<const void*> blobs;   // pinned host weight blobs (never written)
-    // Cross-stream fences.  Every copy and every layer compute of a call records
-    // its own event (copy_ev[i] / comp_ev[j], i-th copy / j-th compute of the call);
-    // layer_loaded / layer_done point at the most recent one for a layer.  With
-    // SP_FLAG_TIMING the events carry timestamps and double as the per-layer trace,
-    // so tracing adds no operation to either stream.
+    // Cross-stream fences.  Every copy of a call, and every layer compute whose slot a
+    // copy may follow into, records its own event (copy_ev[i] / comp_ev[j], i-th copy /
+    // j-th compute of the call); layer_loaded / layer_done point at the most recent one
+    // for a layer.  With SP_FLAG_TIMING the events carry timestamps and double as the
+    // per-layer trace; every compute then records one, also out of a slot that keeps its
+    // layer.
     // The two pools are rings twice as long as the most operations one call can issue, and a
     // call continues where the previous one stopped: an event that an earlier call recorded --
     // the copy of a layer prefetched for this call, the compute of a slot's last user -- is not

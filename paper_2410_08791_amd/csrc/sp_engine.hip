@@ -79,9 +79,10 @@ constexpr uint64_t kMaxQueuedTraining = 1400, kResumeTraining = 350;
 constexpr size_t kThrottleRing = 256;
 // A record stops the stream for 4 to 6 us (tiny kernels 2.5 us each back to back, 6.4 with a record behind each), more
 // than a small kernel takes: a forward handle records after every fourth layer or so, a training one, whose host wait
-// also steers its gradient copies, after every operation.  With the fence of slots that keep their layer (HipSink::compute)
-// left out too, us a pass, before and after: one image through 16 ViT-H layers 1280 and 1148, eight sequences' token
-// through 8 layers of 4096 1007 and 946, two sequences' at 8191 positions through 4 496 and 464.
+// also steers its gradient copies, after every operation.  us a pass, with a mark behind every layer and a fence behind
+// every slot that keeps its layer (HipSink::compute), with fewer marks, with fewer fences, with both: one image through 16
+// ViT-H layers 1246, 1186, 1164, 1117; eight sequences' token through 8 layers of 4096 1011, 980, 971, 949; two sequences' at
+// 8191 positions through 4 483, 467, 461, 451.
 constexpr uint64_t kMarkForward = 64, kMarkTraining = 1;
 constexpr unsigned kPacketsForward = 16, kPacketsForwardTrain = 14, kPacketsBackward = 44;
 
