@@ -842,31 +842,35 @@ int pick_tile(const TileCost (&cand)[NC], int M, int N, int epi, float* cost_out
 
 // Operands with the row index contiguous: the estimated time in us of a tile, as fitted to some 300 shapes with the weights
 // transposed and 260 with both operands (rows 64..33536, contraction 64..23808, weights not in the caches; rms of the
-// LDS-DMA tiles 4-9 %, of the small ones 8-17 %): launch and prologue a, per unit (one
-// work-group on every CU) b and c per 1000 of K, w per MB of output.  A last round of the two-per-CU tiles that fills one
+// LDS-DMA tiles 4-9 %, of the small ones 5-10 %): launch and prologue a, per unit (one
+// work-group on every CU) b and c per 1000 of K, w per MB of output; the small tiles also ma and mw per MB of the A and W
+// operands, whose first reads so many short work-groups do not hide.  A last round of the two-per-CU tiles that fills one
 // half of the slots counts `half` units.  The LDS-DMA tiles and the small ones (16, 18; not with the residual epilogue)
-// stand in one table, so that every pair is compared by measured time.  On 171 and 131 other shapes the choice is 0.4 %
-// off the best tile on average, at most 14 and 7 %.  (A fit to 79 shapes was 2.0 and 0.9 % off on these, its small tiles up
-// to 30 %: 704 x 640 x 4864 23.6 us on 32x32 tiles, 18.3 on 64x64.)
-struct TileTime { int id, bm, bn, concurrent; float a, b, c, w, half; };
-constexpr TileTime kTimesKR[] = {{5, 256, 256, 256, 0.f, 3.884f, 18.928f, 0.279f, 1.f}, {10, 256, 320, 256, 1.291f, 2.627f, 25.057f, 0.22f, 1.f},
-                                 {8, 256, 192, 256, 0.f, 4.292f, 15.534f, 0.218f, 1.f}, {6, 128, 256, 256, 0.097f, 3.491f, 11.553f, 0.194f, 1.f},
-                                 {7, 128, 128, 512, 2.548f, 0.666f, 6.842f, 0.137f, 1.22f}, {16, 32, 32, 512, 2.599f, 0.033f, 2.102f, 0.22f, 0.9f},
-                                 {18, 64, 64, 256, 1.283f, 1.954f, 3.516f, 0.407f, 1.f}};
-constexpr TileTime kTimesRR[] = {{5, 256, 256, 256, 3.437f, 3.673f, 20.84f, 0.124f, 1.f}, {10, 256, 320, 256, 2.236f, 6.602f, 25.206f, 0.095f, 1.f},
-                                 {8, 256, 192, 256, 2.682f, 3.774f, 16.575f, 0.108f, 1.f}, {6, 128, 256, 256, 2.93f, 1.453f, 12.001f, 0.151f, 1.f},
-                                 {7, 128, 128, 512, 3.845f, 0.f, 7.384f, 0.129f, 1.02f}, {16, 32, 32, 512, 2.292f, 0.f, 2.31f, 0.443f, 1.02f},
-                                 {18, 64, 64, 256, 2.08f, 1.096f, 3.451f, 0.388f, 1.f}};
+// stand in one table, so that every pair is compared by measured time.  On 171 and 131 other shapes the choice is 0.4 and
+// 0.3 % off the best tile on average, at most 15 and 6 %.  (A fit to 79 shapes was 2.0 and 0.9 % off on these, its small tiles
+// up to 30 %: 704 x 640 x 4864 23.6 us on 32x32 tiles, 18.3 on 64x64.)
+struct TileTime { int id, bm, bn, concurrent; float a, b, c, w, half, ma, mw; };
+constexpr TileTime kTimesKR[] = {
+    {5, 256, 256, 256, 0.f, 3.884f, 18.928f, 0.279f, 1.f, 0.f, 0.f}, {10, 256, 320, 256, 1.291f, 2.627f, 25.057f, 0.22f, 1.f, 0.f, 0.f},
+    {8, 256, 192, 256, 0.f, 4.292f, 15.534f, 0.218f, 1.f, 0.f, 0.f}, {6, 128, 256, 256, 0.097f, 3.491f, 11.553f, 0.194f, 1.f, 0.f, 0.f},
+    {7, 128, 128, 512, 2.548f, 0.666f, 6.842f, 0.137f, 1.22f, 0.f, 0.f}, {16, 32, 32, 512, 2.194f, 0.342f, 1.558f, 0.f, 1.02f, 0.499f, 0.228f},
+    {18, 64, 64, 256, 1.388f, 2.138f, 2.876f, 0.214f, 1.f, 0.304f, 0.154f}};
+constexpr TileTime kTimesRR[] = {
+    {5, 256, 256, 256, 3.437f, 3.673f, 20.84f, 0.124f, 1.f, 0.f, 0.f}, {10, 256, 320, 256, 2.236f, 6.602f, 25.206f, 0.095f, 1.f, 0.f, 0.f},
+    {8, 256, 192, 256, 2.682f, 3.774f, 16.575f, 0.108f, 1.f, 0.f, 0.f}, {6, 128, 256, 256, 2.93f, 1.453f, 12.001f, 0.151f, 1.f, 0.f, 0.f},
+    {7, 128, 128, 512, 3.845f, 0.f, 7.384f, 0.129f, 1.02f, 0.f, 0.f}, {16, 32, 32, 512, 2.101f, 0.166f, 1.673f, 0.328f, 1.16f, 0.717f, 0.028f},
+    {18, 64, 64, 256, 1.474f, 2.039f, 2.446f, 0.168f, 1.f, 0.589f, 0.07f}};
 
 int quickest_tile(int epi, int a_form, int M, int N, int K, float* us) {
     const bool small_ok = epi != EPI_RESID_F32;
     const float out_mb = (float)M * (float)N * (epi == EPI_BF16 ? 2e-6f : 4e-6f);
+    const float a_mb = (float)M * (float)K * 2e-6f, w_mb = (float)N * (float)K * 2e-6f;
     int best = 0;
     for (const TileTime& t : a_form == OP_KMAJOR ? kTimesKR : kTimesRR) {
         if (t.id >= 14 && !small_ok) continue;
         const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), rem = tiles % t.concurrent;
         const float units = (float)(tiles / t.concurrent * (t.concurrent / 256)) + (rem == 0 ? 0.f : rem <= 256 ? t.half : (float)(t.concurrent / 256));
-        const float c = t.a + units * (t.b + t.c * (float)K * 1e-3f) + t.w * out_mb;
+        const float c = t.a + units * (t.b + t.c * (float)K * 1e-3f) + t.w * out_mb + t.ma * a_mb + t.mw * w_mb;
         if (!best || c < *us) { best = t.id; *us = c; }
     }
     return best;
