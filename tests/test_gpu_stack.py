@@ -433,3 +433,44 @@ def test_captured_resident_pass_replays_and_leaves_the_handle_usable():
         assert torch.equal(y, want)
     del g
     assert eng.destroy() == sp.SP_OK
+
+
+def test_update_of_weights_does_not_join_a_capture():
+    """sp_weights_updated while a pass of the handle is being captured: the graph replays as captured, a captured pass
+    behind it is refused and leaves the capture intact, and the next eager pass streams the rewritten layer in."""
+    w = synth.WORKLOADS["tiny"]
+    desc = sp.make_desc(w)
+    blobs, views = sp.pinned_blobs(w, desc)
+    xd = dev_f32(synth.make_input(w))
+    eng = sp.Engine(desc, blobs, w.n_layers, 1)
+    y, yg, flag = torch.empty_like(xd), torch.empty_like(xd), torch.zeros(1, device=DEV)
+    eng.forward(xd, y, w.batch, w.seq)
+    eng.sync()
+    want = y.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=eng.compute):
+        eng.forward(xd, yg, w.batch, w.seq)
+        eng.weights_updated(1)
+        with pytest.raises(sp.SuperpipeError) as ex:
+            eng.forward(xd, y, w.batch, w.seq)
+        flag.add_(1)
+    assert ex.value.code == sp.SP_ERR_STATE
+    for i in range(3):
+        yg.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(yg, want) and int(flag.item()) == i + 1
+    synth.fill_layer(views[1], w, 1, seed=w.seed + 1)
+    for _ in range(2):
+        y.fill_(float("nan"))
+        eng.forward(xd, y, w.batch, w.seq)
+        eng.sync()
+    del g
+    assert eng.destroy() == sp.SP_OK
+    fresh = sp.Engine(desc, blobs, 1, 1)
+    y2 = torch.empty_like(xd)
+    fresh.forward(xd, y2, w.batch, w.seq)
+    fresh.sync()
+    assert fresh.destroy() == sp.SP_OK
+    assert torch.equal(y, y2) and not torch.equal(y, want)
